@@ -730,7 +730,7 @@ def bench_autograd(args):
                 "n_hidden": H, "n_out": K, "lr": w["lr"], "step": "one epoch"},
         roofline={"bound": "alu", "achieved": achieved, "peak": PEAK["fp32"], "unit": "TFLOP/s",
                   "frac": achieved / PEAK["fp32"], "traffic": None, "traffic_unit": "bytes per launch",
-                  "kernel": "mlpk::k_forward_tiled + k_backward_rows + k_backward_sum + k_step (per epoch)",
+                  "kernel": "mlpk::k_forward_tiled + k_grad_sum (+ k_grad_reduce) + k_step (per epoch)",
                   "kernel_ms": kern * 1e3, "flops_per_launch": flops},
         graph={"value": N * gsteps / gwall, "ms_per_step": gwall * 1e3 / gsteps, "epochs": gsteps,
                "form": f"per epoch mlp_forward, mlp_backward (the library's MSE adjoint) and mlp_step as library "

@@ -5,11 +5,10 @@
 //   k_dense_fwd<ACT>  Y = act(X W^T + b); a workgroup computes 64 rows x 64
 //                     outputs, 16 rows per wave, on v_mfma_f32_16x16x4_f32
 //                     with X and W staged in LDS in chunks of 32 inputs
-//   k_dense_dz<ACT>   dZ = dY . act'(Y)   (act' from the layer's output)
-//   k_dense_wsum      gW[o][i] = sum_r dZ[r][o] X[r][i], gb[o] = sum_r dZ[r][o]:
-//                     one wave per parameter, lanes over rows, fixed butterfly
-//                     (bitwise repeatable)
-//   k_dense_dx        dX[r][i] = sum_o dZ[r][o] W[o][i], one thread per entry
+//   adjoint           grad.hpp: dZ = dY . act'(Y) (act' from the layer's
+//                     output) is formed where the gradient sums gW = dZ^T X,
+//                     gb = sum dZ and the optional dX = dZ W consume it; row
+//                     sums run in a fixed order (bitwise repeatable)
 //   k_update          theta <- theta - lr g over a packed parameter vector,
 //                     optionally Kahan-compensated
 //   k_mse_grad        the error of section 2.2 read as the mean squared error,
@@ -17,6 +16,7 @@
 //                     workgroup, threads strided over the entries, a fixed-order
 //                     block sum (bitwise repeatable)
 // ACT: 0 the sigmoid of Equation 1, 1 tanh.
+#include "grad.hpp"
 #include "mlp_device.hpp"
 
 namespace mlpk {
@@ -76,47 +76,6 @@ __global__ __launch_bounds__(256) void k_dense_fwd(int64_t n, int din, int dout,
   }
 }
 
-template <int ACT>
-__global__ __launch_bounds__(256) void k_dense_dz(int64_t m, const float *__restrict__ Y, const float *__restrict__ dY,
-                                                  float *__restrict__ dZ) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= m) return;
-  const float y = Y[q];
-  dZ[q] = dY[q] * (ACT == 1 ? 1.0f - y * y : y * (1.0f - y));
-}
-
-__global__ __launch_bounds__(256) void k_dense_wsum(int64_t n, int din, int dout, const float *__restrict__ X,
-                                                    const float *__restrict__ dZ, float *__restrict__ gW,
-                                                    float *__restrict__ gb) {
-  const int64_t q = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
-  const int lane = threadIdx.x & (kWave - 1);
-  const int64_t nw = (int64_t)dout * din;
-  if (q >= nw + dout) return;   // whole waves leave together
-  float s = 0.0f;
-  if (q < nw) {
-    const int o = (int)(q / din), i = (int)(q - (int64_t)o * din);
-    for (int64_t r = lane; r < n; r += kWave) s = fmaf(dZ[r * dout + o], X[r * din + i], s);
-    s = wave_sum(s);
-    if (lane == 0) gW[q] = s;
-  } else {
-    const int o = (int)(q - nw);
-    for (int64_t r = lane; r < n; r += kWave) s += dZ[r * dout + o];
-    s = wave_sum(s);
-    if (lane == 0) gb[o] = s;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_dense_dx(int64_t n, int din, int dout, const float *__restrict__ dZ,
-                                                  const float *__restrict__ W, float *__restrict__ dX) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n * din) return;
-  const int64_t r = q / din;
-  const int i = (int)(q - r * din);
-  float s = 0.0f;
-  for (int o = 0; o < dout; ++o) s = fmaf(dZ[r * dout + o], W[(int64_t)o * din + i], s);
-  dX[q] = s;
-}
-
 __global__ __launch_bounds__(256) void k_update(int64_t P, float *__restrict__ theta, const float *__restrict__ g,
                                                 float *__restrict__ comp, float lr) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -163,24 +122,16 @@ hipError_t launch_dense_forward(int64_t n, int din, int dout, const float *X, co
   return hipGetLastError();
 }
 
+// ws: n dout floats, for the row ranges' partial gradients ([gW | gb] each).
 hipError_t launch_dense_backward(int64_t n, int din, int dout, const float *X, const float *Y, const float *dY,
-                                 const float *W, int act, float *gW, float *gb, float *dX, float *dZ,
+                                 const float *W, int act, float *gW, float *gb, float *dX, float *ws,
                                  hipStream_t s) {
-  const int64_t m = n * dout;
-  if (act == 1)
-    hipLaunchKernelGGL(mlpk::k_dense_dz<1>, blocks_for(m, 256), dim3(256), 0, s, m, Y, dY, dZ);
-  else
-    hipLaunchKernelGGL(mlpk::k_dense_dz<0>, blocks_for(m, 256), dim3(256), 0, s, m, Y, dY, dZ);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(mlpk::k_dense_wsum, blocks_for((int64_t)dout * din + dout, 256 / mlpk::kWave), dim3(256), 0, s,
-                     n, din, dout, X, dZ, gW, gb);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (dX) {
-    hipLaunchKernelGGL(mlpk::k_dense_dx, blocks_for(n * din, 256), dim3(256), 0, s, n, din, dout, dZ, W, dX);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  return hipSuccess;
+  const mlpk::DenseDelta src{Y, dY, act};
+  const int64_t nW = (int64_t)dout * din, Q = nW + dout;
+  const mlpk::GradDst dst{{gW, gb, nullptr, nullptr, nullptr}, {nW, Q, Q, Q, Q}, 1.0f};
+  hipError_t e = launch_grad_sum(n, din, dout, X, src, gW, gb, ws, n * dout, Q, dst, s);
+  if (e != hipSuccess || !dX) return e;
+  return launch_grad_dx(n, din, dout, W, src, dX, s);
 }
 
 hipError_t launch_mse_grad(int64_t n, int k, const float *Y, const float *T, float *dY, float *loss, hipStream_t s) {

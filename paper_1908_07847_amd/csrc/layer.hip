@@ -9,13 +9,11 @@
 //                  lanes of a row (n_in <= 256, n_out <= 16)
 //  k_forward       one thread per row (any n_in): z1 = X W1^T + b1,
 //                  A = sigma(z1), Y = sigma(A W2^T + b2).
-//  k_backward_rows one thread per row: delta2 = dY . Y (1 - Y) (dY from the
-//                  caller, or the MSE reading 2 (Y - T) / (n K)),
-//                  delta1 = (delta2 W2) . A (1 - A); optional dX = delta1 W1;
-//                  writes delta1, delta2 and the row's squared error.
-//  k_backward_sum  one wave per parameter (plus one for the loss): lane
-//                  partial sums over the rows, then a fixed butterfly, so
-//                  the result is bitwise repeatable.
+//  backward        grad.hpp: the output deltas (dY from the caller, or the MSE
+//                  reading 2 (Y - T) / (n K)) and delta1 = (delta2 W2) .
+//                  A (1 - A) are formed where the gradient sums and the
+//                  optional dX = delta1 W1 consume them; row sums run in
+//                  a fixed order, so the result is bitwise repeatable.
 //  k_step          theta <- theta - lr g, optionally Kahan-compensated; with
 //                  a velocity buffer, heavy-ball momentum (v <- mu v + g,
 //                  theta <- theta - lr v).  Forward and backward take the
@@ -31,6 +29,7 @@
 //                  count does not depend on their order).
 #include <algorithm>
 
+#include "grad.hpp"
 #include "mlp_device.hpp"
 
 namespace mlpk {
@@ -126,83 +125,6 @@ __global__ __launch_bounds__(256) void k_forward_tiled(int64_t n, int D, int H, 
         if (l16 == 0 && r < rows) Y[(r0 + r) * K + k] = sigmoid(z2 + p.b2[k]);
       }
     }
-  }
-}
-
-__global__ __launch_bounds__(256) void k_backward_rows(
-    int64_t n, int64_t n_total, int D, int H, int K, const float *__restrict__ A, const float *__restrict__ Y,
-    const float *__restrict__ dY, const float *__restrict__ T, mlp_params p,
-    float *__restrict__ dX, float *__restrict__ d1_out, float *__restrict__ d2_out,
-    float *__restrict__ sq_out, int act) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n) return;
-  const float mse_scale = 2.0f / ((float)n_total * (float)K);
-  float sq = 0.0f;
-  for (int k = 0; k < K; ++k) {
-    float y = Y[r * K + k];
-    float g;
-    if (dY) {
-      g = dY[r * K + k];
-    } else {
-      float err = y - T[r * K + k];
-      sq += err * err;
-      g = mse_scale * err;
-    }
-    d2_out[r * K + k] = g * y * (1.0f - y);
-  }
-  sq_out[r] = sq;
-  for (int h = 0; h < H; ++h) {
-    float s = 0.0f;
-    for (int k = 0; k < K; ++k) s += d2_out[r * K + k] * p.W2[(int64_t)k * H + h];
-    float a = A[r * H + h];
-    d1_out[r * H + h] = act == 1 ? s * (1.0f - a * a) : s * a * (1.0f - a);
-  }
-  if (dX) {
-    for (int d = 0; d < D; ++d) {
-      float s = 0.0f;
-      for (int h = 0; h < H; ++h) s += d1_out[r * H + h] * p.W1[(int64_t)h * D + d];
-      dX[r * D + d] = s;
-    }
-  }
-}
-
-// One wave per parameter q in packed order [W1 | b1 | W2 | b2], plus q == P
-// for the loss: lane l sums rows l, l + 64, ... in order, then a fixed
-// butterfly adds the 64 lane sums, so the result is bitwise repeatable.
-__global__ __launch_bounds__(256) void k_backward_sum(
-    int64_t n, int64_t n_total, int accumulate, int D, int H, int K, const float *__restrict__ X,
-    const float *__restrict__ A, const float *__restrict__ d1, const float *__restrict__ d2,
-    const float *__restrict__ sq, mlp_params g, float *__restrict__ loss) {
-  const int64_t P = (int64_t)D * H + H + (int64_t)H * K + K;
-  const int64_t q = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
-  const int lane = threadIdx.x & (kWave - 1);
-  if (q > P) return;   // whole waves leave together
-  float s = 0.0f;
-  if (q < (int64_t)D * H) {
-    const int h = (int)(q / D), d = (int)(q - (int64_t)h * D);
-    for (int64_t r = lane; r < n; r += kWave) s += d1[r * H + h] * X[r * D + d];
-    s = wave_sum(s);
-    if (lane == 0) g.W1[q] = accumulate ? g.W1[q] + s : s;
-  } else if (q < (int64_t)D * H + H) {
-    const int h = (int)(q - (int64_t)D * H);
-    for (int64_t r = lane; r < n; r += kWave) s += d1[r * H + h];
-    s = wave_sum(s);
-    if (lane == 0) g.b1[h] = accumulate ? g.b1[h] + s : s;
-  } else if (q < (int64_t)D * H + H + (int64_t)H * K) {
-    const int64_t o = q - ((int64_t)D * H + H);
-    const int k = (int)(o / H), h = (int)(o - (int64_t)k * H);
-    for (int64_t r = lane; r < n; r += kWave) s += d2[r * K + k] * A[r * H + h];
-    s = wave_sum(s);
-    if (lane == 0) g.W2[o] = accumulate ? g.W2[o] + s : s;
-  } else if (q < P) {
-    const int k = (int)(q - ((int64_t)D * H + H + (int64_t)H * K));
-    for (int64_t r = lane; r < n; r += kWave) s += d2[r * K + k];
-    s = wave_sum(s);
-    if (lane == 0) g.b2[k] = accumulate ? g.b2[k] + s : s;
-  } else if (loss) {
-    for (int64_t r = lane; r < n; r += kWave) s += sq[r];
-    s = wave_sum(s) / ((float)n_total * (float)K);
-    if (lane == 0) loss[0] = accumulate ? loss[0] + s : s;
   }
 }
 
@@ -444,30 +366,28 @@ hipError_t launch_predict(int64_t n, int D, int H, int K, const float *X, mlp_pa
   return hipGetLastError();
 }
 
-// ws layout (floats): delta1 [chunk][H] | delta2 [chunk][K] | sq [chunk].  Rows
-// are processed in chunks of at most ws_rows; each chunk's sums are
-// added to the previous ones in chunk order (fixed, so still repeatable).
-hipError_t launch_backward(int64_t n, int64_t ws_rows, int D, int H, int K, const float *X,
+// ws: `ws_floats` floats for the row ranges' partial gradients (packed order
+// [W1 | b1 | W2 | b2 | loss] each).
+template <int KO>
+static hipError_t backward_ko(int64_t n, int64_t ws_floats, int D, int H, int K, const float *X, const float *A,
+                              const float *Y, const float *dY, const float *T, mlp_params p, mlp_params g, float *dX,
+                              float *loss, float *ws, int act, hipStream_t s) {
+  const float inv_nk = 1.0f / ((float)n * (float)K);
+  if (dY) loss = nullptr;
+  mlpk::HiddenDelta<KO> src{A, p.W2, Y, dY, T, K, act, 2.0f / ((float)n * (float)K), g.W2, g.b2, loss, inv_nk};
+  const int64_t oB1 = (int64_t)D * H, oW2 = oB1 + H, oB2 = oW2 + (int64_t)H * K, P = oB2 + K;
+  const mlpk::GradDst dst{{g.W1, g.b1, g.W2, g.b2, loss}, {oB1, oW2, oB2, P, P + 1}, inv_nk};
+  hipError_t e = launch_grad_sum(n, D, H, X, src, g.W1, g.b1, ws, ws_floats, P + 1, dst, s);
+  if (e != hipSuccess || !dX) return e;
+  return launch_grad_dx(n, D, H, p.W1, src, dX, s);
+}
+
+hipError_t launch_backward(int64_t n, int64_t ws_floats, int D, int H, int K, const float *X,
                            const float *A, const float *Y, const float *dY, const float *T,
                            mlp_params p, mlp_params g, float *dX, float *loss, float *ws, int act,
                            hipStream_t s) {
-  const int64_t chunk = std::min<int64_t>(n, ws_rows);
-  float *d1 = ws, *d2 = ws + chunk * H, *sq = d2 + chunk * K;
-  const int64_t P = (int64_t)D * H + H + (int64_t)H * K + K;
-  for (int64_t r0 = 0; r0 < n; r0 += chunk) {
-    const int64_t m = std::min(chunk, n - r0);
-    hipLaunchKernelGGL(mlpk::k_backward_rows, grid_for(m, 256), dim3(256), 0, s, m, n, D, H, K,
-                       A + r0 * H, Y + r0 * K, dY ? dY + r0 * K : nullptr, T ? T + r0 * K : nullptr,
-                       p, dX ? dX + r0 * D : nullptr, d1, d2, sq, act);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mlpk::k_backward_sum, grid_for(P + 1, 256 / mlpk::kWave), dim3(256), 0, s, m, n,
-                       r0 > 0 ? 1 : 0, D, H, K, X + r0 * D, A + r0 * H, d1, d2, sq, g,
-                       dY ? nullptr : loss);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  if (K <= 4) return backward_ko<4>(n, ws_floats, D, H, K, X, A, Y, dY, T, p, g, dX, loss, ws, act, s);
+  return backward_ko<mlpk::kLayerMaxOut>(n, ws_floats, D, H, K, X, A, Y, dY, T, p, g, dX, loss, ws, act, s);
 }
 
 hipError_t launch_step(int D, int H, int K, mlp_params p, mlp_params g, float *comp, float lr, float mu,

@@ -245,10 +245,10 @@ mlp_status mlp_backward(mlp_net *net, const float *X, const float *A, const floa
   if (!net->ws || net->ws_bytes < mlph::kStatusBytes + backward_ws_bytes(c))
     return fail(MLP_ERR_WORKSPACE, "backward needs %zu workspace bytes",
                 mlph::kStatusBytes + backward_ws_bytes(c));
-  const int64_t ws_rows = std::min<int64_t>(c.n_rows, mlph::kBackwardChunk);
+  const int64_t ws_floats = (int64_t)(backward_ws_bytes(c) / sizeof(float));
   // the workspace's head holds the status block of training launches
   float *scratch = reinterpret_cast<float *>(static_cast<char *>(net->ws) + mlph::kStatusBytes);
-  hipError_t e = mlph::launch_backward(n, ws_rows, c.n_in, c.n_hidden, c.n_out, X, A, Y, dY, T,
+  hipError_t e = mlph::launch_backward(n, ws_floats, c.n_in, c.n_hidden, c.n_out, X, A, Y, dY, T,
                                        net->theta, grads, dX, loss, scratch, act_of(c), (hipStream_t)stream);
   return e == hipSuccess ? MLP_OK : hip_fail(e, "mlp_backward launch");
 }

@@ -116,7 +116,8 @@ __device__ __forceinline__ float sum16(float v) {
 // Launch wrappers implemented in the .hip files and used by the host API.
 namespace mlph {
 
-// Rows of one pass of the generic backward kernels (bounds their workspace).
+// Rows whose deltas the backward workspace could hold: its size, min(n, this)
+// (H + K + 1) floats, bounds the partial gradients of the row ranges.
 constexpr int64_t kBackwardChunk = 16384;
 
 // Small-network trainer: one workgroup per net, all epochs in one launch.
@@ -139,7 +140,7 @@ hipError_t launch_small_train(const mlp_batch_item *items, mlp_batch_item one, i
 // Generic layer kernels (any sizes) for mlp_forward / mlp_backward / mlp_step.
 hipError_t launch_forward(int64_t n, int D, int H, int K, const float *X, mlp_params p, float *A,
                           float *Y, int act, hipStream_t s);
-hipError_t launch_backward(int64_t n, int64_t ws_rows, int D, int H, int K, const float *X,
+hipError_t launch_backward(int64_t n, int64_t ws_floats, int D, int H, int K, const float *X,
                            const float *A, const float *Y, const float *dY, const float *T,
                            mlp_params p, mlp_params g, float *dX, float *loss, float *ws, int act,
                            hipStream_t s);
@@ -151,7 +152,7 @@ hipError_t launch_predict(int64_t n, int D, int H, int K, const float *X, mlp_pa
 hipError_t launch_dense_forward(int64_t n, int din, int dout, const float *X, const float *W, const float *b,
                                 int act, float *Y, hipStream_t s);
 hipError_t launch_dense_backward(int64_t n, int din, int dout, const float *X, const float *Y, const float *dY,
-                                 const float *W, int act, float *gW, float *gb, float *dX, float *dZ,
+                                 const float *W, int act, float *gW, float *gb, float *dX, float *ws,
                                  hipStream_t s);
 hipError_t launch_update(int64_t P, float *theta, const float *g, float *comp, float lr, hipStream_t s);
 hipError_t launch_mse_grad(int64_t n, int k, const float *Y, const float *T, float *dY, float *loss, hipStream_t s);
