@@ -128,6 +128,203 @@ __global__ __launch_bounds__(256) void k_forward_tiled(int64_t n, int D, int H, 
   }
 }
 
+// Class of a row of outputs (or targets): the largest entry, the lowest
+// index on ties; a single output is a two-class net, class 1 above 1/2.
+__device__ __forceinline__ int argmax_row(const float *v, int K) {
+  if (K == 1) return v[0] > 0.5f ? 1 : 0;
+  int best = 0;
+  for (int k = 1; k < K; ++k)
+    if (v[k] > v[best]) best = k;   // strict: the lowest index wins ties
+  return best;
+}
+
+// Forward pass (and class predictions) for n_in <= 64 and at most 4 outputs.
+// A workgroup of 4 waves walks the rows, 32 per wave at a time (two 16-row
+// tiles that share every W1 operand and interleave their product chains):
+// the X operands go from global memory into registers, W1 | b1 | W2 sit in
+// LDS -- staged once per workgroup when the whole hidden layer fits kFwrHB
+// units, else block by block.  After the last hidden tile, lane 4 i + k of a
+// row group holds output k of row i, so one sigmoid per lane finishes four
+// rows, and the class (and the count against targets) comes from the same
+// registers.  The products, the activation and the output sums run in
+// k_forward_tiled's order, so the outputs are the same bits.
+// Bound: the float32 matrix cores (2 D H of the row's flops) and the vector
+// ALU of the activation about equally; the next rows' X loads overlap.
+// Staging X and W1 per 64 rows with an index division per element held
+// 1,048,576 rows of a 33-256-3 network at 582 us with the separate argmax.
+constexpr int kFwrHB = 256;
+
+struct PredictOut {
+  int32_t *labels;     // null: forward pass only
+  const float *T;      // null: no count
+  int32_t *correct;
+};
+
+__device__ __forceinline__ float quad_bcast(float v, int k) {
+  const int b = __builtin_bit_cast(int, v);
+  const int r = k == 0 ? __builtin_amdgcn_update_dpp(0, b, 0x00, 0xF, 0xF, false)
+              : k == 1 ? __builtin_amdgcn_update_dpp(0, b, 0x55, 0xF, 0xF, false)
+              : k == 2 ? __builtin_amdgcn_update_dpp(0, b, 0xAA, 0xF, 0xF, false)
+                       : __builtin_amdgcn_update_dpp(0, b, 0xFF, 0xF, 0xF, false);
+  return __builtin_bit_cast(float, r);
+}
+
+// LDS row stride of W1 (floats): a multiple of 4 whose quarter is odd, so the
+// 16 rows x 4 columns of an operand read fall in 64 different banks.
+constexpr int fwr_stride(int ns) { return (ns & 1) ? 4 * ns : 4 * ns + 4; }
+
+// NS: 4-feature steps of the contraction, ceil(D / 4); ACT: 0 sigma, 1 tanh.
+template <int NS, int ACT>
+__global__ __launch_bounds__(256) void k_forward_rows(int64_t n, int D, int H, int K, const float *__restrict__ X,
+                                                      mlp_params p, float *__restrict__ A, float *__restrict__ Y,
+                                                      PredictOut po) {
+  constexpr int XS = fwr_stride(NS);
+  extern __shared__ float4 fsm4[];
+  float *ws = reinterpret_cast<float *>(fsm4);       // [HB][XS]
+  const int HB = min(kFwrHB, (H + 15) / 16 * 16);
+  float *b1 = ws + HB * XS;                          // [HB]
+  float *w2 = b1 + HB;                               // [4][HB]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, lg = lane >> 4;
+  const bool once = H <= kFwrHB;                     // one block: staged before the rows
+  auto stage = [&](int h0) {
+    // lanes run over columns, 4 rows per wave and pass: no index division
+    for (int h = tid >> 4; h < HB; h += 16) {
+      const bool on = h0 + h < H;
+      const float *src = p.W1 + (int64_t)(on ? h0 + h : 0) * D;
+      float v[(NS * 4 + 15) / 16];
+#pragma unroll
+      for (int j = 0; j < (NS * 4 + 15) / 16; ++j) {
+        const int c = l16 + 16 * j;
+        v[j] = src[c < D ? c : 0];
+      }
+#pragma unroll
+      for (int j = 0; j < (NS * 4 + 15) / 16; ++j) {
+        const int c = l16 + 16 * j;
+        if (c < 4 * NS) ws[h * XS + c] = on && c < D ? v[j] : 0.0f;
+      }
+    }
+    for (int h = tid; h < HB; h += 256) {
+      const bool on = h0 + h < H;
+      b1[h] = on ? p.b1[h0 + h] : 0.0f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) w2[k * HB + h] = on && k < K ? p.W2[(int64_t)k * H + h0 + h] : 0.0f;
+    }
+  };
+  float xa[2][NS];
+  auto load_x = [&](int64_t r0) {
+#pragma unroll
+    for (int rs = 0; rs < 2; ++rs) {
+      const int64_t r = r0 + 16 * rs + l16;
+      const float *x = X + (r < n ? r : n - 1) * D;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int c = 4 * s + lg;
+        const float v = x[c < D ? c : 0];
+        xa[rs][s] = c < D ? v : 0.0f;
+      }
+    }
+  };
+  const int64_t stride = (int64_t)gridDim.x * 128;
+  int64_t r0 = (int64_t)blockIdx.x * 128 + wave * 32;
+  if (once) {
+    stage(0);
+    __syncthreads();
+  }
+  int hits = 0;
+  // every wave runs the same number of rounds (the block staging has barriers)
+  for (int64_t base = (int64_t)blockIdx.x * 128; base < n; base += stride, r0 += stride) {
+    const bool live = r0 < n;
+    if (live) load_x(r0);
+    float zp[2][4][4];
+#pragma unroll
+    for (int rs = 0; rs < 2; ++rs)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) zp[rs][i][k] = 0.0f;
+    for (int h0 = 0; h0 < H; h0 += kFwrHB) {
+      if (!once) {
+        __syncthreads();   // the previous block is no longer read
+        stage(h0);
+        __syncthreads();
+      }
+      if (!live) continue;
+      const int nt = (min(kFwrHB, H - h0) + 15) / 16;
+      for (int ht = 0; ht < nt; ++ht) {
+        const int hl = ht * 16 + l16, h = h0 + hl;
+        const float *wb = ws + hl * XS + lg;
+        float wv[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) wv[s] = wb[4 * s];
+        f32x4_l z[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          z[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[0][s], wv[s], z[0], 0, 0, 0);
+          z[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[1][s], wv[s], z[1], 0, 0, 0);
+        }
+        const float bias = b1[hl];
+        float w[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w[k] = w2[k * HB + hl];
+#pragma unroll
+        for (int rs = 0; rs < 2; ++rs)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float slope;
+            float a = hidden_act(ACT, z[rs][i] + bias, slope);
+            if (h >= H) a = 0.0f;
+            if (A) {
+              const int64_t r = r0 + 16 * rs + 4 * lg + i;
+              if (r < n && h < H) A[r * H + h] = a;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) zp[rs][i][k] = fmaf(a, w[k], zp[rs][i][k]);
+          }
+      }
+    }
+    if (!live) continue;
+#pragma unroll
+    for (int rs = 0; rs < 2; ++rs) {
+      // the row sums end in all 16 lanes; lane 4 i + k keeps row i, output k
+      float z2 = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float v = sum16(zp[rs][i][k]);
+          z2 = l16 == 4 * i + k ? v : z2;
+        }
+      const int k = l16 & 3;
+      const int64_t r = r0 + 16 * rs + 4 * lg + (l16 >> 2);
+      const float y = sigmoid(z2 + p.b2[k < K ? k : 0]);
+      if (k < K && r < n) Y[r * K + k] = y;
+      if (po.labels) {
+        const float y4[4] = {quad_bcast(y, 0), quad_bcast(y, 1), quad_bcast(y, 2), quad_bcast(y, 3)};
+        if (k == 0 && r < n) {
+          int best = K == 1 && y4[0] > 0.5f ? 1 : 0;
+          float top = y4[0];
+#pragma unroll
+          for (int j = 1; j < 4; ++j)
+            if (j < K && y4[j] > top) {   // strict: the lowest index wins ties
+              top = y4[j];
+              best = j;
+            }
+          po.labels[r] = best;
+          if (po.T) hits += best == argmax_row(po.T + r * K, K);
+        }
+      }
+    }
+  }
+  if (po.labels && po.T) {
+    __shared__ int part[4];
+    for (int off = 32; off >= 1; off >>= 1) hits += __shfl_xor(hits, off, kWave);
+    if (lane == 0) part[wave] = hits;
+    __syncthreads();
+    if (tid == 0) atomicAdd(po.correct, (part[0] + part[1]) + (part[2] + part[3]));
+  }
+}
+
 __global__ __launch_bounds__(256) void k_step(int D, int H, int K, mlp_params p, mlp_params g,
                                               float *__restrict__ comp, float lr, float mu,
                                               float *__restrict__ vel) {
@@ -157,16 +354,6 @@ __global__ __launch_bounds__(256) void k_step(int D, int H, int K, mlp_params p,
 namespace mlpk {
 
 __global__ void k_fill_i32(int32_t *p, int32_t v) { *p = v; }
-
-// Class of a row of outputs (or targets): the largest entry, the lowest
-// index on ties; a single output is a two-class net, class 1 above 1/2.
-__device__ __forceinline__ int argmax_row(const float *v, int K) {
-  if (K == 1) return v[0] > 0.5f ? 1 : 0;
-  int best = 0;
-  for (int k = 1; k < K; ++k)
-    if (v[k] > v[best]) best = k;   // strict: the lowest index wins ties
-  return best;
-}
 
 __global__ __launch_bounds__(256) void k_eval_batched(const mlp_batch_item *__restrict__ items, int D, int K,
                                                       const float *__restrict__ X, const float *__restrict__ T,
@@ -244,8 +431,37 @@ namespace mlph {
 
 static dim3 grid_for(int64_t n, int b) { return dim3((unsigned)((n + b - 1) / b)); }
 
+// k_forward_rows for every contraction length and activation.
+template <int NS>
+static const void *forward_rows_kernel(int ns, int act) {
+  if (ns == NS)
+    return act ? (const void *)mlpk::k_forward_rows<NS, 1> : (const void *)mlpk::k_forward_rows<NS, 0>;
+  if constexpr (NS < 16) return forward_rows_kernel<NS + 1>(ns, act);
+  return nullptr;
+}
+
+static bool forward_rows_covers(int D, int K) { return D <= 64 && K <= 4; }
+
+static hipError_t launch_forward_rows(int64_t n, int D, int H, int K, const float *X, mlp_params p, float *A,
+                                      float *Y, mlpk::PredictOut po, int act, int n_cu, hipStream_t s) {
+  const int ns = (D + 3) / 4;
+  const int HB = std::min(mlpk::kFwrHB, (H + 15) / 16 * 16);
+  const size_t lds = sizeof(float) * (size_t)HB * (mlpk::fwr_stride(ns) + 5);
+  const void *kern = forward_rows_kernel<1>(ns, act);
+  hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  // resident workgroups: four per CU while their LDS allows it
+  const int per_cu = lds <= 40 * 1024 ? 4 : 2;
+  const int64_t blocks = std::min<int64_t>((n + 127) / 128, (int64_t)n_cu * per_cu);
+  void *args[] = {&n, &D, &H, &K, &X, &p, &A, &Y, &po};
+  e = hipLaunchKernel(kern, dim3((unsigned)blocks), dim3(256), args, lds, s);
+  return e == hipSuccess ? hipGetLastError() : e;
+}
+
 hipError_t launch_forward(int64_t n, int D, int H, int K, const float *X, mlp_params p, float *A,
-                          float *Y, int act, hipStream_t s) {
+                          float *Y, int act, int n_cu, hipStream_t s) {
+  if (forward_rows_covers(D, K))
+    return launch_forward_rows(n, D, H, K, X, p, A, Y, mlpk::PredictOut{nullptr, nullptr, nullptr}, act, n_cu, s);
   if (D <= mlpk::kFwdMaxD && K <= mlpk::kLayerMaxOut) {
     const int XS = (D + 3) / 4 * 4 + 1;
     const size_t lds = sizeof(float) * ((size_t)(mlpk::kFwdRows + mlpk::kFwdHB) * XS +
@@ -353,13 +569,16 @@ hipError_t launch_eval_batched(const mlp_batch_item *items_dev, int n_nets, int 
 }
 
 hipError_t launch_predict(int64_t n, int D, int H, int K, const float *X, mlp_params p, float *Y,
-                          int32_t *labels, const float *T, int32_t *correct, int act, hipStream_t s) {
-  hipError_t e = launch_forward(n, D, H, K, X, p, nullptr, Y, act, s);
-  if (e != hipSuccess) return e;
+                          int32_t *labels, const float *T, int32_t *correct, int act, int n_cu, hipStream_t s) {
+  hipError_t e;
   if (T) {
     hipLaunchKernelGGL(mlpk::k_fill_i32, dim3(1), dim3(1), 0, s, correct, 0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
+  if (forward_rows_covers(D, K))
+    return launch_forward_rows(n, D, H, K, X, p, nullptr, Y, mlpk::PredictOut{labels, T, correct}, act, n_cu, s);
+  e = launch_forward(n, D, H, K, X, p, nullptr, Y, act, n_cu, s);
+  if (e != hipSuccess) return e;
   // at most 512 blocks (rows in a grid-stride loop): one count add per block
   const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(512, (n + 255) / 256)));
   hipLaunchKernelGGL(mlpk::k_argmax, grid, dim3(256), 0, s, n, K, Y, T, labels, correct);

@@ -210,7 +210,7 @@ mlp_status mlp_forward(mlp_net *net, const float *X, int64_t n, float *A, float 
     return fail(MLP_ERR_ALIGN, "X must be 16-byte and A, Y 4-byte aligned");
   const mlp_config &c = net->cfg;
   hipError_t e = mlph::launch_forward(n, c.n_in, c.n_hidden, c.n_out, X, net->theta, A, Y, act_of(c),
-                                      (hipStream_t)stream);
+                                      net->n_cu, (hipStream_t)stream);
   return e == hipSuccess ? MLP_OK : hip_fail(e, "mlp_forward launch");
 }
 
@@ -224,7 +224,7 @@ mlp_status mlp_predict(mlp_net *net, const float *X, int64_t n, float *Y, int32_
     return fail(MLP_ERR_ALIGN, "X must be 16-byte and Y, labels, T, correct 4-byte aligned");
   const mlp_config &c = net->cfg;
   hipError_t e = mlph::launch_predict(n, c.n_in, c.n_hidden, c.n_out, X, net->theta, Y, labels, T, correct,
-                                      act_of(c), (hipStream_t)stream);
+                                      act_of(c), net->n_cu, (hipStream_t)stream);
   return e == hipSuccess ? MLP_OK : hip_fail(e, "mlp_predict launch");
 }
 

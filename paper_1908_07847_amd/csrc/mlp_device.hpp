@@ -139,7 +139,7 @@ hipError_t launch_small_train(const mlp_batch_item *items, mlp_batch_item one, i
 
 // Generic layer kernels (any sizes) for mlp_forward / mlp_backward / mlp_step.
 hipError_t launch_forward(int64_t n, int D, int H, int K, const float *X, mlp_params p, float *A,
-                          float *Y, int act, hipStream_t s);
+                          float *Y, int act, int n_cu, hipStream_t s);
 hipError_t launch_backward(int64_t n, int64_t ws_floats, int D, int H, int K, const float *X,
                            const float *A, const float *Y, const float *dY, const float *T,
                            mlp_params p, mlp_params g, float *dX, float *loss, float *ws, int act,
@@ -147,7 +147,7 @@ hipError_t launch_backward(int64_t n, int64_t ws_floats, int D, int H, int K, co
 hipError_t launch_step(int D, int H, int K, mlp_params p, mlp_params g, float *comp, float lr, float mu,
                        float *vel, hipStream_t s);
 hipError_t launch_predict(int64_t n, int D, int H, int K, const float *X, mlp_params p, float *Y,
-                          int32_t *labels, const float *T, int32_t *correct, int act, hipStream_t s);
+                          int32_t *labels, const float *T, int32_t *correct, int act, int n_cu, hipStream_t s);
 // One dense layer (several-hidden-layer networks) and a packed update.
 hipError_t launch_dense_forward(int64_t n, int din, int dout, const float *X, const float *W, const float *b,
                                 int act, float *Y, hipStream_t s);
