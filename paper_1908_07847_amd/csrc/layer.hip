@@ -173,9 +173,12 @@ __device__ __forceinline__ float quad_bcast(float v, int k) {
 // 16 rows x 4 columns of an operand read fall in 64 different banks.
 constexpr int fwr_stride(int ns) { return (ns & 1) ? 4 * ns : 4 * ns + 4; }
 
-// NS: 4-feature steps of the contraction, ceil(D / 4); ACT: 0 sigma, 1 tanh.
-template <int NS, int ACT>
-__global__ __launch_bounds__(256) void k_forward_rows(int64_t n, int D, int H, int K, const float *__restrict__ X,
+// NS: 4-feature steps of the contraction, ceil(D / 4); ACT: 0 sigma, 1 tanh;
+// STORE: the hidden activations are written (forward) or not (predictions).
+// Three or four waves per SIMD (what fits without spilling): one wave's
+// products overlap the others' activations.
+template <int NS, int ACT, bool STORE>
+__global__ __launch_bounds__(256, NS <= 9 && !STORE ? 4 : 3) void k_forward_rows(int64_t n, int D, int H, int K, const float *__restrict__ X,
                                                       mlp_params p, float *__restrict__ A, float *__restrict__ Y,
                                                       PredictOut po) {
   constexpr int XS = fwr_stride(NS);
@@ -184,7 +187,8 @@ __global__ __launch_bounds__(256) void k_forward_rows(int64_t n, int D, int H, i
   const int HB = min(kFwrHB, (H + 15) / 16 * 16);
   float *b1 = ws + HB * XS;                          // [HB]
   float *w2 = b1 + HB;                               // [4][HB]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // the wave index in a scalar register: row bases derived from it are uniform
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, lg = lane >> 4;
   const bool once = H <= kFwrHB;                     // one block: staged before the rows
   auto stage = [&](int h0) {
@@ -243,6 +247,8 @@ __global__ __launch_bounds__(256) void k_forward_rows(int64_t n, int D, int H, i
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int k = 0; k < 4; ++k) zp[rs][i][k] = 0.0f;
+    float *Ab = STORE ? A + r0 * H : nullptr;   // this wave's rows (uniform base, 32-bit lane offsets)
+    const int left = (int)min((int64_t)32, n - r0);
     for (int h0 = 0; h0 < H; h0 += kFwrHB) {
       if (!once) {
         __syncthreads();   // the previous block is no longer read
@@ -274,9 +280,9 @@ __global__ __launch_bounds__(256) void k_forward_rows(int64_t n, int D, int H, i
             float slope;
             float a = hidden_act(ACT, z[rs][i] + bias, slope);
             if (h >= H) a = 0.0f;
-            if (A) {
-              const int64_t r = r0 + 16 * rs + 4 * lg + i;
-              if (r < n && h < H) A[r * H + h] = a;
+            if (STORE) {
+              float *row = Ab + (int64_t)(16 * rs + i) * H;
+              if (16 * rs + 4 * lg + i < left && h < H) row[(uint32_t)(4 * lg * H + h)] = a;
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) zp[rs][i][k] = fmaf(a, w[k], zp[rs][i][k]);
@@ -432,11 +438,11 @@ namespace mlph {
 static dim3 grid_for(int64_t n, int b) { return dim3((unsigned)((n + b - 1) / b)); }
 
 // k_forward_rows for every contraction length and activation.
-template <int NS>
+template <int NS, bool STORE>
 static const void *forward_rows_kernel(int ns, int act) {
   if (ns == NS)
-    return act ? (const void *)mlpk::k_forward_rows<NS, 1> : (const void *)mlpk::k_forward_rows<NS, 0>;
-  if constexpr (NS < 16) return forward_rows_kernel<NS + 1>(ns, act);
+    return act ? (const void *)mlpk::k_forward_rows<NS, 1, STORE> : (const void *)mlpk::k_forward_rows<NS, 0, STORE>;
+  if constexpr (NS < 16) return forward_rows_kernel<NS + 1, STORE>(ns, act);
   return nullptr;
 }
 
@@ -447,7 +453,7 @@ static hipError_t launch_forward_rows(int64_t n, int D, int H, int K, const floa
   const int ns = (D + 3) / 4;
   const int HB = std::min(mlpk::kFwrHB, (H + 15) / 16 * 16);
   const size_t lds = sizeof(float) * (size_t)HB * (mlpk::fwr_stride(ns) + 5);
-  const void *kern = forward_rows_kernel<1>(ns, act);
+  const void *kern = A ? forward_rows_kernel<1, true>(ns, act) : forward_rows_kernel<1, false>(ns, act);
   hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   // resident workgroups: four per CU while their LDS allows it
