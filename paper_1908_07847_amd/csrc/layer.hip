@@ -169,6 +169,19 @@ __device__ __forceinline__ float quad_bcast(float v, int k) {
   return __builtin_bit_cast(float, r);
 }
 
+// argmax_row of at most four values in registers.
+__device__ __forceinline__ int argmax4(const float (&v)[4], int K) {
+  int best = K == 1 && v[0] > 0.5f ? 1 : 0;
+  float top = v[0];
+#pragma unroll
+  for (int j = 1; j < 4; ++j)
+    if (j < K && v[j] > top) {   // strict: the lowest index wins ties
+      top = v[j];
+      best = j;
+    }
+  return best;
+}
+
 // LDS row stride of W1 (floats): a multiple of 4 whose quarter is odd, so the
 // 16 rows x 4 columns of an operand read fall in 64 different banks.
 constexpr int fwr_stride(int ns) { return (ns & 1) ? 4 * ns : 4 * ns + 4; }
@@ -308,14 +321,7 @@ __global__ __launch_bounds__(256, NS <= 9 && !STORE ? 4 : 3) void k_forward_rows
       if (po.labels) {
         const float y4[4] = {quad_bcast(y, 0), quad_bcast(y, 1), quad_bcast(y, 2), quad_bcast(y, 3)};
         if (k == 0 && r < n) {
-          int best = K == 1 && y4[0] > 0.5f ? 1 : 0;
-          float top = y4[0];
-#pragma unroll
-          for (int j = 1; j < 4; ++j)
-            if (j < K && y4[j] > top) {   // strict: the lowest index wins ties
-              top = y4[j];
-              best = j;
-            }
+          const int best = argmax4(y4, K);
           po.labels[r] = best;
           if (po.T) hits += best == argmax_row(po.T + r * K, K);
         }
@@ -412,6 +418,128 @@ __global__ __launch_bounds__(256) void k_eval_batched(const mlp_batch_item *__re
   }
 }
 
+// The same for n_in <= 64: the network's hidden tiles (16 units) are split
+// over the workgroup's 4 waves and its rows taken 32 at a time, z1 on
+// v_mfma_f32_16x16x4_f32 with every operand straight from global memory (each
+// is used once or twice), the output sums meeting in LDS in wave order.
+// A network is a few microseconds of latency, not of work, so the chip is
+// filled with one network per workgroup; one thread per row left 230 of 256
+// threads idle on a 25-row fold and walked W1 alone (4096 networks of up to
+// 64 units: 250 us).  NS = ceil(n_in / 4).
+template <int NS>
+__global__ __launch_bounds__(256) void k_eval_tiled(const mlp_batch_item *__restrict__ items, int D, int K,
+                                                    const float *__restrict__ X, const float *__restrict__ T,
+                                                    const float *__restrict__ theta, float *__restrict__ loss,
+                                                    int32_t *__restrict__ correct) {
+  __shared__ float zs[2][4][32][5];   // [buffer][wave][row][output], rows 5 apart: distinct banks
+  __shared__ float ps[2];
+  __shared__ int ph[2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lg = lane >> 4;
+  const mlp_batch_item it = items[blockIdx.x];
+  const int N = it.n_rows, H = it.n_hidden, HT = (H + 15) / 16;
+  const float *W1 = theta + it.p_off, *b1 = W1 + (int64_t)H * D, *W2 = b1 + H, *b2 = W2 + (int64_t)K * H;
+  const float *Xn = X + it.x_off * D, *Tn = T + it.x_off * K;
+  float sq = 0.0f;
+  int hit = 0, buf = 0;
+  for (int r0 = 0; r0 < N; r0 += 32, buf ^= 1) {
+    const int rows = min(32, N - r0);
+    float zp[2][4][4];
+#pragma unroll
+    for (int rs = 0; rs < 2; ++rs)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) zp[rs][i][k] = 0.0f;
+    if (wave < HT) {
+      const float *Xc = Xn + (int64_t)r0 * D;
+      float xa[2][NS];
+#pragma unroll
+      for (int rs = 0; rs < 2; ++rs) {
+        const int r = 16 * rs + l16;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const int c = 4 * s + lg;
+          const bool on = r < rows && c < D;
+          const float v = Xc[on ? (int64_t)r * D + c : 0];
+          xa[rs][s] = on ? v : 0.0f;
+        }
+      }
+      for (int t = wave; t < HT; t += 4) {
+        const int h = 16 * t + l16;
+        const bool hon = h < H;
+        const float *wr = W1 + (int64_t)(hon ? h : 0) * D;
+        float wv[NS], w2[4];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const int c = 4 * s + lg;
+          const float v = wr[c < D ? c : 0];
+          wv[s] = hon && c < D ? v : 0.0f;
+        }
+        const float bias = b1[hon ? h : 0];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float v = W2[hon && k < K ? (int64_t)k * H + h : 0];
+          w2[k] = hon && k < K ? v : 0.0f;
+        }
+        f32x4_l z[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          z[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[0][s], wv[s], z[0], 0, 0, 0);
+          z[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[1][s], wv[s], z[1], 0, 0, 0);
+        }
+#pragma unroll
+        for (int rs = 0; rs < 2; ++rs)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float a = hon ? sigmoid(z[rs][i] + bias) : 0.0f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) zp[rs][i][k] = fmaf(a, w2[k], zp[rs][i][k]);
+          }
+      }
+    }
+    // lane 4 i + k of a row group keeps row i, output k of the wave's share
+#pragma unroll
+    for (int rs = 0; rs < 2; ++rs) {
+      float z2 = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float v = sum16(zp[rs][i][k]);
+          z2 = l16 == 4 * i + k ? v : z2;
+        }
+      zs[buf][wave][16 * rs + 4 * lg + (l16 >> 2)][l16 & 3] = z2;
+    }
+    __syncthreads();   // the next round writes the other buffer
+    if (wave < 2) {
+      const int r = tid >> 2, k = tid & 3;
+      const bool on = r < rows && k < K;
+      const float z2 = (zs[buf][0][r][k] + zs[buf][1][r][k]) + (zs[buf][2][r][k] + zs[buf][3][r][k]);
+      const float y = sigmoid(z2 + b2[k < K ? k : 0]);
+      const float t = on ? Tn[(int64_t)(r0 + r) * K + k] : 0.0f;
+      const float e = on ? y - t : 0.0f;
+      sq = fmaf(e, e, sq);
+      const float y4[4] = {quad_bcast(y, 0), quad_bcast(y, 1), quad_bcast(y, 2), quad_bcast(y, 3)};
+      const float t4[4] = {quad_bcast(t, 0), quad_bcast(t, 1), quad_bcast(t, 2), quad_bcast(t, 3)};
+      if (k == 0 && r < rows) hit += argmax4(y4, K) == argmax4(t4, K);
+    }
+  }
+  if (wave < 2) {
+    const float v = wave_sum(sq);
+    for (int off = 32; off >= 1; off >>= 1) hit += __shfl_xor(hit, off, kWave);
+    if (lane == 0) {
+      ps[wave] = v;
+      ph[wave] = hit;
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    loss[blockIdx.x] = (ps[0] + ps[1]) / ((float)N * (float)K);
+    if (correct) correct[blockIdx.x] = ph[0] + ph[1];
+  }
+}
+
 __global__ __launch_bounds__(256) void k_argmax(int64_t n, int K, const float *__restrict__ Y,
                                                 const float *__restrict__ T, int32_t *__restrict__ labels,
                                                 int32_t *__restrict__ correct) {
@@ -493,67 +621,87 @@ hipError_t launch_forward(int64_t n, int D, int H, int K, const float *X, mlp_pa
 
 namespace mlpk {
 
-// Cross-validation selection: one workgroup.  Thread t owns the groups t,
-// t + 1024, ...: for each it walks every net in increasing order (the
-// (loss, group) pairs staged through LDS in chunks, read as broadcasts), so a
-// mean is one fixed-order float32 sum.  Then a (mean, group) minimum over
-// the threads, ties to the lower group.
+// Cross-validation selection.  k_cv_means: a wave owns gpw (<= 64) groups,
+// lane q group g0 + q, and scans every net 64 at a time: a ballot finds the
+// nets of its groups, which it adds one by one in increasing order, so a
+// mean is one fixed-order float32 sum.  k_cv_best: a (mean, group) minimum,
+// ties to the lower group.  (One workgroup with a thread per group reading
+// every (loss, group) pair from LDS took 299 us for 4096 nets in 820 groups.)
+constexpr int kSelU = 8;   // 64-net blocks whose loads are in flight together
+__global__ __launch_bounds__(256) void k_cv_means(const float *__restrict__ loss, const int32_t *__restrict__ group,
+                                                  int n, int ng, int gpw, float *__restrict__ mean) {
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  if ((int64_t)w * gpw >= ng) return;   // whole waves leave
+  const int g0 = w * gpw, m = min(gpw, ng - g0);
+  float sum = 0.0f;
+  int cnt = 0;
+  for (int64_t c0 = 0; c0 < n; c0 += 64 * kSelU) {
+    float lv[kSelU];
+    int gv[kSelU];
+#pragma unroll
+    for (int u = 0; u < kSelU; ++u) {
+      const int64_t i = c0 + 64 * u + lane;
+      lv[u] = loss[i < n ? i : 0];
+      gv[u] = i < n ? group[i] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kSelU; ++u) {
+      uint64_t hits = __ballot(gv[u] >= g0 && gv[u] - g0 < m);
+      while (hits) {
+        const int j = __builtin_ctzll(hits);
+        hits &= hits - 1;
+        const int q = __builtin_amdgcn_readlane(gv[u], j) - g0;
+        const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lv[u]), j));
+        if (lane == q) {
+          sum += v;
+          cnt += 1;
+        }
+      }
+    }
+  }
+  if (lane < m) {
+    float v = cnt ? sum / (float)cnt : __builtin_inff();
+    if (!(v < __builtin_inff())) v = __builtin_inff();   // NaN or +inf
+    mean[g0 + lane] = v;
+  }
+}
+
 constexpr int kSelThreads = 1024;
-constexpr int kSelChunk = 2048;
-__global__ __launch_bounds__(kSelThreads) void k_cv_select(const float *__restrict__ loss,
-                                                         const int32_t *__restrict__ group, int n, int ng,
-                                                         float *__restrict__ mean, int32_t *__restrict__ best) {
-  __shared__ float ls[kSelChunk];
-  __shared__ int32_t gs[kSelChunk];
-  __shared__ float bv[kSelThreads];
-  __shared__ int32_t bi[kSelThreads];
+__global__ __launch_bounds__(kSelThreads) void k_cv_best(const float *__restrict__ mean, int ng,
+                                                         int32_t *__restrict__ best) {
+  __shared__ float bv[kSelThreads / kWave];
+  __shared__ int32_t bi[kSelThreads / kWave];
   const int t = threadIdx.x;
   float mv = __builtin_inff();
   int mi = 0x7fffffff;
-  for (int r = 0; r * kSelThreads < ng; ++r) {
-    const int g = t + r * kSelThreads;
-    float sum = 0.0f;
-    int cnt = 0;
-    for (int c0 = 0; c0 < n; c0 += kSelChunk) {
-      const int m = min(kSelChunk, n - c0);
-      __syncthreads();   // the previous chunk is no longer read
-      for (int i = t; i < m; i += kSelThreads) {
-        ls[i] = loss[c0 + i];
-        gs[i] = group[c0 + i];
-      }
-      __syncthreads();
-      if (g < ng)
-        for (int i = 0; i < m; ++i)
-          if (gs[i] == g) {
-            sum += ls[i];
-            cnt += 1;
-          }
-    }
-    if (g < ng) {
-      float v = cnt ? sum / (float)cnt : __builtin_inff();
-      if (!(v < __builtin_inff())) v = __builtin_inff();   // NaN or +inf
-      mean[g] = v;
-      if (v < mv || (v == mv && g < mi)) {
-        mv = v;
-        mi = g;
-      }
+  for (int g = t; g < ng; g += kSelThreads) {
+    const float v = mean[g];
+    if (v < mv || (v == mv && g < mi)) {
+      mv = v;
+      mi = g;
     }
   }
-  bv[t] = mv;
-  bi[t] = mi;
+  for (int off = 32; off >= 1; off >>= 1) {
+    const float v = __shfl_xor(mv, off, kWave);
+    const int i = __shfl_xor(mi, off, kWave);
+    if (v < mv || (v == mv && i < mi)) {
+      mv = v;
+      mi = i;
+    }
+  }
+  if ((t & 63) == 0) {
+    bv[t >> 6] = mv;
+    bi[t >> 6] = mi;
+  }
   __syncthreads();
-  for (int st = kSelThreads / 2; st > 0; st >>= 1) {
-    if (t < st) {
-      const float v = bv[t + st];
-      const int i = bi[t + st];
-      if (v < bv[t] || (v == bv[t] && i < bi[t])) {
-        bv[t] = v;
-        bi[t] = i;
-      }
+  if (t != 0) return;
+  for (int w = 1; w < kSelThreads / kWave; ++w)
+    if (bv[w] < mv || (bv[w] == mv && bi[w] < mi)) {
+      mv = bv[w];
+      mi = bi[w];
     }
-    __syncthreads();
-  }
-  if (t == 0) best[0] = bi[0] == 0x7fffffff ? 0 : bi[0];
+  best[0] = mi == 0x7fffffff ? 0 : mi;
 }
 
 }  // namespace mlpk
@@ -562,14 +710,28 @@ namespace mlph {
 
 hipError_t launch_cv_select(const float *loss, const int32_t *group, int n_nets, int n_groups, float *group_mean,
                             int32_t *best, hipStream_t s) {
-  hipLaunchKernelGGL(mlpk::k_cv_select, dim3(1), dim3(mlpk::kSelThreads), 0, s, loss, group, n_nets, n_groups,
-                     group_mean, best);
+  // one group per wave until the waves fill the chip, then several
+  const int gpw = std::min(64, (n_groups + 4095) / 4096);
+  const int waves = (n_groups + gpw - 1) / gpw;
+  hipLaunchKernelGGL(mlpk::k_cv_means, dim3((waves + 3) / 4), dim3(256), 0, s, loss, group, n_nets, n_groups, gpw,
+                     group_mean);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(mlpk::k_cv_best, dim3(1), dim3(mlpk::kSelThreads), 0, s, group_mean, n_groups, best);
   return hipGetLastError();
+}
+
+// k_eval_tiled for every contraction length.
+template <int NS>
+static auto eval_kernel(int ns) -> decltype(&mlpk::k_eval_batched) {
+  if (ns == NS) return mlpk::k_eval_tiled<NS>;
+  if constexpr (NS < 16) return eval_kernel<NS + 1>(ns);
+  return mlpk::k_eval_batched;   // n_in > 64: one thread per row
 }
 
 hipError_t launch_eval_batched(const mlp_batch_item *items_dev, int n_nets, int D, int K, const float *X,
                                const float *T, const float *theta, float *loss, int32_t *correct, hipStream_t s) {
-  hipLaunchKernelGGL(mlpk::k_eval_batched, dim3(n_nets), dim3(256), 0, s, items_dev, D, K, X, T, theta, loss,
+  hipLaunchKernelGGL(eval_kernel<1>((D + 3) / 4), dim3(n_nets), dim3(256), 0, s, items_dev, D, K, X, T, theta, loss,
                      correct);
   return hipGetLastError();
 }
