@@ -91,7 +91,9 @@ __global__ __launch_bounds__(64 * kGWaves) void k_grad_sum(int64_t n, int din, i
   __shared__ float small[kGWaves][kGT][KR + 1];   // gb and gW2 of each wave
   __shared__ float d2s[kGWaves][kGSet][KR];
   __shared__ float tail[kGWaves][KR + 1];         // gb2 and the squared error of each wave
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // the wave index in a scalar register: row bases are uniform, lanes add
+  // 32-bit offsets
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, lg = lane >> 4;
   const int o0 = (blockIdx.x / ftiles) * kGT, f0 = (blockIdx.x % ftiles) * kGT;
   const bool first_f = f0 == 0;            // this tile also sums gb (and gW2)
@@ -149,16 +151,15 @@ __global__ __launch_bounds__(64 * kGWaves) void k_grad_sum(int64_t n, int din, i
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         const int row = h + 4 * s + lg, rc = row < rows ? row : 0;
-        const float *xr = xb + (int64_t)rc * din;
-        const int64_t orow = (base + rc) * dout;
+        const uint32_t xo = (uint32_t)(rc * din), oo_ = (uint32_t)(rc * dout);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          xv[s][t] = xr[fc[t]];
+          xv[s][t] = xb[xo + (uint32_t)fc[t]];
           if constexpr (KO > 0) {
-            ov[s][t] = src.A[orow + oc[t]];
+            ov[s][t] = (src.A + base * dout)[oo_ + (uint32_t)oc[t]];
           } else {
-            ov[s][t] = src.Y[orow + oc[t]];
-            uv[s][t] = src.dY[orow + oc[t]];
+            ov[s][t] = (src.Y + base * dout)[oo_ + (uint32_t)oc[t]];
+            uv[s][t] = (src.dY + base * dout)[oo_ + (uint32_t)oc[t]];
           }
         }
       }

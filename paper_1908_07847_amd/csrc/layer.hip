@@ -230,14 +230,16 @@ __global__ __launch_bounds__(256, NS <= 9 && !STORE ? 4 : 3) void k_forward_rows
   };
   float xa[2][NS];
   auto load_x = [&](int64_t r0) {
+    const float *x = X + r0 * D;   // uniform base, 32-bit lane offsets
+    const int last = (int)min((int64_t)31, n - 1 - r0);
 #pragma unroll
     for (int rs = 0; rs < 2; ++rs) {
-      const int64_t r = r0 + 16 * rs + l16;
-      const float *x = X + (r < n ? r : n - 1) * D;
+      // a row past the end reads the last one (its results are dropped)
+      const uint32_t ro = (uint32_t)(min(16 * rs + l16, last) * D);
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         const int c = 4 * s + lg;
-        const float v = x[c < D ? c : 0];
+        const float v = x[ro + (uint32_t)(c < D ? c : 0)];
         xa[rs][s] = c < D ? v : 0.0f;
       }
     }
@@ -427,7 +429,7 @@ __global__ __launch_bounds__(256) void k_eval_batched(const mlp_batch_item *__re
 // threads idle on a 25-row fold and walked W1 alone (4096 networks of up to
 // 64 units: 250 us).  NS = ceil(n_in / 4).
 template <int NS>
-__global__ __launch_bounds__(256) void k_eval_tiled(const mlp_batch_item *__restrict__ items, int D, int K,
+__global__ __launch_bounds__(256, 4) void k_eval_tiled(const mlp_batch_item *__restrict__ items, int D, int K,
                                                     const float *__restrict__ X, const float *__restrict__ T,
                                                     const float *__restrict__ theta, float *__restrict__ loss,
                                                     int32_t *__restrict__ correct) {
@@ -444,6 +446,11 @@ __global__ __launch_bounds__(256) void k_eval_tiled(const mlp_batch_item *__rest
   int hit = 0, buf = 0;
   for (int r0 = 0; r0 < N; r0 += 32, buf ^= 1) {
     const int rows = min(32, N - r0);
+    // this thread's output of the round (waves 0 and 1): its target and bias
+    // load with the operands, not after the barrier
+    const int rt = (tid >> 2) & 31, kt = tid & 3;
+    const bool on_t = rt < rows && kt < K;
+    const float tl = Tn[on_t ? (int64_t)(r0 + rt) * K + kt : 0], bl = b2[kt < K ? kt : 0];
     float zp[2][4][4];
 #pragma unroll
     for (int rs = 0; rs < 2; ++rs)
@@ -461,25 +468,25 @@ __global__ __launch_bounds__(256) void k_eval_tiled(const mlp_batch_item *__rest
         for (int s = 0; s < NS; ++s) {
           const int c = 4 * s + lg;
           const bool on = r < rows && c < D;
-          const float v = Xc[on ? (int64_t)r * D + c : 0];
+          const float v = Xc[(uint32_t)(on ? r * D + c : 0)];
           xa[rs][s] = on ? v : 0.0f;
         }
       }
       for (int t = wave; t < HT; t += 4) {
         const int h = 16 * t + l16;
         const bool hon = h < H;
-        const float *wr = W1 + (int64_t)(hon ? h : 0) * D;
+        const int ho = hon ? h * D : 0;   // 32-bit offsets from scalar bases throughout
         float wv[NS], w2[4];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
           const int c = 4 * s + lg;
-          const float v = wr[c < D ? c : 0];
+          const float v = W1[(uint32_t)(ho + (c < D ? c : 0))];
           wv[s] = hon && c < D ? v : 0.0f;
         }
-        const float bias = b1[hon ? h : 0];
+        const float bias = b1[(uint32_t)(hon ? h : 0)];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const float v = W2[hon && k < K ? (int64_t)k * H + h : 0];
+          const float v = W2[(uint32_t)(hon && k < K ? k * H + h : 0)];
           w2[k] = hon && k < K ? v : 0.0f;
         }
         f32x4_l z[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
@@ -513,12 +520,11 @@ __global__ __launch_bounds__(256) void k_eval_tiled(const mlp_batch_item *__rest
     }
     __syncthreads();   // the next round writes the other buffer
     if (wave < 2) {
-      const int r = tid >> 2, k = tid & 3;
-      const bool on = r < rows && k < K;
+      const int r = rt, k = kt;
       const float z2 = (zs[buf][0][r][k] + zs[buf][1][r][k]) + (zs[buf][2][r][k] + zs[buf][3][r][k]);
-      const float y = sigmoid(z2 + b2[k < K ? k : 0]);
-      const float t = on ? Tn[(int64_t)(r0 + r) * K + k] : 0.0f;
-      const float e = on ? y - t : 0.0f;
+      const float y = sigmoid(z2 + bl);
+      const float t = on_t ? tl : 0.0f;
+      const float e = on_t ? y - t : 0.0f;
       sq = fmaf(e, e, sq);
       const float y4[4] = {quad_bcast(y, 0), quad_bcast(y, 1), quad_bcast(y, 2), quad_bcast(y, 3)};
       const float t4[4] = {quad_bcast(t, 0), quad_bcast(t, 1), quad_bcast(t, 2), quad_bcast(t, 3)};
