@@ -86,6 +86,14 @@ bool small_path(const mlp_config &c) {
 
 int act_of(const mlp_config &c) { return (c.flags & MLP_F_TANH_HIDDEN) ? 1 : 0; }
 
+mlp_status device_cus(int *ncu) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+  e = hipDeviceGetAttribute(ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
+  return MLP_OK;
+}
 size_t backward_ws_bytes(const mlp_config &c) {
   const int64_t rows = std::min<int64_t>(c.n_rows, mlph::kBackwardChunk);
   return sizeof(float) * (size_t)rows * (size_t)(c.n_hidden + c.n_out + 1);
@@ -289,7 +297,7 @@ mlp_status mlp_train(mlp_net *net, const float *X, const float *T, int32_t epoch
     one.x_off = 0;
     one.p_off = 0;
     // the tanh variant runs 8 waves per net (its only instances)
-    const int threads = act_of(c) ? 512 : mlph::small_threads(1, g_hint.small_threads);
+    const int threads = act_of(c) ? 512 : mlph::small_threads(1, (int)H, net->n_cu, g_hint.small_threads);
     if (act_of(c) && mlph::small_lds_bytes((int)c.n_rows, (int)H, (int)D, 512, net->velocity != nullptr) >
                          160 * 1024)
       return fail(MLP_ERR_UNSUPPORTED, "the tanh variant's 8-wave plan does not fit in LDS at this shape");
@@ -351,10 +359,13 @@ mlp_status mlp_train_batched(const mlp_batch_item *items_host, const mlp_batch_i
     max_rows = std::max(max_rows, items_host[i].n_rows);
     max_h = std::max(max_h, items_host[i].n_hidden);
   }
+  int n_cu = 0;
+  const mlp_status s = device_cus(&n_cu);
+  if (s != MLP_OK) return s;
   mlp_batch_item none{};
   hipError_t e = mlph::launch_small_train(items_dev, none, n_nets, n_in, n_out, max_rows, max_h, X_packed,
                                           T_packed, theta_packed, comp_packed, epochs, loss_hist, 0, 0.0f,
-                                          nullptr, mlph::small_threads(n_nets, g_hint.small_threads),
+                                          nullptr, mlph::small_threads(n_nets, max_h, n_cu, g_hint.small_threads),
                                           (hipStream_t)stream);
   return e == hipSuccess ? MLP_OK : hip_fail(e, "mlp_train_batched launch");
 }
@@ -440,14 +451,6 @@ mlp_status check_shared(const mlp_config *cfg, int32_t n_nets, const float *lr, 
   return MLP_OK;
 }
 
-mlp_status device_cus(int *ncu) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-  e = hipDeviceGetAttribute(ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
-  return MLP_OK;
-}
 }  // namespace
 
 mlp_status mlp_train_shared(const mlp_config *cfg, int32_t n_nets, const float *lr, const float *X,

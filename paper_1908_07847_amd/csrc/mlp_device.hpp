@@ -41,6 +41,16 @@ __device__ __forceinline__ float sigmoid_e(float z, float &e_out) {
   return r;
 }
 
+// sigma and its slope from e = e^-z as sigmoid_e left it: the same bits as
+// sigmoid_slope(z) without the exponential.
+__device__ __forceinline__ float sigmoid_slope_of_e(float e, float &slope) {
+  const float d = 1.0f + e;
+  float r = __builtin_amdgcn_rcpf(d);
+  r = fmaf(r, fmaf(-d, r, 1.0f), r);
+  slope = (e * r) * r;
+  return r;
+}
+
 __device__ __forceinline__ float sigmoid(float z) {
   float e;
   return sigmoid_e(z, e);
@@ -125,11 +135,11 @@ constexpr int64_t kBackwardChunk = 16384;
 // 256 or 512 (waves split the rows), or kHiddenSplit: one wave per 16
 // hidden units of the widest net (waves split the hidden layer; the paper's
 // sigmoid network without momentum, others fall back to 128 threads).
-// small_threads picks it from the net count and a hint.
+// small_threads picks it from the net count, the widest net and a hint.
 constexpr int kHiddenSplit = 64;
 size_t small_lds_bytes(int n_rows, int n_hidden, int n_in, int threads, bool momentum = false);
 size_t small_launch_lds_bytes(int max_rows, int max_hidden, int n_in, int threads, bool momentum = false);
-int small_threads(int n_nets, int hint);
+int small_threads(int n_nets, int max_hidden, int n_cu, int hint);
 // act: hidden activation (0 sigma, 1 tanh); vel != nullptr: heavy-ball
 // momentum mu with the velocity vel[P] (packed, a single net only).
 hipError_t launch_small_train(const mlp_batch_item *items, mlp_batch_item one, int n_nets,

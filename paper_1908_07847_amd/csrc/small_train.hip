@@ -454,14 +454,15 @@ hipError_t launch_nw(int max_hidden, const mlp_batch_item *items, mlp_batch_item
 // instead of the rows.  Wave w owns hidden tile w (units 16 w .. 16 w + 15)
 // for every row of the net; waves past the net's last tile only pass the
 // barriers.  Per epoch:
-//   phase A (every 16-row tile): z1^T of the wave's tile on MFMA, kept in
-//     registers for the epoch, and the tile's share of z2 (its
+//   phase A (every 16-row tile): z1^T of the wave's tile on MFMA, e^-z1 kept
+//     in registers for the epoch, and the tile's share of z2 (its
 //     16 hidden units, reduce-scattered over the lanes of a row) to LDS;
 //   one barrier;
 //   phase B (every row tile): z2 = the tiles' shares summed in tile order
 //     plus b2, y and delta2 (each wave forms them itself, so every wave holds
 //     the same values), then for the wave's own units a and the slope again
-//     from z1 (two sigmoids per element cost less than holding both),
+//     from e^-z1 (a reciprocal; holding both would take 32 more registers and
+//     a third of the resident nets),
 //     gW2 += a^T delta2,
 //     delta1 = (W2^T delta2) . slope with the pre-update W2, and
 //     gW1 += delta1^T [X 1], all on MFMA and accumulated in registers;
@@ -587,7 +588,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
     // epoch loop and held (or spilled) for the whole run
     int l16 = l16_0, lg = lg_0;
     asm volatile("" : "+v"(l16), "+v"(lg));
-    float zz[8][4];   // z1 of this wave's units, every row tile (a and the slope are re-formed from it)
+    float ez[8][4];   // e^-z1 of this wave's units, every row tile (a and the slope are re-formed from it)
     // ======================= phase A: a of this wave's tile, its share of z2
     // Row tiles go in pairs whose two z1 chains share the W1 operand and
     // interleave on the matrix cores (a lone last tile runs its own chain).
@@ -598,8 +599,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
         float a[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          zz[rt][i] = z[i];
-          a[i] = sigmoid(z[i]);
+          a[i] = sigmoid_e(z[i], ez[rt][i]);
         }
         float zp[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -677,7 +677,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
 #pragma unroll
       for (int j = 0; j < NR; ++j) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) av[j][i] = sigmoid_slope(zz[r0 + j][i], sl[j][i]);
+        for (int i = 0; i < 4; ++i) av[j][i] = sigmoid_slope_of_e(ez[r0 + j][i], sl[j][i]);
         Dd[j * 64 + l16 * 4 + lg] = d2[j];
         *reinterpret_cast<f32x4_s *>(Dst + j * 256 + l16 * 16 + 4 * lg) = f32x4_s{av[j][0], av[j][1], av[j][2], av[j][3]};
       }
@@ -824,9 +824,16 @@ size_t small_lds_bytes(int n_rows, int n_hidden, int n_in, int threads, bool mom
   return sizeof(float) * (size_t)L.total(momentum);
 }
 
-int small_threads(int n_nets, int hint) {
+// Launch shape of n_nets nets of at most max_hidden units (0: no hint).  Up
+// to one net per CU a net's own epoch counts: 8 waves (86 nets of 120 rows x
+// 63 units, 20 epochs: 192 us against 306 on 4 waves, 302 hidden-split).
+// Above, the chip is shared and the work of a net counts: hidden-split over
+// 16 units (1450 nets of 120 rows x 64 units: 808 us against 1004 on 8 waves
+// and 1450 on 2), 4 waves up to 16 (2759 nets: 563 us against 647 and 875).
+int small_threads(int n_nets, int max_hidden, int n_cu, int hint) {
   if (hint == kHiddenSplit || hint == 128 || hint == 256 || hint == 512) return hint;
-  return n_nets <= 64 ? 512 : 128;
+  if (n_nets <= n_cu) return 512;
+  return max_hidden > 16 ? kHiddenSplit : 256;
 }
 
 size_t small_launch_lds_bytes(int max_rows, int max_hidden, int n_in, int threads, bool momentum) {
