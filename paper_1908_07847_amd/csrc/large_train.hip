@@ -16,16 +16,29 @@
 // the deltas, gb1, gW2, gb2, the loss and the update of the float32 master
 // parameters -- is float32 VALU work.
 //
-// A step is three phases separated by grid barriers:
+// A step is three phases:
 //   1  each workgroup forms a = sigma(z1 + b1) for its tile, row chunk by row
 //      chunk, and the partial output pre-activation over its hidden block;
-//      the Gj partials of a row meet in the workspace (skipped when Gj = 1).
+//      the Gj workgroups of a row block exchange them through the workspace
+//      at a barrier of their own (skipped when Gj = 1).
 //   2  each workgroup completes z2, y, delta2 (and the loss) for its rows,
 //      recomputes its tile of a (cheaper on MFMA than a trip through HBM),
 //      forms delta1 = (delta2 W2) . a (1 - a) with the pre-update W2, and
-//      accumulates its partial gW1, gb1, gW2 (and gb2) over its rows.
+//      accumulates its partial gW1, gb1, gW2 (and gb2) over its rows; a grid
+//      barrier.
 //   3  every workgroup sums a slice of the Gi partials of each parameter in
-//      a fixed order and applies the (optionally Kahan-compensated) update.
+//      a fixed order and applies the (optionally Kahan-compensated) update;
+//      a grid barrier.
+// What bounds a step: for 33-256-3 at 4096-row minibatches its latencies, the
+// products taking a fifth of it.  Exchanges without cache maintenance, the
+// row blocks' own barrier, X and T loaded under the last barrier (from lines
+// brought to the L2 a step earlier), W1 staged from the update's padded copy
+// and the partials summed 16 bytes a load took a step from 26.6 to 18.8 us
+// (float32; bf16 24.4 to 16.1): staging 1.5, phase 1 2.2, its barrier 1.6,
+// output deltas 1.4, gradients 3.4 and their stores 1.3, grid barrier 2.9,
+// update 1.8, grid barrier 2.7.  For 64-1024-3 at 16384 rows the float32
+// products (z1 twice, gW1) and the vector work, which share the SIMDs' float32
+// units, take 54 of 88.5 us (96.5 before); bf16 44, e4m3 48 us.
 // All reductions use fixed orders, so runs are bitwise repeatable.
 #include <hip/hip_runtime.h>
 
@@ -42,6 +55,7 @@
 namespace mlpk {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kMaxNW = 8;    // most waves per workgroup (the LDS plan is sized for it)
@@ -55,14 +69,16 @@ struct LargeArgs {
   const float *X, *T;
   float *theta, *comp, *loss_hist;
   float *z2p;        // [M Gj][b][4] partial output pre-activations
-  float *gp;         // [Gi][M P] partial gradients
+  float *gp;         // [Gi][M Q] partial gradients, in the order of GradOrder
   float *lossp;      // [Gi][M] partial squared errors
   float *amax;       // [2][G] W1 amax partials, [2][G] delta1 amax partials, [G] |X|
   float *acc;        // [M]: epoch loss accumulators
-  unsigned short *w1h;  // [P] bf16 copy of theta written by each update (bf16 operands, one net), else null
+  char *w1c;         // one net: [Hp][DS] copy of W1 written by each update (see w1_copy_stride), else null
   unsigned *bar;     // grid-barrier counters and status words (see GridSync)
+  unsigned *rowbar;  // [Gi M][16] arrivals at the row blocks' barriers
   uint64_t wait_limit;  // wall-clock ticks a grid-barrier wait may take
   int64_t N, b;
+  uint32_t gp_bytes;
   int D, H, Hp, K, Gi, Gj, M, RBP, epochs, steps_per_epoch;
   float lr[kMaxNets];  // learning rate of each net
 };
@@ -70,11 +86,17 @@ struct LargeArgs {
 // ---------------------------------------------------------------- barrier
 // Hierarchical grid barrier.  Every workgroup is resident (cooperative
 // launch).  Arrivals are counted per XCD (the physical XCC id, read from the
-// hardware register); the last arriver of an XCD makes that XCD's L2
-// contents visible device-wide (one agent-scope release per XCD instead of
-// one per workgroup) and bumps the global count; everyone waits for the
-// global count and then acquires.  Counters only grow: the k-th barrier waits
-// for k arrivals per member.
+// hardware register); the last arriver of an XCD bumps the global count;
+// everyone waits for the global count.  Counters only grow: the k-th barrier
+// waits for k arrivals per member.
+//
+// The barrier carries no cache maintenance: everything that workgroups
+// exchange (partial sums, partial gradients, parameters, amax words) is
+// stored and loaded with agent-scope accesses (xld / xst below), which reach
+// the coherence point by themselves, and every wave waits for its own stores
+// before its workgroup arrives.  With an agent release (write back the L2)
+// and acquire (invalidate it) per barrier, one barrier took 4.03 us for 256
+// workgroups arriving together; without, 2.27 us, and X stays in the L2.
 //
 // Every wait is bounded in time: a wait that is still unsatisfied after
 // `limit` ticks of the constant-rate wall clock sets the sticky give-up word
@@ -143,20 +165,93 @@ struct GridSync {
       n_xcd += __hip_atomic_load(bar + 16 * (10 + q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0u;
     return ok;
   }
-  // thread 0 only, between two __syncthreads; false: gave up
-  __device__ bool arrive_and_wait() {
+  // thread 0 only, between two __syncthreads; wait: false if it gave up
+  __device__ void arrive() {
     k += 1;
     const unsigned old =
         __hip_atomic_fetch_add(bar + 16 * (2 + x), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (old + 1 == k * members) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    const bool ok = spin(bar, k * n_xcd);
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    return ok;
+    if (old + 1 == k * members) __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ bool wait() { return spin(bar, k * n_xcd); }
+  __device__ bool arrive_and_wait() {
+    arrive();
+    return wait();
   }
 };
+
+// ---------------------------------------------------------------- exchange
+// Agent-scope accesses of data that workgroups exchange inside a launch:
+// stores go through to the coherence point, loads take nothing from a cache
+// that another XCD's store does not update.  A reader is a barrier after the
+// writer.  xld4 / xld16 / xst16 are buffer accesses with the same scope bit
+// (sc1), 4 or 16 bytes, which the compiler may issue together; a load past
+// the resource's end returns zero.
+__device__ __forceinline__ float xld(const float *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void xst(float *p, float v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+constexpr int kSc1 = 16;   // cache-policy bit of the buffer builtins: sc1 (agent scope)
+constexpr uint32_t kPastEnd = 0xfffffff0u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t xbuf(void *p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ float xld4(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, kSc1));
+}
+__device__ __forceinline__ u32x4 xld16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, kSc1);
+}
+__device__ __forceinline__ void xst16(__amdgpu_buffer_rsrc_t r, uint32_t off, f32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)off, 0, kSc1);
+}
+
+// Order of one net's partial gradient: W1 as the 16 x 16 accumulator tiles of
+// gW1 lie in the lanes (tile, feature block, lane, 4 units), so a lane
+// stores 16 bytes and a wave 1 KB in one piece; then b1 [Hp], W2 [K][Hp] and
+// b2 [4].  Entries of padding units and features are never applied.
+struct GradOrder {
+  int D, H, K, Hp, NFB, nw, q;   // nw: floats of the W1 part, q: of all
+  __host__ __device__ GradOrder(int D_, int H_, int K_, int Hp_) : D(D_), H(H_), K(K_), Hp(Hp_) {
+    NFB = (D + 15) / 16;
+    nw = Hp / 16 * NFB * 256;
+    q = nw + Hp * (1 + K) + 4;
+  }
+  // parameters of entries 4 c .. 4 c + 3: p0 + i stride, those with i < n real
+  __device__ void decode(int c, int &p0, int &stride, int &n, int &h, int &d) const {
+    const int e = 4 * c;
+    if (e < nw) {
+      const int lane = c & 63, tb = c >> 6, tile = tb / NFB, fb = tb - tile * NFB;
+      h = 16 * tile + 4 * (lane >> 4);
+      d = 16 * fb + (lane & 15);
+      p0 = h * D + d;
+      stride = D;
+      n = d < D ? min(4, H - h) : 0;
+    } else {
+      const int r = (e - nw) / Hp, o = e - nw - r * Hp;   // row 0: b1, 1 .. K: W2
+      h = o;
+      d = -1;
+      stride = 1;
+      if (r <= K) {
+        p0 = D * H + r * H + o;
+        n = min(4, H - o);
+      } else {
+        p0 = D * H + H + K * H;
+        n = K;
+      }
+    }
+  }
+};
+
+// Row stride (elements) of the W1 copy each update of a single net writes:
+// rows in the operand type (e4m3, whose scale is known only after the
+// update: float), padded with zeros to whole 16-byte pieces, so that a
+// step stages its slice in one batch of 16-byte loads for every D.
+__host__ __device__ constexpr int w1_copy_stride(int prec, int D) {
+  return prec == 1 ? (D + 7) / 8 * 8 : (D + 3) / 4 * 4;
+}
 
 // ---------------------------------------------------------------- operands
 // OCP e4m3 with a power-of-two scale 2^e: saturate to +-448 first (the
@@ -216,8 +311,7 @@ __device__ __forceinline__ float hidden_sigmoid_slope(float z, float &slope) {
 
 constexpr int kStageU = 16;  // loads in flight per thread while staging
 constexpr int kPre = 32;     // X elements per thread loaded in one batch for a step's first piece
-constexpr int kRedU = 32;    // partial-gradient loads in flight per thread
-constexpr int kUpdU = 4;     // parameters per thread per batch when there are at most 4 partials
+constexpr int kRedU = 12;    // 16-byte partial-gradient loads in flight per thread
 
 // q / D for 0 <= q < 2^16 and 1 <= D <= 64 with md = ceil(2^22 / D): the
 // error md*D - 2^22 <= D - 1 keeps q*md / 2^22 below the next integer.
@@ -234,7 +328,13 @@ __device__ __forceinline__ float load_if(const float *p, const float *safe, bool
   return ok ? v : 0.0f;
 }
 
-// Copy n contiguous floats src[0..n) through registers: each thread loads
+// The same as an agent-scope load (parameters, exchanged between workgroups).
+__device__ __forceinline__ float xld_if(const float *p, const float *safe, bool ok) {
+  const float v = xld(ok ? p : safe);
+  return ok ? v : 0.0f;
+}
+
+// Copy n contiguous floats src[0..n) through registers (agent-scope loads): each thread loads
 // U elements (stride LT, the workgroup's thread count) before storing any,
 // so a batch costs one memory round trip.  store(q, v) places element q.
 template <int U, int LT, typename F>
@@ -244,7 +344,7 @@ __device__ __forceinline__ void stage_flat(const float *src, int n, int tid, F &
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int q = base + u * LT + tid;
-      v[u] = load_if(src + q, src, q < n);
+      v[u] = xld_if(src + q, src, q < n);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -344,7 +444,6 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
   // first unit (within the block) of this wave's local tile hb
   auto tile_unit = [&](int hb) { return (hb * kNW + wave) * 16; };
   const int64_t P = (int64_t)D * H + H + (int64_t)H * K + K;
-  const int64_t PT = P * a.M;           // parameters of all nets
   const int64_t oB1 = (int64_t)D * H, oW2 = oB1 + H, oB2 = oW2 + (int64_t)H * K;
   float *th = a.theta + (int64_t)net * P;   // this workgroup's net
   const LLayout<PREC> L(HB, RBP);
@@ -394,10 +493,36 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
   if (tid == 0) ok_s = gs.init(a.bar, (unsigned)G, a.wait_limit) ? 1 : 0;
   __syncthreads();
   bool ok = ok_s != 0;
+  // A grid barrier in two halves: between them a workgroup does what does not
+  // depend on the others (loads of its own data, index arithmetic), which the
+  // barrier's latency then hides.
+  auto arrive = [&]() {
+    // every wave's stores have reached the coherence point before the
+    // workgroup arrives (__syncthreads alone does not wait for them)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) gs.arrive();
+  };
   // false when the barrier gave up (uniform over the workgroup)
+  auto wait = [&]() -> bool {
+    if (tid == 0 && !gs.wait()) ok_s = 0;
+    __syncthreads();
+    return ok_s != 0;
+  };
   auto barrier = [&]() -> bool {
-    __syncthreads();  // this workgroup's stores are complete (in L2) before it arrives
-    if (tid == 0 && !gs.arrive_and_wait()) ok_s = 0;
+    arrive();
+    return wait();
+  };
+  // The same among the Gj workgroups of this net's row block (the k-th time
+  // it is passed), which exchange the output pre-activations.
+  auto row_barrier = [&](unsigned k) -> bool {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) {
+      unsigned *ctr = a.rowbar + 16 * (gi * a.M + net);
+      __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!gs.spin(ctr, k * (unsigned)a.Gj)) ok_s = 0;
+    }
     __syncthreads();
     return ok_s != 0;
   };
@@ -405,14 +530,26 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
   // ---- one-time: dataset amax of |X| for the e4m3 X scale
   int ex = 0;
   if (PREC == 2 && ok) {
+    // eight loads in flight per thread (an index past the end repeats the first element)
     float m = 0.0f;
     const int64_t nx = a.N * D;
-    for (int64_t q = (int64_t)bid * kLT + tid; q < nx; q += (int64_t)G * kLT) m = fmaxf(m, fabsf(a.X[q]));
+    for (int64_t q0 = (int64_t)bid * kLT + tid; q0 < nx; q0 += (int64_t)8 * G * kLT) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int64_t q = q0 + (int64_t)u * G * kLT;
+        v[u] = a.X[q < nx ? q : 0];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) m = fmaxf(m, fabsf(v[u]));
+    }
     m = wg_reduce_max(m, 0);
-    if (tid == 0) a.amax[4 * G + bid] = m;
+    if (tid == 0) xst(a.amax + 4 * G + bid, m);
     ok = barrier();
+    // one workgroup per CU keeps G <= kLT; a repeated index leaves a maximum unchanged
     float mm = 0.0f;
-    for (int g = 0; g < G; ++g) mm = fmaxf(mm, a.amax[4 * G + g]);
+    for (int g = tid; g < G; g += kLT) mm = fmaxf(mm, xld(a.amax + 4 * G + g));
+    mm = wg_reduce_max(mm, 40);
     ex = e4m3_scale_exp(mm);
   }
   const float sx = ldexpf(1.0f, ex), isx = ldexpf(1.0f, -ex);
@@ -440,7 +577,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
   constexpr int kUnitsPre = kPre / 8;      // units per thread held in xpre
   constexpr int kUnitsBatch = kStageU / 8;  // units per thread per direct batch
   const int n_units = RBP / 8 * D;
-  auto put_unit = [&](int u, const float *v) {
+  auto put_unit = [&](int u, f32x8 v) {
     const int r8 = div_by(u, mdD), c = u - r8 * D, rr = r8 * 8;
     if (PREC == 0) {
 #pragma unroll
@@ -464,91 +601,170 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
       *reinterpret_cast<uint64_t *>(reinterpret_cast<uint8_t *>(xt) + c * XTS + rr) = t;
     }
   };
-  // the 8 values of unit u (zero past the real rows of the piece)
-  auto load_unit = [&](const float *src, int rows_, int u, float *v) {
-    const int r8 = div_by(u, mdD), c = u - r8 * D, rr = r8 * 8;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = load_if(src + ((rr + j) * D + c), a.X, u < n_units && rr + j < rows_);
+  // the 8 values of unit u: buffer loads from the piece's real rows, so a row
+  // past them (or a unit past the piece) reads past the end, which is zero
+  auto x_rows = [&](int64_t rb0_, int rows_) {
+    return xbuf(const_cast<float *>(a.X) + rb0_ * D, (uint32_t)(rows_ * D * 4));
   };
-  auto load_x = [&](int st, float (&v)[kPre]) {
+  auto load_unit = [&](__amdgpu_buffer_rsrc_t xr_, int u) -> f32x8 {
+    const int r8 = div_by(u, mdD), c = u - r8 * D;
+    const int off = 4 * (r8 * 8 * D + c);
+    f32x8 v;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      v[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr_, off, 4 * j * D, 0));
+    return v;
+  };
+  // (values and not arrays: they live across the step loop's back edge, and
+  // an array would be kept in scratch memory for it)
+  static_assert(kUnitsPre == 4, "XPre");
+  struct XPre {
+    f32x8 u0, u1, u2, u3;
+  };
+  auto load_x = [&](int st, XPre &v) {
     int64_t rb0_;
     int rows_;
     block_rows(st, 0, rb0_, rows_);
-    const float *src = a.X + rb0_ * D;
+    const __amdgpu_buffer_rsrc_t src = x_rows(rb0_, rows_);
     int tid_o = tid;
     asm volatile("" : "+v"(tid_o));   // addresses formed here, per step, not hoisted out of the loop
-#pragma unroll
-    for (int k = 0; k < kUnitsPre; ++k) load_unit(src, rows_, k * kLT + tid_o, v + 8 * k);
+    v.u0 = load_unit(src, tid_o);
+    v.u1 = load_unit(src, kLT + tid_o);
+    v.u2 = load_unit(src, 2 * kLT + tid_o);
+    v.u3 = load_unit(src, 3 * kLT + tid_o);
   };
-  // stage piece pc of step st; with v (piece 0 only) its first
-  // kUnitsPre * kLT units come from the registers
-  auto store_x = [&](int st, int pc, const float (*v)[kPre]) {
-    int from = 0;
-    if (v) {
-#pragma unroll
-      for (int k = 0; k < kUnitsPre; ++k) {
-        const int u = k * kLT + tid;
-        if (u < n_units) put_unit(u, *v + 8 * k);
-      }
-      from = kUnitsPre * kLT;
-    }
-    if (n_units > from) {
-      int64_t rb0_;
-      int rows_;
-      block_rows(st, pc, rb0_, rows_);
-      const float *src = a.X + rb0_ * D;
-      for (int base = from; base < n_units; base += kUnitsBatch * kLT) {
-        float w[kStageU];
-#pragma unroll
-        for (int k = 0; k < kUnitsBatch; ++k) load_unit(src, rows_, base + k * kLT + tid, w + 8 * k);
-#pragma unroll
-        for (int k = 0; k < kUnitsBatch; ++k) {
-          const int u = base + k * kLT + tid;
-          if (u < n_units) put_unit(u, w + 8 * k);
-        }
-      }
+  // units [from, n_units) of piece pc of step st, in batches
+  auto stage_units = [&](int st, int pc, int from) {
+    if (n_units <= from) return;
+    int64_t rb0_;
+    int rows_;
+    block_rows(st, pc, rb0_, rows_);
+    const __amdgpu_buffer_rsrc_t src = x_rows(rb0_, rows_);
+    static_assert(kUnitsBatch == 2, "batch");
+    for (int base = from; base < n_units; base += 2 * kLT) {
+      const f32x8 w0 = load_unit(src, base + tid), w1 = load_unit(src, base + kLT + tid);
+      if (base + tid < n_units) put_unit(base + tid, w0);
+      if (base + kLT + tid < n_units) put_unit(base + kLT + tid, w1);
     }
   };
-  float xpre[kPre];
+  // the first piece of step st, its first kUnitsPre * kLT units from registers
+  auto store_x = [&](int st, const XPre &v) {
+    if (tid < n_units) put_unit(tid, v.u0);
+    if (kLT + tid < n_units) put_unit(kLT + tid, v.u1);
+    if (2 * kLT + tid < n_units) put_unit(2 * kLT + tid, v.u2);
+    if (3 * kLT + tid < n_units) put_unit(3 * kLT + tid, v.u3);
+    stage_units(st, 0, kUnitsPre * kLT);
+  };
+  XPre xpre;
 
-  // LDS operand padding (feature columns D..DK, hidden rows past H) is
-  // written once here; the per-step staging writes only real entries.
-  for (int q = tid; q < L.b1() / 4; q += kLT) reinterpret_cast<float *>(smb)[q] = 0.0f;
+  // LDS operand padding (feature columns D..DK, hidden rows past H, outputs
+  // past K of W2) is written once here; the per-step staging writes only real entries.
+  for (int q = tid; q < L.d2() / 4; q += kLT) reinterpret_cast<float *>(smb)[q] = 0.0f;
   __syncthreads();
 
+  // ... and so are the zero columns and rows of the W1 copy (read from the
+  // second step on, three barriers later)
+  constexpr int kCE = PREC == 1 ? 2 : 4;      // bytes per element of the copy
+  const int DS = w1_copy_stride(PREC, D);
+  if (a.w1c != nullptr) {
+    for (int q = bid * kLT + tid; q < a.Hp * DS; q += G * kLT) {
+      const int h = q / DS, c = q - h * DS;
+      if (h >= H || c >= D) {
+        if (PREC == 1)
+          __hip_atomic_store(reinterpret_cast<unsigned short *>(a.w1c) + q, (unsigned short)0, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+        else
+          xst(reinterpret_cast<float *>(a.w1c) + q, 0.0f);
+      }
+    }
+  }
+  const GradOrder go(D, H, K, a.Hp);
+  const __amdgpu_buffer_rsrc_t gpr = xbuf(a.gp, a.gp_bytes);
+  const __amdgpu_buffer_rsrc_t thr = xbuf(th, (uint32_t)(P * 4));   // this net's parameters
+
+  // The targets of piece pc of step st (kIt entries (row, output) per
+  // thread); those of the piece that phase 2 starts with load with the
+  // step's X, not after phase 1, where they would be a round trip of their own.
+  constexpr int kIt = 512 * 4 / kLT;
+  const int pc0 = a.Gj > 1 ? NPc - 1 : 0;
+  typedef float fvec __attribute__((ext_vector_type(kIt)));
+  auto load_targets = [&](int st, int pc) -> fvec {
+    fvec tv;
+    int64_t rb0_;
+    int rows_;
+    block_rows(st, pc, rb0_, rows_);
+    const __amdgpu_buffer_rsrc_t tr = xbuf(const_cast<float *>(a.T) + rb0_ * K, (uint32_t)(rows_ * K * 4));
+    int tid_o = tid;
+    asm volatile("" : "+v"(tid_o));
+#pragma unroll
+    for (int it = 0; it < kIt; ++it) {
+      const int q = tid_o + it * kLT, rr = q >> 2, k = q & 3;
+      const uint32_t off = k < K ? 4u * (uint32_t)(rr * K + k) : kPastEnd;
+      tv[it] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(tr, (int)off, 0, 0));
+    }
+    return tv;
+  };
+
+  // With 4 waves (512 registers a lane) a step's X (its first piece) and
+  // targets are loaded between the two halves of the barrier that ends the
+  // previous step; with 8 the 36 values would be spilled, and the loads are
+  // the first of the step.
+  constexpr bool kAhead = NW == 4;
+  fvec tv;
   const int total_steps = a.epochs * a.steps_per_epoch;
+  if (kAhead && ok && total_steps > 0) {
+    load_x(0, xpre);
+    tv = load_targets(0, pc0);
+  }
   int step = 0;
   for (; ok && step < total_steps; ++step) {
     const int e = step / a.steps_per_epoch, sidx = step - e * a.steps_per_epoch;
-    const int64_t r0 = (int64_t)sidx * a.b;
-    const int64_t m = min((int64_t)a.b, a.N - r0);      // rows in this minibatch
-    const int64_t rb0 = r0 + (int64_t)gi * RB;          // first row of this block
+    const int64_t m = min((int64_t)a.b, a.N - (int64_t)sidx * a.b);      // rows in this minibatch
     const int rows_here = (int)max((int64_t)0, min((int64_t)RB, m - (int64_t)gi * RB));
     const float dscale = 2.0f / ((float)m * (float)K);
 
-    // ---- the first piece of this step's row block of X: its loads are
-    // issued first, so they are in flight with the W1 slice's (and the e4m3
-    // scale partials') and the staging costs one memory round trip, not two
-    // (33-256-3, same-box A/B: bf16 6.65 -> 6.43 ms per epoch, e4m3 7.39 ->
-    // 7.20; the wide e4m3 form 15.91 -> 15.19; the wide bf16 form, once its
-    // W1 slice comes from the bf16 copy, 12.84 -> 12.77; the wide float32
-    // form, once its slice is one batch of 16-byte loads, 25.03 -> 24.77).
-    // (Loading it during the previous step's update keeps the values live
-    // across the partial sums, which every instance spills.)
-    //
-    // e4m3: the amax partials of the previous update (W1) and of the
-    // previous step (delta1), issued ahead of X so the scales' reduction
-    // waits for them alone (loaded at every step, without a branch that
-    // would make the compiler wait for them before X; used after the first).
-    // One workgroup per CU keeps G <= kLT, and a repeated index leaves a
-    // maximum unchanged.
+    if (!kAhead) {
+      load_x(step, xpre);
+      tv = load_targets(step, pc0);
+    }
+    // ---- staging.  First the loads that had to wait for the update: b1 and
+    // W2 of the hidden block, its slice of the W1 copy (whole, in one batch),
+    // and for e4m3 the amax partials of the previous update (W1) and of the
+    // previous step (delta1); X, which is in registers by now, goes to LDS
+    // while they fly.  (Loaded at every step, used after the first.  One
+    // workgroup per CU keeps G <= kLT, and a repeated index leaves a maximum
+    // unchanged.)
     float pw = 0.0f, pd = 0.0f;
     if (PREC == 2) {
       const int g = min(tid, G - 1), par = step & 1;
-      pw = a.amax[par * G + g];
-      pd = a.amax[2 * G + (par ^ 1) * G + g];
+      pw = xld(a.amax + par * G + g);
+      pd = xld(a.amax + 2 * G + (par ^ 1) * G + g);
     }
-    load_x(step, xpre);
+    // b1 and W2 of the hidden block: 64-unit runs, (1 + K) HB / 64 of them
+    // dealt to the waves (run, row and offset are scalar values)
+    constexpr int kBW = ((1 + kMaxK) * 4 + kNW - 1) / kNW;
+    const int nb64 = HB / 64;
+    float bw[kBW];
+#pragma unroll
+    for (int u = 0; u < kBW; ++u) {
+      const int run = wave + u * kNW, k = run / nb64, h = gj * HB + (run - k * nb64) * 64 + lane;   // k = 0: b1
+      bw[u] = xld4(thr, k <= K && h < H ? 4u * (uint32_t)(D * H + k * H + h) : kPastEnd);
+    }
+    // the slice of the W1 copy that the previous update wrote (one net, after
+    // the first step of the launch): whole padded rows, 16 bytes a load, at
+    // any D; bf16 operands arrive rounded, half the bytes
+    constexpr int kPE = 16 / kCE;                 // elements per piece
+    constexpr int kV = PREC == 1 ? 4 : 8;         // a 256 x 64 slice on 8 waves in one batch
+    const bool from_copy = a.w1c != nullptr && step > 0;
+    const int ppr = DS / kPE, np = HB * ppr;      // pieces per row, of the slice
+    const __amdgpu_buffer_rsrc_t wr =
+        xbuf(from_copy ? a.w1c + (int64_t)gj * HB * DS * kCE : nullptr, from_copy ? (uint32_t)(HB * DS * kCE) : 0u);
+    int tid_c = tid;
+    asm volatile("" : "+v"(tid_c));               // addresses formed per step (see the X staging)
+    u32x4 wv[kV];
+#pragma unroll
+    for (int u = 0; u < kV; ++u) wv[u] = xld16(wr, (uint32_t)(u * kLT + tid_c) * 16u);
+    store_x(step, xpre);
 
     // ---- scales of this step (e4m3): W1 from the master, delta1 delayed
     int ew = 0, ed = 0;
@@ -556,22 +772,29 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
       const int par = step & 1;
       if (step == 0) {
         float mw = 0.0f;
-        for (int64_t q = tid; q < (int64_t)H * D; q += kLT) mw = fmaxf(mw, fabsf(th[q]));
+        for (int q0 = tid; q0 < H * D; q0 += 16 * kLT) {
+          float v[16];
+#pragma unroll
+          for (int u = 0; u < 16; ++u) v[u] = xld(th + (q0 + u * kLT < H * D ? q0 + u * kLT : 0));
+#pragma unroll
+          for (int u = 0; u < 16; ++u) mw = fmaxf(mw, fabsf(v[u]));
+        }
         ew = e4m3_scale_exp(wg_reduce_max(mw, 0));
-        __syncthreads();
-        // first step: the bound max_h sum_k |W2[k][h]| / (8 m K), in float32, left to right
+        // first step: the bound max_h sum_k |W2[k][h]| / (8 m K), in float32,
+        // each column left to right, threads over columns
         float bound = 0.0f;
-        for (int h = 0; h < H; ++h) {
+        for (int h = tid; h < H; h += kLT) {
           float col = 0.0f;
-          for (int k = 0; k < K; ++k) col = col + fabsf(th[oW2 + (int64_t)k * H + h]);
+          for (int k = 0; k < K; ++k) col = col + fabsf(xld(th + oW2 + (int64_t)k * H + h));
           if (col > bound) bound = col;
         }
+        bound = wg_reduce_max(bound, 48);
         bound = bound / (float)(8 * m * K);
         ed = e4m3_scale_exp(bound);
       } else {
         for (int g = tid + kLT; g < G; g += kLT) {
-          pw = fmaxf(pw, a.amax[par * G + g]);
-          pd = fmaxf(pd, a.amax[2 * G + (par ^ 1) * G + g]);
+          pw = fmaxf(pw, xld(a.amax + par * G + g));
+          pd = fmaxf(pd, xld(a.amax + 2 * G + (par ^ 1) * G + g));
         }
         ew = e4m3_scale_exp(wg_reduce_max(pw, 24));
         ed = e4m3_scale_exp(wg_reduce_max(pd, 32));
@@ -580,96 +803,29 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
     const float sw = ldexpf(1.0f, ew), isw = ldexpf(1.0f, -ew);
     const float sd = ldexpf(1.0f, ed), isd = ldexpf(1.0f, -ed);
 
-    // ---- stage this workgroup's slice of W1 (operand precision), b1, W2.
-    // The slice is a contiguous run of theta; every thread issues all of its
-    // loads before the first store (one memory round trip, not one per row).
+    // ---- this workgroup's slice of W1 (operand precision), b1, W2 to LDS
     {
-      // b1 and W2 of the hidden block: (1 + kMaxK) HB <= 5 kLT values,
-      // loaded together with the first batch of W1
-      constexpr int kBW = ((1 + kMaxK) * 256 + kLT - 1) / kLT;
-      float bw[kBW];
-#pragma unroll
-      for (int u = 0; u < kBW; ++u) {
-        const int q = tid + u * kLT;             // q < HB: b1, else W2 row k = q / HB - 1
-        const int k = q / HB - 1, hl = q - (k + 1) * HB, h = gj * HB + hl;
-        const bool ok = q < (1 + kMaxK) * HB && h < H && k < K;
-        bw[u] = load_if(th + (k < 0 ? oB1 + h : oW2 + (int64_t)k * H + h), th, ok);
-      }
       const int hv = max(0, min(HB, H - gj * HB));          // real hidden units here
-      if (PREC == 1 && a.w1h != nullptr && step > 0) {
-        // bf16, one net, after the first step of the launch: the slice of
-        // the bf16 copy of W1 that the previous update wrote (the rounding
-        // below, done once per parameter instead of once per workgroup):
-        // half the bytes, and with D a multiple of 8 eight values per
-        // 16-byte load, so the whole slice is one batch of loads
-        const unsigned short *hsrc = a.w1h + (int64_t)gj * HB * D;
-        const int n = hv * D;
-        int tid_o = tid;
-        asm volatile("" : "+v"(tid_o));   // addresses formed per step (see the X staging)
-        if ((D & 7) == 0) {
-          constexpr int kV = 4;   // a 256 x 64 slice on 8 waves, a 128 x 64 one on 4
-          for (int base = 0; base < n; base += 8 * kV * kLT) {
-            uint4 v[kV];
-#pragma unroll
-            for (int u = 0; u < kV; ++u) {
-              const int q = base + 8 * (u * kLT + tid_o);
-              v[u] = *reinterpret_cast<const uint4 *>(hsrc + (q < n ? q : 0));
-            }
-#pragma unroll
-            for (int u = 0; u < kV; ++u) {
-              const int q = base + 8 * (u * kLT + tid_o);
-              if (q < n) {
-                const int hl = div_by(q, mdD), c = q - hl * D;   // the 8 values share row hl
-                *reinterpret_cast<uint4 *>(reinterpret_cast<unsigned short *>(w1s) + hl * XROW + c) = v[u];
-              }
-            }
+      if (from_copy) {
+        const uint32_t mdP = ((1u << 22) + (uint32_t)ppr - 1) / (uint32_t)ppr;
+        auto put = [&](int q, u32x4 v) {
+          if (q >= np) return;
+          const int hl = div_by(q, mdP), c = (q - hl * ppr) * kPE;
+          if (PREC == 0) {
+            uint2 *d = reinterpret_cast<uint2 *>(reinterpret_cast<float *>(w1s) + hl * XROW + c);
+            d[0] = uint2{v.x, v.y};
+            d[1] = uint2{v.z, v.w};
+          } else if (PREC == 1) {
+            *reinterpret_cast<u32x4 *>(reinterpret_cast<unsigned short *>(w1s) + hl * XROW + c) = v;
+          } else {
+            const f32x4 f = __builtin_bit_cast(f32x4, v);
+            *reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(w1s) + hl * XROW + c) =
+                pack_e4m3x4(f.x * sw, f.y * sw, f.z * sw, f.w * sw);
           }
-        } else {
-          for (int base = 0; base < n; base += kStageU * kLT) {
-            unsigned short v[kStageU];
+        };
 #pragma unroll
-            for (int u = 0; u < kStageU; ++u) {
-              const int q = base + u * kLT + tid_o;
-              v[u] = hsrc[q < n ? q : 0];
-            }
-#pragma unroll
-            for (int u = 0; u < kStageU; ++u) {
-              const int q = base + u * kLT + tid_o;
-              if (q < n) {
-                const int hl = div_by(q, mdD), c = q - hl * D;
-                reinterpret_cast<unsigned short *>(w1s)[hl * XROW + c] = v[u];
-              }
-            }
-          }
-        }
-      } else if (PREC == 0 && (D & 3) == 0 && (reinterpret_cast<uintptr_t>(th) & 15) == 0) {
-        // float32 with D a multiple of 4 (and theta 16-byte aligned): four
-        // values (of one row) per 16-byte load, the whole slice in one batch
-        // of at most eight loads per thread (a 256 x 64 slice on 8 waves),
-        // and two 8-byte LDS stores
-        const float *w1src = th + (int64_t)gj * HB * D;
-        const int n = hv * D;
-        int tid_o = tid;
-        asm volatile("" : "+v"(tid_o));   // addresses formed per step (see the X staging)
-        constexpr int kV = 8;
-        for (int base = 0; base < n; base += 4 * kV * kLT) {
-          float4 v[kV];
-#pragma unroll
-          for (int u = 0; u < kV; ++u) {
-            const int q = base + 4 * (u * kLT + tid_o);
-            v[u] = *reinterpret_cast<const float4 *>(w1src + (q < n ? q : 0));
-          }
-#pragma unroll
-          for (int u = 0; u < kV; ++u) {
-            const int q = base + 4 * (u * kLT + tid_o);
-            if (q < n) {
-              const int hl = div_by(q, mdD), c = q - hl * D;
-              float2 *d = reinterpret_cast<float2 *>(reinterpret_cast<float *>(w1s) + hl * XROW + c);
-              d[0] = float2{v[u].x, v[u].y};
-              d[1] = float2{v[u].z, v[u].w};
-            }
-          }
-        }
+        for (int u = 0; u < kV; ++u) put(u * kLT + tid_c, wv[u]);
+        for (int q = kV * kLT + tid_c; q < np; q += kLT) put(q, xld16(wr, (uint32_t)q * 16u));   // (4 waves, wide blocks)
       } else {
         const float *w1src = th + (int64_t)gj * HB * D;
         stage_flat<kStageU, kLT>(w1src, hv * D, tid, [&](int q, float v) {
@@ -681,24 +837,32 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
         });
       }
 #pragma unroll
-      for (int u = 0; u < kBW; ++u) {
-        const int q = tid + u * kLT;
-        if (q < HB) b1s[q] = bw[u];
-        else if (q < (1 + kMaxK) * HB) w2s[q - HB] = bw[u];
+      for (int u = 0; u < kBW; ++u) {   // b1s and w2s are adjacent: run r starts at 64 r
+        const int run = wave + u * kNW;
+        if (run < (1 + K) * nb64) b1s[run * 64 + lane] = bw[u];
       }
     }
-    // ---- this step's row block of X (its first piece), loaded at the start
-    // of the step (see there) and stored after the W1 slice.
-    store_x(step, 0, &xpre);
     int cur_piece = 0;   // piece of the row block held in LDS
     auto stage_piece = [&](int pc) {
       if (pc == cur_piece) return;
       __syncthreads();   // every wave is done with the previous piece
-      store_x(step, pc, nullptr);
+      stage_units(step, pc, 0);
       cur_piece = pc;
       __syncthreads();
     };
     __syncthreads();
+
+    // The next step's rows of X and T go into the L2 while this step computes
+    // (one word per 128-byte line, at most one line of each per thread): its
+    // staging then reads them from there and not from HBM.  The words are
+    // waited for with this step's own stores before the first barrier.
+    float warm_x = 0.0f, warm_t = 0.0f;
+    if (step + 1 < total_steps) {
+      const int64_t rn = (int64_t)((step + 1) % a.steps_per_epoch) * a.b + (int64_t)gi * RB;
+      const int64_t xo = rn * D + 32 * tid, to = rn * K + 32 * tid;
+      if (32 * tid < RB * D && xo < a.N * D) warm_x = a.X[xo];
+      if (32 * tid < RB * K && to < a.N * K) warm_t = a.T[to];
+    }
 
     // z1 tiles for rows [c0, c0 + 32) of the block and every hidden block hb
     // of this wave: zt[hb][rs] holds rows c0 + 16 rs + 4 lg + i, hidden unit
@@ -1006,13 +1170,16 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
         float *zrow = a.z2p + rowbase * 4;   // this piece's rows (uniform base, 32-bit offsets)
         if (by_rows) {
           for (int r0 = 16 * wave; r0 < RBP; r0 += 16 * kNW)
-            z2_rowset(r0, [&](int rr, int k, float v) { zrow[rr * 4 + k] = v; });
+            z2_rowset(r0, [&](int rr, int k, float v) { xst(zrow + (rr * 4 + k), v); });
         } else {
           for (int c0 = 0; c0 < RBP; c0 += kRC)
-            z2_chunk(c0, [&](int rr, int k, float v) { zrow[(c0 + rr) * 4 + k] = v; });
+            z2_chunk(c0, [&](int rr, int k, float v) { xst(zrow + ((c0 + rr) * 4 + k), v); });
         }
       }
-      if (!barrier()) { ok = false; break; }
+      asm volatile("" ::"v"(warm_x), "v"(warm_t));   // only their lines were wanted
+      if (!row_barrier((unsigned)step + 1)) { ok = false; break; }
+    } else {
+      asm volatile("" ::"v"(warm_x), "v"(warm_t));
     }
 
     // ================================================================ phase 2
@@ -1053,33 +1220,35 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
       }
       {
         // entries (row, output) of this piece, kIt per thread at the largest
-        // piece; every load (b2, targets, the Gj partials) is issued before
-        // the first use
-        constexpr int kIt = 512 * 4 / kLT;
-        const float *tb = a.T + (rb0 + prow0) * K;   // the piece's targets
-        float zv[kIt], tv[kIt];
-#pragma unroll
-        for (int it = 0; it < kIt; ++it) {
-          const int q = tid + it * kLT, rr = q >> 2, k = q & 3;
-          const bool on = q < RBP * 4 && k < K && rr < prows;
-          zv[it] = load_if(th + oB2 + k, th, on);
-          tv[it] = load_if(tb + (rr * K + k), a.T, on);
-        }
+        // piece; every load (b2, the Gj partials) is issued before the first
+        // use; the first piece's targets were loaded with its X
+        float zv[kIt];
+        if (pc != pc0) tv = load_targets(step, pc);
+        const float b2v = xld4(thr, (tid & 3) < K ? 4u * ((uint32_t)oB2 + (tid & 3)) : kPastEnd);
         if (split) {
-          const float *zb = a.z2p + ((int64_t)(net * a.Gj) * a.b + (int64_t)gi * RB + prow0) * 4;
-#pragma unroll 4
-          for (int g = 0; g < a.Gj; ++g) {
+          // entry q of hidden block g sits at q of that block's rows of the
+          // piece; a block past Gj is an empty resource (zero)
+          float *zb = a.z2p + ((int64_t)(net * a.Gj) * a.b + (int64_t)gi * RB + prow0) * 4;
 #pragma unroll
-            for (int it = 0; it < kIt; ++it) {
-              const int q = tid + it * kLT, rr = q >> 2, k = q & 3;
-              zv[it] += load_if(zb + (int64_t)g * a.b * 4 + q, a.z2p, q < RBP * 4 && k < K && rr < prows);
+          for (int it = 0; it < kIt; ++it) zv[it] = b2v;
+          for (int g0 = 0; g0 < a.Gj; g0 += 4) {
+            float pz[4][kIt];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              const __amdgpu_buffer_rsrc_t zr = xbuf(zb + (int64_t)(g0 + g) * a.b * 4, g0 + g < a.Gj ? RBP * 16u : 0u);
+#pragma unroll
+              for (int it = 0; it < kIt; ++it) pz[g][it] = xld4(zr, 4u * (uint32_t)(tid + it * kLT));
             }
+#pragma unroll
+            for (int it = 0; it < kIt; ++it)
+#pragma unroll
+              for (int g = 0; g < 4; ++g) zv[it] += pz[g][it];
           }
         } else {
 #pragma unroll
           for (int it = 0; it < kIt; ++it) {
-            const int q = tid + it * kLT, rr = q >> 2, k = q & 3;
-            if (q < RBP * 4 && k < K && rr < prows) zv[it] += d2s[q];
+            const int q = tid + it * kLT;
+            zv[it] = b2v + (q < RBP * 4 ? d2s[q] : 0.0f);
           }
         }
 #pragma unroll
@@ -1221,33 +1390,29 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
     if (gj == 0) {
       for (int off = 32; off >= 1; off >>= 1) gb2 += __shfl_xor(gb2, off, kWave);
       sq = wg_reduce_sum(sq, 0);
-      if (tid == 0) a.lossp[(int64_t)gi * a.M + net] = sq;
-      if (lane == 0 && wave < K) a.gp[(int64_t)gi * PT + (int64_t)net * P + oB2 + wave] = gb2;
+      if (tid == 0) xst(a.lossp + (int64_t)gi * a.M + net, sq);
+      if (lane == 0 && wave < K) xst(a.gp + ((int64_t)gi * a.M + net) * go.q + go.nw + a.Hp * (1 + K) + wave, gb2);
     }
 
     // write this workgroup's partial gradients
     {
-      float *gpi = a.gp + (int64_t)gi * PT + (int64_t)net * P;
+      const uint32_t row = (uint32_t)(((int64_t)gi * a.M + net) * go.q);   // floats; gp is under 4 GB
+      float *gpi = a.gp + row;
       const float gscale = PREC == 2 ? isd * isx : 1.0f;
       // lane coordinates made opaque to the compiler here, so the store
       // addresses below are formed per step next to their stores instead of
       // being hoisted out of the step loop (where they would sit in
       // registers, or in scratch, for the whole run)
-      int lg_o = lg, l16_o = l16;
-      asm volatile("" : "+v"(lg_o), "+v"(l16_o));
+      int lane_o = lane;
+      asm volatile("" : "+v"(lane_o));
 #pragma unroll
       for (int hb = 0; hb < NHM; ++hb) {
         if (hb < NHB) {
+          const int tile = gj * NT + hb * kNW + wave;
 #pragma unroll
-          for (int fb = 0; fb < 4; ++fb) {
-            if (fb < NFB) {
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const int h = gj * HB + (hb * kNW + wave) * 16 + 4 * lg_o + i, d = fb * 16 + l16_o;
-                if (h < H && d < D) gpi[h * D + d] = gacc[hb][fb][i] * gscale;
-              }
-            }
-          }
+          for (int fb = 0; fb < 4; ++fb)
+            if (fb < NFB)
+              xst16(gpr, 4u * (row + (uint32_t)((tile * NFB + fb) * 256 + lane_o * 4)), gacc[hb][fb] * gscale);
           float v = gb1[hb];
           v += __shfl_xor(v, 16, kWave);
           v += __shfl_xor(v, 32, kWave);
@@ -1259,142 +1424,143 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
             t += __shfl_xor(t, 32, kWave);
             w[k] = t;
           }
-          const int h = gj * HB + (hb * kNW + wave) * 16 + l16_o;
-          if (lg_o == 0 && h < H) {
-            gpi[oB1 + h] = v;
+          if (lane_o < 16) {
+            float *g1 = gpi + go.nw + tile * 16 + lane_o;
+            xst(g1, v);
 #pragma unroll
             for (int k = 0; k < KO; ++k)
-              if (k < K) gpi[oW2 + (int64_t)k * H + h] = w[k];
+              if (k < K) xst(g1 + (1 + k) * a.Hp, w[k]);
           }
         }
       }
       if (PREC == 2) {
         d1max = wg_reduce_max(d1max, 8);
-        if (tid == 0) a.amax[2 * G + (step & 1) * G + bid] = d1max;
+        if (tid == 0) xst(a.amax + 2 * G + (step & 1) * G + bid, d1max);
       }
     }
-    if (!barrier()) { ok = false; break; }
-
     // ================================================================ phase 3
     // Sum the Gi partials of this workgroup's slice of the parameters (of all
-    // nets) in a fixed order and update the master copy.  Lanes run over
-    // parameters (coalesced reads of each partial row); with few parameters
-    // per workgroup the waves split the partials and meet in LDS.
+    // nets, in quads of the partial order) in a fixed order and update the
+    // master copy.  Between the halves of the barrier: the slice's indices,
+    // parameters and compensation terms, which only this workgroup writes.
+    arrive();
     {
-      const int64_t per = (PT + G - 1) / G;
-      const int64_t p0 = (int64_t)bid * per;
-      const int np = (int)max((int64_t)0, min(PT, p0 + per) - p0);
+      const int QT = go.q / 4 * a.M;               // quads of one row of partials
+      const int per = (QT + G - 1) / G, c0 = bid * per, nq = max(0, min(QT, c0 + per) - c0);
+      const bool few = 2 * nq <= kLT;
+      int tid_o = tid;
+      asm volatile("" : "+v"(tid_o));   // addresses formed per step (see the gradient stores)
+      const uint32_t rowb = (uint32_t)QT * 16u;
+      // few quads, many partials: the threads split a quad's partials into ng
+      // groups of consecutive rows; a thread per parameter, entries tid and
+      // tid + kLT of the slice, applies the sum
+      const int ng = few && nq > 0 ? min(kLT / nq, a.Gi) : 1;
+      float w[2], c[2];
+      int p[2], h[2], d[2], nt[2];
+      bool on[2];
+      int grp = ng, qi = 0;
+      if (few) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int e = tid_o + j * kLT, cq = c0 + (e >> 2);
+          on[j] = e < 4 * nq;
+          nt[j] = a.M == 1 ? 0 : cq / (go.q / 4);
+          int st, n;
+          go.decode(on[j] ? cq - nt[j] * (go.q / 4) : 0, p[j], st, n, h[j], d[j]);
+          on[j] = on[j] && (e & 3) < n;
+          p[j] += (e & 3) * st;
+          if (d[j] >= 0) h[j] += e & 3;
+          const int64_t q = on[j] ? (int64_t)nt[j] * P + p[j] : 0;
+          w[j] = xld(a.theta + q);
+          c[j] = a.comp ? a.comp[q] : 0.0f;
+        }
+        if (nq > 0) {
+          grp = tid_o / nq;
+          qi = tid_o - grp * nq;
+        }
+      }
+      if (!wait()) { ok = false; break; }
       float wmax = 0.0f;
-      auto update = [&](int64_t p, float w, float c, float gsum) {
-        const float lr = a.M == 1 ? a.lr[0] : a.lr[(int)(p / P)];
-        gd_update(w, c, lr, gsum, a.comp != nullptr);
-        a.theta[p] = w;
-        if (PREC == 1 && a.w1h != nullptr) reinterpret_cast<__bf16 *>(a.w1h)[p] = (__bf16)w;
-        if (a.comp) a.comp[p] = c;
-        if (p < oB1) wmax = fmaxf(wmax, fabsf(w));
-      };
-      // sum of partials g in [g0, g1) of parameter p, in increasing g; the
-      // loads of a batch are all issued before the first add.  g0 and g1 are
-      // uniform over the wave, so the batches need no lane masks; each load
-      // is a uniform partial-row base plus the lane's 32-bit byte offset
-      // (Gi PT < 2^30 floats).
-      auto psum = [&](int64_t p, int g0, int g1) {
-        g0 = __builtin_amdgcn_readfirstlane(g0);
-        g1 = __builtin_amdgcn_readfirstlane(g1);
-        uint32_t pq = (uint32_t)p * 4u;
-        asm volatile("" : "+v"(pq));   // formed per step (see the gradient stores)
-        const char *gpb = reinterpret_cast<const char *>(a.gp);
-        const uint64_t rowb = (uint64_t)PT * 4u;
-        float sum = 0.0f;
-        int gb = g0;
-        for (; gb + kRedU <= g1; gb += kRedU) {
-          const char *base = gpb + (uint64_t)gb * rowb;
-          float v[kRedU];
-#pragma unroll
-          for (int u = 0; u < kRedU; ++u) v[u] = *reinterpret_cast<const float *>(base + u * rowb + pq);
-#pragma unroll
-          for (int u = 0; u < kRedU; ++u) sum += v[u];
-        }
-        if (gb < g1) {
-          // the last, partial batch: a partial past g1 (uniform test) reads
-          // partial g0 instead and adds zero, so every load is issued at once
-          const char *base = gpb + (uint64_t)gb * rowb, *safe = gpb + (uint64_t)g0 * rowb;
-          float v[kRedU];
-#pragma unroll
-          for (int u = 0; u < kRedU; ++u)
-            v[u] = *reinterpret_cast<const float *>((gb + u < g1 ? base + u * rowb : safe) + pq);
-#pragma unroll
-          for (int u = 0; u < kRedU; ++u) sum += gb + u < g1 ? v[u] : 0.0f;
-        }
-        return sum;
-      };
-      if (np <= 64 && a.Gi >= kNW) {
-        // few parameters, many partials: the waves split the partials and
-        // meet in LDS (fixed tree)
-        const int g0 = (a.Gi * wave) / kNW, g1 = (a.Gi * (wave + 1)) / kNW;
-        float w = 0.0f, c = 0.0f, sum = 0.0f;
-        if (lane < np) {
-          if (wave == 0) {
-            w = a.theta[p0 + lane];
-            c = a.comp ? a.comp[p0 + lane] : 0.0f;
+      // the loss partials of net bid (workgroup n keeps net n's loss), issued
+      // with the rest: lanes take every 64th row block
+      float sl = 0.0f;
+      if (bid < a.M && wave == kNW - 1)
+        for (int g = lane; g < a.Gi; g += kWave) sl += xld(a.lossp + (int64_t)g * a.M + bid);
+      auto update = [&](int nt, int p, int h, int d, float w, float c, float gsum) {
+        gd_update(w, c, a.lr[nt], gsum, a.comp != nullptr);
+        const int64_t q = (int64_t)nt * P + p;
+        xst(a.theta + q, w);
+        if (a.comp) a.comp[q] = c;
+        if (d >= 0) {
+          if (PREC == 2) wmax = fmaxf(wmax, fabsf(w));
+          if (a.w1c != nullptr) {
+            if (PREC == 1)
+              __hip_atomic_store(reinterpret_cast<unsigned short *>(a.w1c) + h * DS + d,
+                                 __builtin_bit_cast(unsigned short, (__bf16)w), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+            else
+              xst(reinterpret_cast<float *>(a.w1c) + h * DS + d, w);
           }
-          sum = psum(p0 + lane, g0, g1);
         }
-        z2w[wave * 64 + lane] = sum;
+      };
+      if (few) {
+        // 16 bytes a load, kRedU in flight (a row past the group's end reads
+        // past the buffer: zero); the groups meet in LDS
+        if (grp < ng) {
+          const int g0 = a.Gi * grp / ng, g1 = a.Gi * (grp + 1) / ng;
+          const uint32_t at = (uint32_t)(c0 + qi) * 16u;
+          f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+          for (int gb = g0; gb < g1; gb += kRedU) {
+            u32x4 v[kRedU];
+#pragma unroll
+            for (int u = 0; u < kRedU; ++u) v[u] = xld16(gpr, gb + u < g1 ? (uint32_t)(gb + u) * rowb + at : kPastEnd);
+#pragma unroll
+            for (int u = 0; u < kRedU; ++u) sum += __builtin_bit_cast(f32x4, v[u]);
+          }
+          *reinterpret_cast<f32x4 *>(z2w + 4 * tid_o) = sum;   // [group][quad]
+        }
         __syncthreads();
-        if (wave == 0 && lane < np) {
-          float v[kNW];
 #pragma unroll
-          for (int w8 = 0; w8 < kNW; ++w8) v[w8] = z2w[w8 * 64 + lane];
-#pragma unroll
-          for (int st = 1; st < kNW; st *= 2)
-#pragma unroll
-            for (int w8 = 0; w8 < kNW; w8 += 2 * st) v[w8] += v[w8 + st];
-          update(p0 + lane, w, c, v[0]);
-        }
-      } else if (a.Gi <= 4) {
-        // many parameters, at most 4 partials each (nets sharing X): kUpdU
-        // parameters per thread per batch, all their loads issued together
-        for (int q0 = 0; q0 < np; q0 += kUpdU * kLT) {
-          float w[kUpdU], c[kUpdU], v[kUpdU][4];
-#pragma unroll
-          for (int u = 0; u < kUpdU; ++u) {
-            const int q = q0 + u * kLT + tid;
-            const bool on = q < np;
-            const int64_t pp = p0 + (on ? q : 0);
-            w[u] = a.theta[pp];
-            c[u] = a.comp ? a.comp[pp] : 0.0f;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) v[u][g] = load_if(a.gp + (int64_t)g * PT + pp, a.gp, g < a.Gi);
-          }
-#pragma unroll
-          for (int u = 0; u < kUpdU; ++u) {
-            const int q = q0 + u * kLT + tid;
-            if (q < np) {
-              float sum = v[u][0];
-#pragma unroll
-              for (int g = 1; g < 4; ++g)
-                if (g < a.Gi) sum += v[u][g];
-              update(p0 + q, w[u], c[u], sum);
-            }
+        for (int j = 0; j < 2; ++j) {
+          if (on[j]) {
+            const int e = tid_o + j * kLT;
+            float sum = z2w[e];
+            for (int g = 1; g < ng; ++g) sum += z2w[4 * g * nq + e];
+            update(nt[j], p[j], h[j], d[j], w[j], c[j], sum);
           }
         }
       } else {
-        // one parameter per thread, all of its partials in flight at once
-        for (int q = tid; q < np; q += kLT) {
-          const float w = a.theta[p0 + q], c = a.comp ? a.comp[p0 + q] : 0.0f;
-          update(p0 + q, w, c, psum(p0 + q, 0, a.Gi));
+        // many quads (nets sharing X, small grids): a thread per quad
+        for (int q0 = tid_o; q0 < nq; q0 += kLT) {
+          const int cq = c0 + q0, nt = a.M == 1 ? 0 : cq / (go.q / 4);
+          int p, st, n, h, d;
+          go.decode(cq - nt * (go.q / 4), p, st, n, h, d);
+          float w[4], c[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int64_t q = (int64_t)nt * P + (i < n ? p + i * st : 0);
+            w[i] = xld(a.theta + q);
+            c[i] = a.comp ? a.comp[q] : 0.0f;
+          }
+          const uint32_t at = (uint32_t)cq * 16u;
+          f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+          for (int gb = 0; gb < a.Gi; gb += 4) {
+            u32x4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = xld16(gpr, gb + u < a.Gi ? (uint32_t)(gb + u) * rowb + at : kPastEnd);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) sum += __builtin_bit_cast(f32x4, v[u]);
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (i < n) update(nt, p + i * st, d >= 0 ? h + i : h, d, w[i], c[i], sum[i]);
         }
       }
       if (PREC == 2) {
         wmax = wg_reduce_max(wmax, 16);
-        if (tid == 0) a.amax[((step + 1) & 1) * G + bid] = wmax;
+        if (tid == 0) xst(a.amax + ((step + 1) & 1) * G + bid, wmax);
       }
-      if (bid < a.M && wave == 0) {
-        // workgroup n keeps net n's loss: lanes take every 64th row block,
-        // then a fixed butterfly
-        float sl = 0.0f;
-        for (int g = lane; g < a.Gi; g += kWave) sl += a.lossp[(int64_t)g * a.M + bid];
+      if (bid < a.M && wave == kNW - 1) {   // a fixed butterfly over the lanes
         sl = wave_sum(sl);
         if (lane == 0) {
           const float lstep = sl / ((float)m * (float)K);
@@ -1405,7 +1571,12 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
         }
       }
     }
-    if (!barrier()) { ok = false; break; }
+    arrive();
+    if (kAhead && step + 1 < total_steps) {
+      load_x(step + 1, xpre);
+      tv = load_targets(step + 1, pc0);
+    }
+    if (!wait()) { ok = false; break; }
   }
   // a wait gave up: every workgroup has left the step loop; the losses of
   // the epoch that failed and of every later epoch are NaN (the parameters
@@ -1496,6 +1667,7 @@ namespace mlph {
 namespace {
 
 constexpr int kMaxRowBlocks = 256, kMaxHiddenBlocks = 16;
+constexpr int kMaxGrid = 256;   // workgroups of a launch (one per CU), which sizes the workspace
 constexpr size_t kLdsLimit = 160 * 1024;
 int g_grid_rows = 0, g_grid_hidden = 0, g_waves = 0;  // launch hint (0: automatic)
 constexpr int64_t kDefaultWaitUs = 5000000;  // a grid-barrier wait gives up after 5 s
@@ -1551,26 +1723,30 @@ int min_hidden_blocks(int H) {
 // status words come first, so the status of the last launch sits at a fixed
 // place (mlp_workspace_status reads it).
 struct WsLayout {
-  size_t bar, z2p, gp, lossp, amax, acc, w1h, total;
+  size_t bar, rowbar, z2p, gp, gp_bytes, lossp, amax, acc, w1c, total;
 };
 
 WsLayout ws_layout(const mlp_config &c, int M, int Gi, int Gj) {
   const int64_t b = batch_of(c);
-  const int64_t P = (int64_t)c.n_in * c.n_hidden + c.n_hidden + (int64_t)c.n_hidden * c.n_out + c.n_out;
-  const int64_t bp = (b + 31) / 32 * 32 * 2;   // rows padded for any Gi that divides the block
+  const int Hp = (c.n_hidden + 64 * Gj - 1) / (64 * Gj) * 64 * Gj;
+  const mlpk::GradOrder go(c.n_in, c.n_hidden, c.n_out, Hp);
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
   WsLayout w{};
   size_t o = 0;
   static_assert(sizeof(unsigned) * mlpk::kBarWords <= kStatusBytes, "status block");
   w.bar = o; o += kStatusBytes;
-  w.z2p = o; o += up(sizeof(float) * (size_t)M * Gj * bp * 4);
-  w.gp = o; o += up(sizeof(float) * (size_t)Gi * M * P);
+  w.rowbar = o; o += up(sizeof(unsigned) * 16 * (size_t)Gi * M);   // zeroed with the counters before it
+  w.z2p = o; o += up(sizeof(float) * (size_t)M * Gj * b * 4);
+  w.gp = o; w.gp_bytes = sizeof(float) * (size_t)Gi * M * go.q; o += up(w.gp_bytes);
   w.lossp = o; o += up(sizeof(float) * (size_t)Gi * M);
   w.amax = o; o += up(sizeof(float) * (size_t)5 * Gi * M * Gj);
   w.acc = o; o += up(sizeof(float) * (size_t)(M + 4));
-  // bf16 operands, one net: the bf16 copy of the parameters the update writes
-  w.w1h = 0;
-  if (c.prec == MLP_BF16 && M == 1) { w.w1h = o; o += up(sizeof(unsigned short) * (size_t)P); }
+  // one net: the copy of W1 the update writes
+  w.w1c = 0;
+  if (M == 1) {
+    w.w1c = o;
+    o += up((size_t)Hp * mlpk::w1_copy_stride(c.prec, c.n_in) * (c.prec == MLP_BF16 ? 2 : 4));
+  }
   w.total = o;
   return w;
 }
@@ -1614,7 +1790,7 @@ static bool plan_for(const mlp_config &c, int M, int n_cu, Plan *pl, std::string
   // one workgroup per CU: 8 waves (two per SIMD) when the hidden block has
   // a tile for each, else 4
   const int G = Gi * M * Gj;
-  if (G > n_cu) { *why = "grid above one workgroup per CU"; return false; }
+  if (G > std::min(n_cu, kMaxGrid)) { *why = "grid above one workgroup per CU"; return false; }
   pl->Gi = Gi;
   pl->Gj = Gj;
   pl->Hp = Hp;
@@ -1689,7 +1865,7 @@ mlp_status large_workspace_bytes(const mlp_config &c, int n_nets, size_t *bytes)
   size_t best = 0;
   if (n_nets == 1) {
     for (int gj = 1; gj <= kMaxHiddenBlocks; gj *= 2)
-      for (int gi = 1; gi <= kMaxRowBlocks; gi *= 2) best = std::max(best, ws_layout(c, 1, gi, gj).total);
+      for (int gi = 1; gi * gj <= kMaxGrid; gi *= 2) best = std::max(best, ws_layout(c, 1, gi, gj).total);
   } else {
     const int gj = min_hidden_blocks(c.n_hidden);
     for (int gi = 1; gi <= max_row_blocks(n_nets, gj); gi *= 2)
@@ -1747,8 +1923,10 @@ mlp_status large_train(const mlp_config &c, int n_nets, const float *lrs, const 
   a.lossp = reinterpret_cast<float *>(w + wl.lossp);
   a.amax = reinterpret_cast<float *>(w + wl.amax);
   a.acc = reinterpret_cast<float *>(w + wl.acc);
-  a.w1h = wl.w1h ? reinterpret_cast<unsigned short *>(w + wl.w1h) : nullptr;
+  a.w1c = wl.w1c ? w + wl.w1c : nullptr;
+  a.gp_bytes = (uint32_t)wl.gp_bytes;
   a.bar = reinterpret_cast<unsigned *>(w + wl.bar);
+  a.rowbar = reinterpret_cast<unsigned *>(w + wl.rowbar);
   a.N = c.n_rows;
   a.b = b;
   a.D = (int)D;
@@ -1766,7 +1944,9 @@ mlp_status large_train(const mlp_config &c, int n_nets, const float *lrs, const 
   a.wait_limit = wait_ticks(err, &tick_ok);
   if (!tick_ok) return MLP_ERR_HIP;
 
-  hipLaunchKernelGGL(mlpk::k_zero_u32, dim3(1), dim3(256), 0, s, a.bar, mlpk::kBarWords);
+  // the status block and the row blocks' counters behind it
+  hipLaunchKernelGGL(mlpk::k_zero_u32, dim3(1), dim3(256), 0, s, a.bar,
+                     (int)((wl.rowbar - wl.bar) / sizeof(unsigned)) + 16 * pl.Gi * n_nets);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { *err = hipGetErrorString(e); return MLP_ERR_HIP; }
 
