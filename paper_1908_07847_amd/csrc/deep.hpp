@@ -29,6 +29,28 @@ struct DeepPlan {
 // bytes (or a width or the layer count is out of range).
 bool deep_plan(int L, const int32_t *widths, int64_t n, size_t lds_max, DeepPlan *p);
 
+// LDS plan of the matrix-core form (floats, every array 16-byte aligned): rows
+// padded to 16, every layer input [rows][16 tiles + 4], W_l [16 tiles][16
+// tiles + 4] and b_l zero-padded, one packed partial gradient per wave that
+// owns rows.
+constexpr int kDeepTileWidth = 64;   // widest layer output
+constexpr int kDeepTileWaves = 16;
+struct DeepTilePlan {
+  int L, n, P, NW, NA, NPT;        // waves, waves that own rows, row tiles
+  int w[kDeepMaxLayers + 1], wt[kDeepMaxLayers + 1];   // widths, in 16-unit tiles
+  int poff[kDeepMaxLayers + 1];    // packed offset of W_l (b_l follows it)
+  int aoff[kDeepMaxLayers], sa[kDeepMaxLayers];        // input of layer l and its row stride
+  int woff[kDeepMaxLayers], boff[kDeepMaxLayers];      // W_l (row stride sa[l]) and b_l
+  int toff, st;                    // targets and their row stride
+  int cp, mo, part, dst, red, total;   // compensation, parameter places, partials, staging, loss
+};
+// false when a layer output is wider than kDeepTileWidth or the plan does
+// not fit in `lds_max` bytes.
+bool deep_tile_plan(int L, const int32_t *widths, int64_t n, size_t lds_max, DeepTilePlan *p);
+
+hipError_t launch_deep_train_tiled(const DeepTilePlan &p, int act, const float *X, const float *T, float *theta,
+                                   float *comp, float lr, int epochs, float *loss_hist, hipStream_t s);
+
 hipError_t launch_deep_train(const DeepPlan &p, int act, const float *X, const float *T, float *theta,
                              float *comp, float lr, int epochs, float *loss_hist, hipStream_t s);
 

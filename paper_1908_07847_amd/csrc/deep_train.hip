@@ -206,9 +206,295 @@ __global__ __launch_bounds__(mlph::kDeepThreads) void k_deep_train(
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same training loop on the matrix cores, for layer outputs of up to 64
+// units: every wave owns 16-row tiles and takes them through all layers,
+// forward and back, without a barrier (rows do not interact); only the
+// gradients meet.  Per row tile and layer, on v_mfma_f32_16x16x4_f32:
+//   z^T = W a^T          M = units, N = rows: a lane holds one row and four
+//                        units of a tile, which are the next layer's (and the
+//                        delta's) operands as they lie, the contraction index
+//                        running over 4 lg + step; b starts the accumulator
+//   delta_l-1^T = W^T delta_l^T . slope      the same way, downwards
+//   gW = delta^T a       M = units, N = inputs, K = the tile's rows, both
+//                        operands transposed through LDS
+// and gb by row sums over 16 lanes.  Each wave writes its partial gradient
+// once; after a barrier the owners of the parameters add the partials in wave
+// order and update; a second barrier publishes the weights.
+// Bound: one workgroup's chain of dependent products, LDS reads and
+// activations.  The lane-per-entry form above reads both operands of every
+// product from LDS one float at a time and passes eight barriers per epoch of
+// a three-layer network: 11.6 us for 33-16-16-3 on 120 rows.
+using mlph::DeepTilePlan;
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+template <int HTM, int ACT>
+__global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
+    DeepTilePlan p, const float *__restrict__ X, const float *__restrict__ T, float *__restrict__ theta,
+    float *__restrict__ comp, float lr, int epochs, float *__restrict__ loss_hist) {
+  extern __shared__ float4 smem4[];
+  float *sm = reinterpret_cast<float *>(smem4);
+  const int NT = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lg = lane >> 4;
+  const int L = p.L, n = p.n, P = p.P, K = p.w[L];
+  const bool compensated = comp != nullptr;
+
+  // ---- rows, targets and parameters; everything else (padding) is zero
+  for (int i = tid; i < p.total; i += NT) sm[i] = 0.0f;
+  __syncthreads();
+  for (int i = tid; i < n * p.w[0]; i += NT) {
+    const int r = i / p.w[0], c = i - r * p.w[0];
+    sm[p.aoff[0] + r * p.sa[0] + c] = X[i];
+  }
+  for (int i = tid; i < n * K; i += NT) {
+    const int r = i / K, k = i - r * K;
+    sm[p.toff + r * p.st + k] = T[i];
+  }
+  int *place = reinterpret_cast<int *>(sm + p.mo);   // LDS place of packed parameter q
+  for (int q = tid; q < P; q += NT) {
+    int l = 0;
+    while (l + 1 < L && q >= p.poff[l + 1]) ++l;
+    const int wi = p.w[l], o = q - p.poff[l], nw = wi * p.w[l + 1];
+    const int at = o < nw ? p.woff[l] + o / wi * p.sa[l] + o % wi : p.boff[l] + (o - nw);
+    place[q] = at;
+    sm[at] = theta[q];
+    sm[p.cp + q] = compensated ? comp[q] : 0.0f;
+  }
+  __syncthreads();
+
+  const float dscale = 2.0f / ((float)n * (float)K);
+  const float inv_nk = 1.0f / ((float)n * (float)K);
+  float *Dst = sm + p.dst + wave * (HTM * 256);
+  float *Part = sm + p.part + wave * P;
+
+  for (int e = 0; e < epochs; ++e) {
+    float sq = 0.0f;
+    for (int rt = wave; rt < p.NPT; rt += p.NW) {
+      const int row0 = rt * 16, row = row0 + l16;
+      const bool again = rt != wave;   // a further tile adds to the wave's partial
+      // ---- feed forward
+      f32x4_t a[HTM];
+      for (int l = 0; l < L; ++l) {
+        const int OT = p.wt[l + 1], IT = p.wt[l], wi = p.w[l], s0 = p.sa[l];
+        const float *W = sm + p.woff[l] + l16 * s0 + 4 * lg;
+        f32x4_t z[HTM];
+#pragma unroll
+        for (int t = 0; t < HTM; ++t)
+          z[t] = t < OT ? *reinterpret_cast<const f32x4_t *>(sm + p.boff[l] + 16 * t + 4 * lg) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        auto tile = [&](int it, f32x4_t in) {   // inputs 16 it .. of this row
+#pragma unroll
+          for (int t = 0; t < HTM; ++t) {
+            if (t < OT) {
+              const f32x4_t wv = *reinterpret_cast<const f32x4_t *>(W + t * 16 * s0 + 16 * it);
+#pragma unroll
+              for (int s = 0; s < 4; ++s)
+                if (16 * it + s < wi) z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[s], in[s], z[t], 0, 0, 0);
+            }
+          }
+        };
+        if (l == 0) {
+          const float *x = sm + p.aoff[0] + row * s0 + 4 * lg;
+          for (int it = 0; it < IT; ++it) tile(it, *reinterpret_cast<const f32x4_t *>(x + 16 * it));
+        } else {
+#pragma unroll
+          for (int it = 0; it < HTM; ++it)
+            if (it < IT) tile(it, a[it]);
+        }
+        const bool hidden = l < L - 1;
+#pragma unroll
+        for (int t = 0; t < HTM; ++t) {
+          if (t < OT) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[t][i] = (hidden && ACT == 1) ? tanhf(z[t][i]) : sigmoid(z[t][i]);
+            if (hidden) *reinterpret_cast<f32x4_t *>(sm + p.aoff[l + 1] + row * p.sa[l + 1] + 16 * t + 4 * lg) = a[t];
+          }
+        }
+      }
+      // ---- error and the top layer's delta
+      f32x4_t d[HTM];
+#pragma unroll
+      for (int t = 0; t < HTM; ++t) {
+        d[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if (t < p.wt[L]) {
+          const f32x4_t tv = *reinterpret_cast<const f32x4_t *>(sm + p.toff + row * p.st + 16 * t + 4 * lg);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const bool on = row < n && 16 * t + 4 * lg + i < K;
+            const float y = a[t][i], err = on ? y - tv[i] : 0.0f;
+            sq = fmaf(err, err, sq);
+            d[t][i] = (dscale * err) * (y * (1.0f - y));
+          }
+        }
+      }
+      // ---- backpropagation, top layer first
+      for (int l = L - 1; l >= 0; --l) {
+        const int OT = p.wt[l + 1], IT = p.wt[l], wi = p.w[l], wo = p.w[l + 1], s0 = p.sa[l];
+        const float *A = sm + p.aoff[l];
+        float *G = Part + p.poff[l], *Gb = G + wo * wi;
+        // delta, row-major, for the transposed operand (wave-private); gb
+#pragma unroll
+        for (int t = 0; t < HTM; ++t) {
+          if (t < OT) {
+            *reinterpret_cast<f32x4_t *>(Dst + t * 256 + l16 * 16 + 4 * lg) = d[t];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float v = sum16(d[t][i]);
+              const int o = 16 * t + 4 * lg + i;
+              if (l16 == 0 && o < wo) Gb[o] = again ? Gb[o] + v : v;
+            }
+          }
+        }
+        float dv[HTM][4];
+#pragma unroll
+        for (int t = 0; t < HTM; ++t)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) dv[t][s] = t < OT ? Dst[t * 256 + (4 * s + lg) * 16 + l16] : 0.0f;
+        for (int it = 0; it < IT; ++it) {
+          float av[4];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) av[s] = A[(row0 + 4 * s + lg) * s0 + 16 * it + l16];
+          const int i0 = 16 * it + l16;
+#pragma unroll
+          for (int t = 0; t < HTM; ++t) {
+            if (t < OT) {
+              f32x4_t g = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int s = 0; s < 4; ++s) g = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[t][s], av[s], g, 0, 0, 0);
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const int o = 16 * t + 4 * lg + i;
+                if (o < wo && i0 < wi) {
+                  float *q = G + o * wi + i0;
+                  *q = again ? *q + g[i] : g[i];
+                }
+              }
+            }
+          }
+        }
+        if (l == 0) break;
+        // the delta below, through the pre-update weights
+        f32x4_t dn[HTM];
+        const float *W = sm + p.woff[l] + 4 * lg * s0 + l16;
+#pragma unroll
+        for (int it = 0; it < HTM; ++it) {
+          f32x4_t b = {0.f, 0.f, 0.f, 0.f};
+          if (it < IT) {
+#pragma unroll
+            for (int t = 0; t < HTM; ++t)
+              if (t < OT) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                  b = __builtin_amdgcn_mfma_f32_16x16x4f32(W[(16 * t + s) * s0 + 16 * it], d[t][s], b, 0, 0, 0);
+              }
+            const f32x4_t av = *reinterpret_cast<const f32x4_t *>(A + row * s0 + 16 * it + 4 * lg);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) b[i] *= ACT == 1 ? 1.0f - av[i] * av[i] : av[i] * (1.0f - av[i]);
+          }
+          dn[it] = b;
+        }
+#pragma unroll
+        for (int t = 0; t < HTM; ++t) d[t] = dn[t];
+      }
+    }
+    sq = wave_sum(sq);
+    if (lane == 0) sm[p.red + wave] = sq;
+    __syncthreads();
+
+    // ---- the partials in wave order; the update of every layer at once
+    if (loss_hist && tid == 0) {
+      float s = 0.0f;
+      for (int w = 0; w < p.NA; ++w) s += sm[p.red + w];
+      loss_hist[e] = s * inv_nk;
+    }
+    for (int q = tid; q < P; q += NT) {
+      const float *g0 = sm + p.part + q;
+      float g = g0[0];
+#pragma unroll 8
+      for (int w = 1; w < p.NA; ++w) g += g0[w * P];
+      const int at = place[q];
+      float wv = sm[at], c = sm[p.cp + q];
+      gd_update(wv, c, lr, g, compensated);
+      sm[at] = wv;
+      sm[p.cp + q] = c;
+    }
+    __syncthreads();
+  }
+
+  for (int q = tid; q < P; q += NT) {
+    theta[q] = sm[place[q]];
+    if (compensated) comp[q] = sm[p.cp + q];
+  }
+}
+
 }  // namespace mlpk
 
 namespace mlph {
+
+bool deep_tile_plan(int L, const int32_t *widths, int64_t n, size_t lds_max, DeepTilePlan *p) {
+  if (L < 1 || L > kDeepMaxLayers || n < 1 || n > (1 << 20)) return false;
+  DeepTilePlan q{};
+  const int64_t cap = (int64_t)(lds_max / sizeof(float));
+  int64_t P = 0, o = 0;
+  q.L = L;
+  q.n = (int)n;
+  q.NPT = (int)((n + 15) / 16);
+  auto take = [&](int64_t floats) {   // an array of this many floats, 16-byte aligned
+    const int64_t at = o;
+    o = std::min(o + (floats + 3) / 4 * 4, cap + 1);
+    return (int)at;
+  };
+  for (int l = 0; l <= L; ++l) {
+    if (widths[l] < 1 || widths[l] > kDeepMaxWidth || (l > 0 && widths[l] > kDeepTileWidth)) return false;
+    q.w[l] = widths[l];
+    q.wt[l] = (widths[l] + 15) / 16;
+  }
+  for (int l = 0; l < L; ++l) {
+    q.poff[l] = (int)P;
+    P += (int64_t)widths[l + 1] * widths[l] + widths[l + 1];
+    if (P > cap) return false;
+    q.sa[l] = 16 * q.wt[l] + 4;
+    q.aoff[l] = take((int64_t)16 * q.NPT * q.sa[l]);
+    q.woff[l] = take((int64_t)16 * q.wt[l + 1] * q.sa[l]);
+    q.boff[l] = take(16 * q.wt[l + 1]);
+  }
+  q.poff[L] = (int)P;
+  q.P = (int)P;
+  q.st = 16 * q.wt[L] + 4;
+  q.toff = take((int64_t)16 * q.NPT * q.st);
+  q.cp = take(P);
+  q.mo = take(P);
+  // a wave per row tile (its chain is the epoch's), and at least enough
+  // threads for the update to be one or two parameters each
+  q.NW = std::min(kDeepTileWaves, std::max(q.NPT, (int)std::min<int64_t>(8, (P + 63) / 64)));
+  q.NA = std::min(q.NW, q.NPT);
+  int mt = 1;
+  for (int l = 1; l <= L; ++l) mt = std::max(mt, q.wt[l]);
+  mt = mt <= 2 ? mt : 4;   // the kernel instance
+  q.part = take((int64_t)q.NA * P);
+  q.dst = take((int64_t)q.NW * mt * 256);
+  q.red = take(kDeepTileWaves);
+  if (o > cap) return false;
+  q.total = (int)o;
+  *p = q;
+  return true;
+}
+
+hipError_t launch_deep_train_tiled(const DeepTilePlan &p, int act, const float *X, const float *T, float *theta,
+                                   float *comp, float lr, int epochs, float *loss_hist, hipStream_t s) {
+  using namespace mlpk;
+  int mt = 1;
+  for (int l = 1; l <= p.L; ++l) mt = std::max(mt, p.wt[l]);
+  const void *kern = mt == 1   ? (act == 1 ? (const void *)k_deep_tiled<1, 1> : (const void *)k_deep_tiled<1, 0>)
+                     : mt == 2 ? (act == 1 ? (const void *)k_deep_tiled<2, 1> : (const void *)k_deep_tiled<2, 0>)
+                               : (act == 1 ? (const void *)k_deep_tiled<4, 1> : (const void *)k_deep_tiled<4, 0>);
+  const size_t lds = (size_t)p.total * sizeof(float);
+  hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  DeepTilePlan plan = p;
+  void *args[] = {&plan, &X, &T, &theta, &comp, &lr, &epochs, &loss_hist};
+  e = hipLaunchKernel(kern, dim3(1), dim3(64 * p.NW), args, lds, s);
+  return e == hipSuccess ? hipGetLastError() : e;
+}
 
 bool deep_plan(int L, const int32_t *widths, int64_t n, size_t lds_max, DeepPlan *p) {
   if (L < 1 || L > kDeepMaxLayers || n < 1 || n > (1 << 20)) return false;
