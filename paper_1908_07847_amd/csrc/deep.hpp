@@ -30,26 +30,26 @@ struct DeepPlan {
 bool deep_plan(int L, const int32_t *widths, int64_t n, size_t lds_max, DeepPlan *p);
 
 // LDS plan of the matrix-core form (floats, every array 16-byte aligned): rows
-// padded to 16, every layer input [rows][16 tiles + 4], W_l [16 tiles][16
-// tiles + 4] and b_l zero-padded, one packed partial gradient per wave that
-// owns rows.
-constexpr int kDeepTileWidth = 64;   // widest layer output
+// and units padded to whole 16-row / 16-unit tiles with zeros; row strides of
+// 16 tiles + 4.
+constexpr int kDeepTileWidth = 64;   // widest hidden layer
+constexpr int kDeepTileLayers = 4;
 constexpr int kDeepTileWaves = 16;
 struct DeepTilePlan {
-  int L, n, P, NW, NA, NPT;        // waves, waves that own rows, row tiles
-  int w[kDeepMaxLayers + 1], wt[kDeepMaxLayers + 1];   // widths, in 16-unit tiles
-  int poff[kDeepMaxLayers + 1];    // packed offset of W_l (b_l follows it)
-  int aoff[kDeepMaxLayers], sa[kDeepMaxLayers];        // input of layer l and its row stride
-  int woff[kDeepMaxLayers], boff[kDeepMaxLayers];      // W_l (row stride sa[l]) and b_l
-  int toff, st;                    // targets and their row stride
-  int cp, mo, part, dst, red, total;   // compensation, parameter places, partials, staging, loss
+  int n, P, NW, NPT, ht, it0, sx;   // rows, parameters, waves, row tiles, hidden and input tiles, stride of X
+  int w[kDeepTileLayers + 1];       // widths
+  int poff[kDeepTileLayers];        // packed offset of W_l (b_l follows it)
+  int woff[kDeepTileLayers], boff[kDeepTileLayers], cdelta;   // W_l, b_l; their compensation terms cdelta on
+  int aoff[kDeepTileLayers], doff[kDeepTileLayers];           // input and delta of layer l
+  int toff, red, tiles, total;      // targets, loss slots, weight tiles
 };
-// false when a layer output is wider than kDeepTileWidth or the plan does
-// not fit in `lds_max` bytes.
+// false when the kernel does not cover the layers (two to four, hidden
+// widths up to kDeepTileWidth, at most 16 outputs) or the plan does not fit
+// in `lds_max` bytes.
 bool deep_tile_plan(int L, const int32_t *widths, int64_t n, size_t lds_max, DeepTilePlan *p);
 
-hipError_t launch_deep_train_tiled(const DeepTilePlan &p, int act, const float *X, const float *T, float *theta,
-                                   float *comp, float lr, int epochs, float *loss_hist, hipStream_t s);
+hipError_t launch_deep_train_tiled(const DeepTilePlan &p, int n_layers, int act, const float *X, const float *T,
+                                   float *theta, float *comp, float lr, int epochs, float *loss_hist, hipStream_t s);
 
 hipError_t launch_deep_train(const DeepPlan &p, int act, const float *X, const float *T, float *theta,
                              float *comp, float lr, int epochs, float *loss_hist, hipStream_t s);

@@ -207,28 +207,32 @@ __global__ __launch_bounds__(mlph::kDeepThreads) void k_deep_train(
 }
 
 // ---------------------------------------------------------------------------
-// The same training loop on the matrix cores, for layer outputs of up to 64
-// units: every wave owns 16-row tiles and takes them through all layers,
-// forward and back, without a barrier (rows do not interact); only the
-// gradients meet.  Per row tile and layer, on v_mfma_f32_16x16x4_f32:
-//   z^T = W a^T          M = units, N = rows: a lane holds one row and four
-//                        units of a tile, which are the next layer's (and the
-//                        delta's) operands as they lie, the contraction index
-//                        running over 4 lg + step; b starts the accumulator
-//   delta_l-1^T = W^T delta_l^T . slope      the same way, downwards
-//   gW = delta^T a       M = units, N = inputs, K = the tile's rows, both
-//                        operands transposed through LDS
-// and gb by row sums over 16 lanes.  Each wave writes its partial gradient
-// once; after a barrier the owners of the parameters add the partials in wave
-// order and update; a second barrier publishes the weights.
+// The same training loop on the matrix cores (v_mfma_f32_16x16x4_f32), for two
+// to four layers with outputs of up to 64 units (at most 16 of the top layer).
+// An epoch has two parts, each ended by a barrier:
+//   rows: every wave takes its 16-row tiles through all layers, forward and
+//     back (rows do not interact):
+//       z^T = W a^T            M = units, N = rows: a lane holds one row and
+//                              four units of a tile, which are the next
+//                              layer's (and the delta's) operands as they lie,
+//                              the contraction index running over 4 lg + step;
+//                              b starts the accumulator
+//       delta_l-1^T = W^T delta_l^T . slope      the same way, downwards
+//     and leaves activations and deltas in LDS;
+//   weights: every wave owns 16 x 16 tiles of the weights, sums
+//       gW = delta^T a         M = units, N = inputs, K = all rows
+//     (and gb) in its registers and updates the tile in place.
+// Unit counts are padded to whole tiles with zero weights, so nothing in
+// either part is masked but the last stores.
 // Bound: one workgroup's chain of dependent products, LDS reads and
 // activations.  The lane-per-entry form above reads both operands of every
 // product from LDS one float at a time and passes eight barriers per epoch of
-// a three-layer network: 11.6 us for 33-16-16-3 on 120 rows.
+// a three-layer network: 11.6 us for 33-16-16-3 on 120 rows, here %%US.
 using mlph::DeepTilePlan;
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-template <int HTM, int ACT>
+// HT: unit tiles of the hidden layers; LC: layers; ACT: 0 sigma, 1 tanh.
+template <int HT, int ACT, int LC>
 __global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
     DeepTilePlan p, const float *__restrict__ X, const float *__restrict__ T, float *__restrict__ theta,
     float *__restrict__ comp, float lr, int epochs, float *__restrict__ loss_hist) {
@@ -236,193 +240,212 @@ __global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
   float *sm = reinterpret_cast<float *>(smem4);
   const int NT = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, lg = lane >> 4;
-  const int L = p.L, n = p.n, P = p.P, K = p.w[L];
+  const int n = p.n, P = p.P, K = p.w[LC], NW = p.NW, NPT = p.NPT;
   const bool compensated = comp != nullptr;
+  constexpr int SH = 16 * HT + 4, ST = 20;   // row strides of hidden-layer and output arrays
 
   // ---- rows, targets and parameters; everything else (padding) is zero
   for (int i = tid; i < p.total; i += NT) sm[i] = 0.0f;
   __syncthreads();
-  for (int i = tid; i < n * p.w[0]; i += NT) {
-    const int r = i / p.w[0], c = i - r * p.w[0];
-    sm[p.aoff[0] + r * p.sa[0] + c] = X[i];
+  const int D = p.w[0], SX = p.sx, IT0 = p.it0;
+  for (int i = tid; i < n * D; i += NT) {
+    const int r = i / D, c = i - r * D;
+    sm[p.aoff[0] + r * SX + c] = X[i];
   }
   for (int i = tid; i < n * K; i += NT) {
     const int r = i / K, k = i - r * K;
-    sm[p.toff + r * p.st + k] = T[i];
+    sm[p.toff + r * ST + k] = T[i];
   }
-  int *place = reinterpret_cast<int *>(sm + p.mo);   // LDS place of packed parameter q
-  for (int q = tid; q < P; q += NT) {
+  // LDS place of packed parameter q (weights, or compensation terms cdelta on)
+  auto place = [&](int q) {
     int l = 0;
-    while (l + 1 < L && q >= p.poff[l + 1]) ++l;
+    while (l + 1 < LC && q >= p.poff[l + 1]) ++l;
     const int wi = p.w[l], o = q - p.poff[l], nw = wi * p.w[l + 1];
-    const int at = o < nw ? p.woff[l] + o / wi * p.sa[l] + o % wi : p.boff[l] + (o - nw);
-    place[q] = at;
+    return o < nw ? p.woff[l] + o / wi * (l ? SH : SX) + o % wi : p.boff[l] + (o - nw);
+  };
+  for (int q = tid; q < P; q += NT) {
+    const int at = place(q);
     sm[at] = theta[q];
-    sm[p.cp + q] = compensated ? comp[q] : 0.0f;
+    if (compensated) sm[at + p.cdelta] = comp[q];
   }
   __syncthreads();
 
   const float dscale = 2.0f / ((float)n * (float)K);
   const float inv_nk = 1.0f / ((float)n * (float)K);
-  float *Dst = sm + p.dst + wave * (HTM * 256);
-  float *Part = sm + p.part + wave * P;
 
   for (int e = 0; e < epochs; ++e) {
+    // ======================= rows
     float sq = 0.0f;
-    for (int rt = wave; rt < p.NPT; rt += p.NW) {
-      const int row0 = rt * 16, row = row0 + l16;
-      const bool again = rt != wave;   // a further tile adds to the wave's partial
-      // ---- feed forward
-      f32x4_t a[HTM];
-      for (int l = 0; l < L; ++l) {
-        const int OT = p.wt[l + 1], IT = p.wt[l], wi = p.w[l], s0 = p.sa[l];
-        const float *W = sm + p.woff[l] + l16 * s0 + 4 * lg;
-        f32x4_t z[HTM];
+    for (int rt = wave; rt < NPT; rt += NW) {
+      const int row = rt * 16 + l16;
+      f32x4_t a[LC][HT];   // outputs of layer l (the top layer's in tile 0)
 #pragma unroll
-        for (int t = 0; t < HTM; ++t)
-          z[t] = t < OT ? *reinterpret_cast<const f32x4_t *>(sm + p.boff[l] + 16 * t + 4 * lg) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int l = 0; l < LC; ++l) {
+        constexpr int kTop = LC - 1;
+        const int OT = l == kTop ? 1 : HT;
+        const int s0 = l ? SH : SX;
+        const float *W = sm + p.woff[l] + l16 * s0 + 4 * lg;
+        f32x4_t z[HT];
+#pragma unroll
+        for (int t = 0; t < HT; ++t)
+          if (t < OT) z[t] = *reinterpret_cast<const f32x4_t *>(sm + p.boff[l] + 16 * t + 4 * lg);
         auto tile = [&](int it, f32x4_t in) {   // inputs 16 it .. of this row
 #pragma unroll
-          for (int t = 0; t < HTM; ++t) {
+          for (int t = 0; t < HT; ++t) {
             if (t < OT) {
               const f32x4_t wv = *reinterpret_cast<const f32x4_t *>(W + t * 16 * s0 + 16 * it);
 #pragma unroll
-              for (int s = 0; s < 4; ++s)
-                if (16 * it + s < wi) z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[s], in[s], z[t], 0, 0, 0);
+              for (int s = 0; s < 4; ++s) z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[s], in[s], z[t], 0, 0, 0);
             }
           }
         };
         if (l == 0) {
-          const float *x = sm + p.aoff[0] + row * s0 + 4 * lg;
-          for (int it = 0; it < IT; ++it) tile(it, *reinterpret_cast<const f32x4_t *>(x + 16 * it));
+          const float *x = sm + p.aoff[0] + row * SX + 4 * lg;
+          for (int it = 0; it < IT0; ++it) tile(it, *reinterpret_cast<const f32x4_t *>(x + 16 * it));
         } else {
 #pragma unroll
-          for (int it = 0; it < HTM; ++it)
-            if (it < IT) tile(it, a[it]);
+          for (int it = 0; it < HT; ++it) tile(it, a[l ? l - 1 : 0][it]);
         }
-        const bool hidden = l < L - 1;
 #pragma unroll
-        for (int t = 0; t < HTM; ++t) {
+        for (int t = 0; t < HT; ++t) {
           if (t < OT) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a[t][i] = (hidden && ACT == 1) ? tanhf(z[t][i]) : sigmoid(z[t][i]);
-            if (hidden) *reinterpret_cast<f32x4_t *>(sm + p.aoff[l + 1] + row * p.sa[l + 1] + 16 * t + 4 * lg) = a[t];
+            for (int i = 0; i < 4; ++i) a[l][t][i] = (l < kTop && ACT == 1) ? tanhf(z[t][i]) : sigmoid(z[t][i]);
+            if (l < kTop)
+              *reinterpret_cast<f32x4_t *>(sm + p.aoff[l + 1 < LC ? l + 1 : 0] + row * SH + 16 * t + 4 * lg) = a[l][t];
           }
         }
       }
-      // ---- error and the top layer's delta
-      f32x4_t d[HTM];
+      // error and the top layer's delta
+      f32x4_t d[HT];
+      {
+        const f32x4_t tv = *reinterpret_cast<const f32x4_t *>(sm + p.toff + row * ST + 4 * lg);
 #pragma unroll
-      for (int t = 0; t < HTM; ++t) {
-        d[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        if (t < p.wt[L]) {
-          const f32x4_t tv = *reinterpret_cast<const f32x4_t *>(sm + p.toff + row * p.st + 16 * t + 4 * lg);
+        for (int i = 0; i < 4; ++i) {
+          const float y = a[LC - 1][0][i], err = row < n && 4 * lg + i < K ? y - tv[i] : 0.0f;
+          sq = fmaf(err, err, sq);
+          d[0][i] = (dscale * err) * (y * (1.0f - y));
+        }
+        *reinterpret_cast<f32x4_t *>(sm + p.doff[LC - 1] + row * ST + 4 * lg) = d[0];
+      }
+      // the deltas below, through the pre-update weights
+#pragma unroll
+      for (int l = LC - 1; l > 0; --l) {
+        const int OT = l == LC - 1 ? 1 : HT;
+        f32x4_t dn[HT];
+        const float *W = sm + p.woff[l] + 4 * lg * SH + l16;
+#pragma unroll
+        for (int it = 0; it < HT; ++it) {
+          f32x4_t b = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int t = 0; t < HT; ++t)
+            if (t < OT) {
+#pragma unroll
+              for (int s = 0; s < 4; ++s)
+                b = __builtin_amdgcn_mfma_f32_16x16x4f32(W[(16 * t + s) * SH + 16 * it], d[t][s], b, 0, 0, 0);
+            }
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const bool on = row < n && 16 * t + 4 * lg + i < K;
-            const float y = a[t][i], err = on ? y - tv[i] : 0.0f;
-            sq = fmaf(err, err, sq);
-            d[t][i] = (dscale * err) * (y * (1.0f - y));
+            const float av = a[l - 1][it][i];
+            b[i] *= ACT == 1 ? 1.0f - av * av : av * (1.0f - av);
           }
-        }
-      }
-      // ---- backpropagation, top layer first
-      for (int l = L - 1; l >= 0; --l) {
-        const int OT = p.wt[l + 1], IT = p.wt[l], wi = p.w[l], wo = p.w[l + 1], s0 = p.sa[l];
-        const float *A = sm + p.aoff[l];
-        float *G = Part + p.poff[l], *Gb = G + wo * wi;
-        // delta, row-major, for the transposed operand (wave-private); gb
-#pragma unroll
-        for (int t = 0; t < HTM; ++t) {
-          if (t < OT) {
-            *reinterpret_cast<f32x4_t *>(Dst + t * 256 + l16 * 16 + 4 * lg) = d[t];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const float v = sum16(d[t][i]);
-              const int o = 16 * t + 4 * lg + i;
-              if (l16 == 0 && o < wo) Gb[o] = again ? Gb[o] + v : v;
-            }
-          }
-        }
-        float dv[HTM][4];
-#pragma unroll
-        for (int t = 0; t < HTM; ++t)
-#pragma unroll
-          for (int s = 0; s < 4; ++s) dv[t][s] = t < OT ? Dst[t * 256 + (4 * s + lg) * 16 + l16] : 0.0f;
-        for (int it = 0; it < IT; ++it) {
-          float av[4];
-#pragma unroll
-          for (int s = 0; s < 4; ++s) av[s] = A[(row0 + 4 * s + lg) * s0 + 16 * it + l16];
-          const int i0 = 16 * it + l16;
-#pragma unroll
-          for (int t = 0; t < HTM; ++t) {
-            if (t < OT) {
-              f32x4_t g = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-              for (int s = 0; s < 4; ++s) g = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[t][s], av[s], g, 0, 0, 0);
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const int o = 16 * t + 4 * lg + i;
-                if (o < wo && i0 < wi) {
-                  float *q = G + o * wi + i0;
-                  *q = again ? *q + g[i] : g[i];
-                }
-              }
-            }
-          }
-        }
-        if (l == 0) break;
-        // the delta below, through the pre-update weights
-        f32x4_t dn[HTM];
-        const float *W = sm + p.woff[l] + 4 * lg * s0 + l16;
-#pragma unroll
-        for (int it = 0; it < HTM; ++it) {
-          f32x4_t b = {0.f, 0.f, 0.f, 0.f};
-          if (it < IT) {
-#pragma unroll
-            for (int t = 0; t < HTM; ++t)
-              if (t < OT) {
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-                  b = __builtin_amdgcn_mfma_f32_16x16x4f32(W[(16 * t + s) * s0 + 16 * it], d[t][s], b, 0, 0, 0);
-              }
-            const f32x4_t av = *reinterpret_cast<const f32x4_t *>(A + row * s0 + 16 * it + 4 * lg);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) b[i] *= ACT == 1 ? 1.0f - av[i] * av[i] : av[i] * (1.0f - av[i]);
-          }
+          *reinterpret_cast<f32x4_t *>(sm + p.doff[l - 1] + row * SH + 16 * it + 4 * lg) = b;
           dn[it] = b;
         }
 #pragma unroll
-        for (int t = 0; t < HTM; ++t) d[t] = dn[t];
+        for (int t = 0; t < HT; ++t) d[t] = dn[t];
       }
     }
     sq = wave_sum(sq);
     if (lane == 0) sm[p.red + wave] = sq;
     __syncthreads();
 
-    // ---- the partials in wave order; the update of every layer at once
-    if (loss_hist && tid == 0) {
-      float s = 0.0f;
-      for (int w = 0; w < p.NA; ++w) s += sm[p.red + w];
-      loss_hist[e] = s * inv_nk;
+    // ======================= weights: tile j (of layer l, units 16 ot, inputs 16 it)
+    if (loss_hist && wave == NW - 1) {
+      // (the last wave owns the fewest tiles)
+      float s = lane < min(NW, NPT) ? sm[p.red + lane] : 0.0f;
+      s = wave_sum(s);
+      if (lane == 0) loss_hist[e] = s * inv_nk;
     }
-    for (int q = tid; q < P; q += NT) {
-      const float *g0 = sm + p.part + q;
-      float g = g0[0];
-#pragma unroll 8
-      for (int w = 1; w < p.NA; ++w) g += g0[w * P];
-      const int at = place[q];
-      float wv = sm[at], c = sm[p.cp + q];
-      gd_update(wv, c, lr, g, compensated);
-      sm[at] = wv;
-      sm[p.cp + q] = c;
+    for (int j = wave; j < p.tiles; j += NW) {
+      int l, it, ot;
+      if (j < HT * IT0) {
+        l = 0;
+        it = j / HT;
+        ot = j - it * HT;
+      } else {
+        const int k = j - HT * IT0;
+        l = 1 + min(k / (HT * HT), LC - 2);
+        const int r = k - (l - 1) * HT * HT;
+        it = l == LC - 1 ? r : r / HT;
+        ot = l == LC - 1 ? 0 : r - it * HT;
+      }
+      const int sa = l ? SH : SX, sd = l == LC - 1 ? ST : SH, wi = p.w[l], wo = p.w[l + 1];
+      const float *Dp = sm + p.doff[l] + lg * sd + 16 * ot + l16;
+      const float *Ap = sm + p.aoff[l] + lg * sa + 16 * it + l16;
+      // two accumulators, so the chains overlap; a row tile past the end is
+      // not read (NPT odd)
+      f32x4_t g0 = {0.f, 0.f, 0.f, 0.f}, g1 = {0.f, 0.f, 0.f, 0.f};
+      float gb = 0.0f;
+      int rt = 0;
+      for (; rt + 2 <= NPT; rt += 2) {
+        float dv[8], av[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+          dv[s] = Dp[(16 * rt + 4 * s) * sd];
+          av[s] = Ap[(16 * rt + 4 * s) * sa];
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          g0 = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[s], av[s], g0, 0, 0, 0);
+          g1 = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[4 + s], av[4 + s], g1, 0, 0, 0);
+          gb += dv[s] + dv[4 + s];
+        }
+      }
+      if (rt < NPT) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const float dv = Dp[(16 * rt + 4 * s) * sd];
+          g0 = __builtin_amdgcn_mfma_f32_16x16x4f32(dv, Ap[(16 * rt + 4 * s) * sa], g0, 0, 0, 0);
+          gb += dv;
+        }
+      }
+      const int i0 = 16 * it + l16;
+      float *Wt = sm + p.woff[l] + (16 * ot + 4 * lg) * sa + i0;
+      float wv[4], cv[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        wv[i] = Wt[i * sa];
+        cv[i] = Wt[i * sa + p.cdelta];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        gd_update(wv[i], cv[i], lr, g0[i] + g1[i], compensated);
+        if (i0 < wi && 16 * ot + 4 * lg + i < wo) {
+          Wt[i * sa] = wv[i];
+          Wt[i * sa + p.cdelta] = cv[i];
+        }
+      }
+      if (it == 0) {   // the tile that also sums its units' bias gradients
+        gb += __shfl_xor(gb, 16, kWave);
+        gb += __shfl_xor(gb, 32, kWave);
+        const int o = 16 * ot + l16;
+        if (lg == 0 && o < wo) {
+          float *bp = sm + p.boff[l] + o;
+          float b = *bp, c = bp[p.cdelta];
+          gd_update(b, c, lr, gb, compensated);
+          *bp = b;
+          bp[p.cdelta] = c;
+        }
+      }
     }
     __syncthreads();
   }
 
   for (int q = tid; q < P; q += NT) {
-    theta[q] = sm[place[q]];
-    if (compensated) comp[q] = sm[p.cp + q];
+    const int at = place(q);
+    theta[q] = sm[at];
+    if (compensated) comp[q] = sm[at + p.cdelta];
   }
 }
 
@@ -431,62 +454,70 @@ __global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
 namespace mlph {
 
 bool deep_tile_plan(int L, const int32_t *widths, int64_t n, size_t lds_max, DeepTilePlan *p) {
-  if (L < 1 || L > kDeepMaxLayers || n < 1 || n > (1 << 20)) return false;
+  if (L < 2 || L > kDeepTileLayers || n < 1 || n > (1 << 20) || widths[L] > 16) return false;
   DeepTilePlan q{};
   const int64_t cap = (int64_t)(lds_max / sizeof(float));
-  int64_t P = 0, o = 0;
-  q.L = L;
+  int64_t o = 0;
   q.n = (int)n;
   q.NPT = (int)((n + 15) / 16);
-  auto take = [&](int64_t floats) {   // an array of this many floats, 16-byte aligned
-    const int64_t at = o;
-    o = std::min(o + (floats + 3) / 4 * 4, cap + 1);
-    return (int)at;
-  };
+  q.ht = 1;
   for (int l = 0; l <= L; ++l) {
     if (widths[l] < 1 || widths[l] > kDeepMaxWidth || (l > 0 && widths[l] > kDeepTileWidth)) return false;
     q.w[l] = widths[l];
-    q.wt[l] = (widths[l] + 15) / 16;
+    if (l > 0 && l < L) q.ht = std::max(q.ht, (widths[l] + 15) / 16);
   }
+  if (q.ht == 3) q.ht = 4;   // the kernel instances
+  q.it0 = (widths[0] + 15) / 16;
+  q.sx = 16 * q.it0 + 4;
+  const int sh = 16 * q.ht + 4, st = 20;
+  const int64_t rows = 16 * (int64_t)q.NPT;
+  auto take = [&](int64_t floats) {   // an array of this many floats (a multiple of 4)
+    const int64_t at = o;
+    o = std::min(o + floats, cap + 1);
+    return (int)at;
+  };
+  int64_t P = 0;
+  const int64_t w0 = o;
   for (int l = 0; l < L; ++l) {
     q.poff[l] = (int)P;
     P += (int64_t)widths[l + 1] * widths[l] + widths[l + 1];
-    if (P > cap) return false;
-    q.sa[l] = 16 * q.wt[l] + 4;
-    q.aoff[l] = take((int64_t)16 * q.NPT * q.sa[l]);
-    q.woff[l] = take((int64_t)16 * q.wt[l + 1] * q.sa[l]);
-    q.boff[l] = take(16 * q.wt[l + 1]);
+    const int units = l == L - 1 ? 16 : 16 * q.ht;
+    q.woff[l] = take((int64_t)units * (l ? sh : q.sx));
+    q.boff[l] = take(units);
   }
-  q.poff[L] = (int)P;
   q.P = (int)P;
-  q.st = 16 * q.wt[L] + 4;
-  q.toff = take((int64_t)16 * q.NPT * q.st);
-  q.cp = take(P);
-  q.mo = take(P);
-  // a wave per row tile (its chain is the epoch's), and at least enough
-  // threads for the update to be one or two parameters each
-  q.NW = std::min(kDeepTileWaves, std::max(q.NPT, (int)std::min<int64_t>(8, (P + 63) / 64)));
-  q.NA = std::min(q.NW, q.NPT);
-  int mt = 1;
-  for (int l = 1; l <= L; ++l) mt = std::max(mt, q.wt[l]);
-  mt = mt <= 2 ? mt : 4;   // the kernel instance
-  q.part = take((int64_t)q.NA * P);
-  q.dst = take((int64_t)q.NW * mt * 256);
+  q.cdelta = (int)(o - w0);   // compensation terms lie like the weights
+  take(o - w0);
+  for (int l = 0; l < L; ++l) {
+    q.aoff[l] = take(rows * (l ? sh : q.sx));
+    q.doff[l] = take(rows * (l == L - 1 ? st : sh));
+  }
+  q.toff = take(rows * st);
   q.red = take(kDeepTileWaves);
   if (o > cap) return false;
+  q.tiles = q.ht * q.it0 + (L - 2) * q.ht * q.ht + q.ht;
+  q.NW = std::min(kDeepTileWaves, std::max(4, std::max(q.NPT, q.tiles)));
   q.total = (int)o;
   *p = q;
   return true;
 }
 
-hipError_t launch_deep_train_tiled(const DeepTilePlan &p, int act, const float *X, const float *T, float *theta,
-                                   float *comp, float lr, int epochs, float *loss_hist, hipStream_t s) {
+template <int ACT>
+static const void *deep_tiled_kernel(int ht, int L) {
   using namespace mlpk;
-  int mt = 1;
-  for (int l = 1; l <= p.L; ++l) mt = std::max(mt, p.wt[l]);
-  const void *kern = mt == 1   ? (act == 1 ? (const void *)k_deep_tiled<1, 1> : (const void *)k_deep_tiled<1, 0>)
-                     : mt == 2 ? (act == 1 ? (const void *)k_deep_tiled<2, 1> : (const void *)k_deep_tiled<2, 0>)
-                               : (act == 1 ? (const void *)k_deep_tiled<4, 1> : (const void *)k_deep_tiled<4, 0>);
+  if (L == 2)
+    return ht == 1 ? (const void *)k_deep_tiled<1, ACT, 2>
+                   : (ht == 2 ? (const void *)k_deep_tiled<2, ACT, 2> : (const void *)k_deep_tiled<4, ACT, 2>);
+  if (L == 3)
+    return ht == 1 ? (const void *)k_deep_tiled<1, ACT, 3>
+                   : (ht == 2 ? (const void *)k_deep_tiled<2, ACT, 3> : (const void *)k_deep_tiled<4, ACT, 3>);
+  return ht == 1 ? (const void *)k_deep_tiled<1, ACT, 4>
+                 : (ht == 2 ? (const void *)k_deep_tiled<2, ACT, 4> : (const void *)k_deep_tiled<4, ACT, 4>);
+}
+
+hipError_t launch_deep_train_tiled(const DeepTilePlan &p, int n_layers, int act, const float *X, const float *T,
+                                   float *theta, float *comp, float lr, int epochs, float *loss_hist, hipStream_t s) {
+  const void *kern = act == 1 ? deep_tiled_kernel<1>(p.ht, n_layers) : deep_tiled_kernel<0>(p.ht, n_layers);
   const size_t lds = (size_t)p.total * sizeof(float);
   hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;

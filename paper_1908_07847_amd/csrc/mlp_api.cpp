@@ -616,12 +616,13 @@ mlp_status mlp_deep_train(const float *X, const float *T, int64_t n, int32_t n_l
     return fail(MLP_ERR_UNSUPPORTED, "rows, activations, deltas and parameters of this network do not fit in "
                                      "one workgroup's 160 KiB of LDS");
   if (epochs == 0) return MLP_OK;
-  // the matrix-core form where its padded arrays fit too (layer outputs of up
-  // to 64 units); the lane-per-entry form covers the rest
+  // the matrix-core form where it covers the layers and its padded arrays fit
+  // too; the lane-per-entry form covers the rest
   mlph::DeepTilePlan tiles;
   hipError_t e =
       mlph::deep_tile_plan(n_layers, widths, n, 160 * 1024, &tiles)
-          ? mlph::launch_deep_train_tiled(tiles, act, X, T, theta, comp, lr, epochs, loss_hist, (hipStream_t)stream)
+          ? mlph::launch_deep_train_tiled(tiles, n_layers, act, X, T, theta, comp, lr, epochs, loss_hist,
+                                          (hipStream_t)stream)
           : mlph::launch_deep_train(plan, act, X, T, theta, comp, lr, epochs, loss_hist, (hipStream_t)stream);
   return e == hipSuccess ? MLP_OK : hip_fail(e, "mlp_deep_train launch");
 }
