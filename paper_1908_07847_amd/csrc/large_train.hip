@@ -612,7 +612,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
     f32x8 v;
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      v[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr_, off, 4 * j * D, 0));
+      v[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr_, off + 4 * j * D, 0, 0));
     return v;
   };
   // (values and not arrays: they live across the step loop's back edge, and

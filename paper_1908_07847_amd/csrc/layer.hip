@@ -450,7 +450,8 @@ __global__ __launch_bounds__(256, 4) void k_eval_tiled(const mlp_batch_item *__r
     // load with the operands, not after the barrier
     const int rt = (tid >> 2) & 31, kt = tid & 3;
     const bool on_t = rt < rows && kt < K;
-    const float tl = Tn[on_t ? (int64_t)(r0 + rt) * K + kt : 0], bl = b2[kt < K ? kt : 0];
+    const float tl = gld(gbuf(Tn + (int64_t)r0 * K, (uint32_t)(rows * K) * 4u), kt < K ? 4u * (rt * K + kt) : kNoLoad);
+    const float bl = gld(gbuf(b2, K * 4u), 4u * kt);
     float zp[2][4][4];
 #pragma unroll
     for (int rs = 0; rs < 2; ++rs)
@@ -459,36 +460,28 @@ __global__ __launch_bounds__(256, 4) void k_eval_tiled(const mlp_batch_item *__r
 #pragma unroll
         for (int k = 0; k < 4; ++k) zp[rs][i][k] = 0.0f;
     if (wave < HT) {
-      const float *Xc = Xn + (int64_t)r0 * D;
       float xa[2][NS];
+      const __amdgpu_buffer_rsrc_t xc = gbuf(Xn + (int64_t)r0 * D, (uint32_t)(rows * D) * 4u);
+      const __amdgpu_buffer_rsrc_t w1r = gbuf(W1, (uint32_t)(H * D) * 4u);
+      const __amdgpu_buffer_rsrc_t b1r = gbuf(b1, (uint32_t)H * 4u), w2r = gbuf(W2, (uint32_t)(K * H) * 4u);
+      uint32_t co[NS];   // column offsets of the lane, past the end for padding
 #pragma unroll
-      for (int rs = 0; rs < 2; ++rs) {
-        const int r = 16 * rs + l16;
+      for (int s = 0; s < NS; ++s) co[s] = 4 * s + lg < D ? 4u * (4 * s + lg) : kNoLoad;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const int c = 4 * s + lg;
-          const bool on = r < rows && c < D;
-          const float v = Xc[(uint32_t)(on ? r * D + c : 0)];
-          xa[rs][s] = on ? v : 0.0f;
-        }
-      }
+      for (int rs = 0; rs < 2; ++rs)
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+          xa[rs][s] = gld(xc, co[s] + 4u * (uint32_t)((16 * rs + l16) * D));
       for (int t = wave; t < HT; t += 4) {
         const int h = 16 * t + l16;
         const bool hon = h < H;
-        const int ho = hon ? h * D : 0;   // 32-bit offsets from scalar bases throughout
+        const uint32_t ho = 4u * (uint32_t)(h * D);   // (a row past H lies past the end)
         float wv[NS], w2[4];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const int c = 4 * s + lg;
-          const float v = W1[(uint32_t)(ho + (c < D ? c : 0))];
-          wv[s] = hon && c < D ? v : 0.0f;
-        }
-        const float bias = b1[(uint32_t)(hon ? h : 0)];
+        for (int s = 0; s < NS; ++s) wv[s] = gld(w1r, ho + co[s]);
+        const float bias = gld(b1r, 4u * h);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float v = W2[(uint32_t)(hon && k < K ? k * H + h : 0)];
-          w2[k] = hon && k < K ? v : 0.0f;
-        }
+        for (int k = 0; k < 4; ++k) w2[k] = gld(w2r, hon && k < K ? 4u * (uint32_t)(k * H + h) : kNoLoad);
         f32x4_l z[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
         for (int s = 0; s < NS; ++s) {

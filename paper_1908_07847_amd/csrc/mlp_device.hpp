@@ -93,6 +93,19 @@ __device__ __forceinline__ void gd_update(float &w, float &c, float lr, float g,
   }
 }
 
+// Buffer loads: from a uniform base with a 32-bit byte offset; an offset past
+// `bytes` reads zero, so a batch needs no masks and no 64-bit addresses.
+// (Written with clamped 64-bit addresses, a batch of loads was issued one by
+// one, each waited for, where scalar registers ran out.)
+// Resources are under 2 GB, so kNoLoad plus an offset inside one stays past the end.
+constexpr uint32_t kNoLoad = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t gbuf(const float *p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ float gld(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
+
 // Sum over the 64 lanes of a wave, fixed butterfly order (deterministic).
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
