@@ -48,34 +48,25 @@ __device__ __forceinline__ float lane_value(float v, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
-// LDS plan (floats).
-struct SmallLayout {
-  int N, H, D, K, NW, NP, NPT, DA, DK, DN, XS, HP, HT, FT, PW;
-  __host__ __device__ SmallLayout(int n, int h, int d, int k, int nw)
-      : N(n), H(h), D(d), K(k), NW(nw) {
-    NP = (n + 15) / 16 * 16;  // rows padded to 16-row tiles
-    NPT = NP / 16;
-    DA = d + 1;               // features + the constant-1 column
-    DK = (DA + 3) / 4 * 4;    // contraction length of z1 (steps of 4)
-    DN = (DA + 15) / 16 * 16; // feature tiles of gW1
-    FT = DN / 16;
-    XS = DN + 2;              // row stride of X and W1: 16 rows of a tile hit distinct banks
-    HP = (h + 15) / 16 * 16;  // hidden units padded to 16-unit tiles
-    HT = HP / 16;
-    PW = HP * DN + 4 * HP + 4 + 4;  // one wave's partials: gW1 | gW2 | gb2 | loss
-  }
-  __host__ __device__ int xs() const { return 0; }                  // [NP][XS]
-  __host__ __device__ int w1() const { return xs() + NP * XS; }     // [HP][XS] master W1|b1
-  __host__ __device__ int w2() const { return w1() + HP * XS; }     // [4][HP]  master W2
-  __host__ __device__ int b2() const { return w2() + 4 * HP; }      // [4]      master b2
-  __host__ __device__ int ts() const { return b2() + 4; }           // [NP][4]  targets
-  __host__ __device__ int dst() const { return ts() + NP * 4; }     // [NW][16][16] a / delta1 staging
-  __host__ __device__ int dd() const { return dst() + NW * 256; }   // [NW][16][4] delta2 staging
-  __host__ __device__ int part() const { return dd() + NW * 64; }   // [NW][PW] partials
-  __host__ __device__ int vs() const { return part() + NW * PW; }   // [P] velocity (momentum only)
-  __host__ __device__ int total(bool mom = false) const {
-    return vs() + (mom ? (H * (D + 1) + K * H + K + 3) / 4 * 4 : 0);
-  }
+// LDS plan (floats).  The row count is the only size that is not fixed per
+// kernel instance, so what depends on it comes last and every other address is
+// a constant.
+template <int NW, int HTM, int FT>
+struct SmallPlan {
+  static constexpr int HP = 16 * HTM;   // hidden units padded to 16-unit tiles
+  static constexpr int DN = 16 * FT;    // features and the constant-1 column, padded to 16-wide tiles
+  static constexpr int XS = DN + 2;     // row stride of X and W1: 16 rows of a tile hit distinct banks
+  static constexpr int PW = HP * DN + 4 * HP + 4 + 4;   // one wave's partials: gW1 | gW2 | gb2 | loss
+  static constexpr int w1 = 0;                  // [HP][XS] master W1|b1
+  static constexpr int w2 = w1 + HP * XS;       // [4][HP]  master W2
+  static constexpr int b2 = w2 + 4 * HP;        // [4]      master b2
+  static constexpr int dst = b2 + 4;            // [NW][16][16] a staging (delta1's: in part)
+  static constexpr int dd = dst + NW * 256;     // [NW][16][4] delta2 staging
+  static constexpr int part = dd + NW * 64;     // [NW][PW] partials
+  static constexpr int ts = part + NW * PW;     // [NP][4]  targets
+  __host__ __device__ static int np(int n) { return (n + 15) / 16 * 16; }   // rows padded to 16-row tiles
+  __host__ __device__ static int xs(int n) { return ts + np(n) * 4; }       // [NP][XS] rows
+  __host__ __device__ static int vs(int n) { return xs(n) + np(n) * XS; }   // [P] velocity (momentum only)
 };
 
 // Training variants (the paper's method is act 0 without momentum):
@@ -87,35 +78,44 @@ struct SmallVariant {
   float *vel;
 };
 
-// KO: outputs the output-layer code runs over (K <= KO; 3 covers K <= 3).
-// ACT: the hidden activation (0 sigma, 1 tanh), fixed per instance so the
-// paper's sigmoid network carries no branch for the variant.
-template <int NW, int HTM, int KO, int ACT>
+// NW: waves; HTM: hidden tiles of the launch's widest net; FT: feature tiles
+// (D + 1 columns); ACT: the hidden activation (0 sigma, 1 tanh).  Fixed per
+// instance, so that LDS addresses are constants and nothing in the paper's
+// sigmoid network branches for a variant.
+// Four consecutive floats of LDS, 8-byte aligned.
+__device__ __forceinline__ f32x4_s quad(const float *q) {
+  const float2 lo = *reinterpret_cast<const float2 *>(q), hi = *reinterpret_cast<const float2 *>(q + 2);
+  return f32x4_s{lo.x, lo.y, hi.x, hi.y};
+}
+
+template <int NW, int HTM, int FT, int ACT>
 __global__ __launch_bounds__(NW * 64) void k_small_train(
     const mlp_batch_item *__restrict__ items, mlp_batch_item one, int D, int K,
     const float *__restrict__ X, const float *__restrict__ T, float *__restrict__ theta,
     float *__restrict__ comp, int epochs, float *__restrict__ loss_hist, SmallVariant var) {
+  using L = SmallPlan<NW, HTM, FT>;
   constexpr int NT = NW * 64;
-  constexpr int PMAX = 48 * 64 + 64 + 64 * 4 + 4;   // largest parameter count
-  constexpr int JM = (PMAX + NT - 1) / NT;          // parameters per thread
+  constexpr int PMAX = 16 * HTM * 16 * FT + 16 * HTM * 4 + 4;   // largest parameter count
+  constexpr int JM = (PMAX + NT - 1) / NT;                      // parameters per thread
+  constexpr int XS = L::XS, HP = L::HP, DN = L::DN, PW = L::PW, KO = 4;
   const mlp_batch_item it = items ? items[blockIdx.x] : one;
   const int N = it.n_rows, H = it.n_hidden;
   const float lr = it.lr;
-  const SmallLayout L(N, H, D, K, NW);
-  const int XS = L.XS, HP = L.HP, HT = L.HT, FT = L.FT, DN = L.DN, DK = L.DK, PW = L.PW;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int NP = L::np(N), NPT = NP / 16, HT = HTM == 1 ? 1 : (H + 15) / 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, lg = lane >> 4;
 
   extern __shared__ float4 smem4[];
   float *sm = reinterpret_cast<float *>(smem4);
-  float *Xs = sm + L.xs();
-  float *W1s = sm + L.w1();
-  float *W2s = sm + L.w2();
-  float *b2s = sm + L.b2();
-  float *Ts = sm + L.ts();
-  float *Dst = sm + L.dst() + wave * 256;
-  float *Dd = sm + L.dd() + wave * 64;
-  float *Part = sm + L.part();
+  float *Xs = sm + L::xs(N);
+  float *W1s = sm + L::w1;
+  float *W2s = sm + L::w2;
+  float *b2s = sm + L::b2;
+  float *Ts = sm + L::ts;
+  float *Dst = sm + L::dst + wave * 256;
+  float *Dd = sm + L::dd + wave * 64;
+  float *Part = sm + L::part;
+  float *Dst2 = Part + wave * PW;   // the wave's partials, free until they are written
 
   const float *Xg = X + it.x_off * D;
   const float *Tg = T + it.x_off * K;
@@ -127,11 +127,11 @@ __global__ __launch_bounds__(NW * 64) void k_small_train(
   const int nP = H * D1 + K * H + K;   // parameters, in update order: [W1 b1] rows, W2, b2
 
   // ---- stage rows, targets, parameters (coalesced); zero every padding entry
-  for (int i = tid; i < L.NP * XS; i += NT) {
+  for (int i = tid; i < NP * XS; i += NT) {
     const int r = i / XS, c = i - r * XS;
     Xs[i] = (r < N && c < D) ? Xg[(int64_t)r * D + c] : ((r < N && c == D) ? 1.0f : 0.0f);
   }
-  for (int i = tid; i < L.NP * 4; i += NT) {
+  for (int i = tid; i < NP * 4; i += NT) {
     const int r = i >> 2, k = i & 3;
     Ts[i] = (r < N && k < K) ? Tg[(int64_t)r * K + k] : 0.0f;
   }
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(NW * 64) void k_small_train(
     ccomp[j] = (compensated && q < nP) ? Cp[packed(q)] : 0.0f;
   }
   // momentum: the velocity lives in LDS in update order for the whole run
-  float *Vs = sm + L.vs();
+  float *Vs = sm + L::vs(N);
   if (var.vel)
     for (int q = tid; q < nP; q += NT) Vs[q] = var.vel[packed(q)];
   // LDS offsets of parameter q (update order): its partial within a wave's
@@ -170,16 +170,17 @@ __global__ __launch_bounds__(NW * 64) void k_small_train(
   auto offsets = [&](int q, int &po, int &mo) {
     if (q < H * D1) {
       const int h = q / D1, d = q - h * D1;
-      po = h * DN + d;
-      mo = L.w1() + h * XS + d;
+      // tile (h / 16, d / 16), lane (d % 16, h / 4 % 4), element h % 4
+      po = ((h >> 4) * FT + (d >> 4)) * 256 + ((h >> 2 & 3) * 16 + (d & 15)) * 4 + (h & 3);
+      mo = L::w1 + h * XS + d;
     } else if (q < H * D1 + K * H) {
       const int o = q - H * D1, k = o / H, h = o - k * H;
       po = HP * DN + k * HP + h;
-      mo = L.w2() + k * HP + h;
+      mo = L::w2 + k * HP + h;
     } else {
       const int k = q - H * D1 - K * H;
       po = HP * DN + 4 * HP + k;
-      mo = L.b2() + k;
+      mo = L::b2 + k;
     }
   };
   constexpr bool kKeepOfs = JM <= 8;
@@ -198,36 +199,61 @@ __global__ __launch_bounds__(NW * 64) void k_small_train(
   const float dscale = 2.0f / (float)(N * K);
   const float inv_nk = 1.0f / (float)(N * K);
 
+  // X operands of a row tile: of z1 (whole 16-feature groups) and of gW1 (rows
+  // 4 s + lg).  With 8 waves most nets have a row tile per wave at most; the
+  // operands then stay in registers for the run.
+  f32x4_s xv[FT];
+  float xb[FT][4];
+  auto load_x = [&](int r0) {
+    const float *xa = Xs + (r0 + l16) * XS + 4 * lg;
+#pragma unroll
+    for (int g = 0; g < FT; ++g) xv[g] = quad(xa + 16 * g);
+#pragma unroll
+    for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) xb[ft][s] = Xs[(r0 + lg + 4 * s) * XS + ft * 16 + l16];
+  };
+  const bool keep_x = NW == 8 && NPT <= NW;
+  if (keep_x) load_x(min(wave, NPT - 1) * 16);
+
   for (int e = 0; e < epochs; ++e) {
     // ======================= rows of this wave: forward, deltas, partial gradients
-    f32x4_s gacc[HTM][4];   // gW1 tiles [hidden][feature]
+    f32x4_s gacc[HTM][FT];   // gW1 tiles [hidden][feature]
     f32x4_s g2acc[HTM];     // gW2^T tiles [hidden][output]
 #pragma unroll
     for (int ht = 0; ht < HTM; ++ht) {
       g2acc[ht] = f32x4_s{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ft = 0; ft < 4; ++ft) gacc[ht][ft] = f32x4_s{0.f, 0.f, 0.f, 0.f};
+      for (int ft = 0; ft < FT; ++ft) gacc[ht][ft] = f32x4_s{0.f, 0.f, 0.f, 0.f};
     }
     float gb2 = 0.0f;   // output lg of this lane's rows
     float sq = 0.0f;
 
-    for (int rt = wave; rt < L.NPT; rt += NW) {
+    for (int rt = wave; rt < NPT; rt += NW) {
       const int r0 = rt * 16;
       const int n = r0 + l16;   // this lane's row
       // z1^T tiles (M = hidden, N = rows): lane (row l16, group lg) holds
       // hidden units 4 lg .. 4 lg + 3 of each tile; a and its slope stay in
-      // registers
+      // registers.  The contraction runs over whole 16-feature groups (the
+      // padding is zero), index 4 lg + step within a group, so an operand of
+      // four steps is one LDS read, and all of a tile's are issued ahead of
+      // its products (one step at a time, each product waited for its own
+      // reads: z1 and sigma took 1490 of a 60-row epoch's 5460 cycles).
+      if (!keep_x) load_x(r0);
       float av[HTM][4], sl[HTM][4];
 #pragma unroll
       for (int ht = 0; ht < HTM; ++ht) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) { av[ht][i] = 0.0f; sl[ht][i] = 0.0f; }
         if (ht < HT) {
-          f32x4_s z = {0.f, 0.f, 0.f, 0.f};
-          const float *xa = Xs + (r0 + l16) * XS + lg;
-          const float *wb = W1s + (ht * 16 + l16) * XS + lg;
-          for (int k0 = 0; k0 < DK; k0 += 4)
-            z = __builtin_amdgcn_mfma_f32_16x16x4f32(wb[k0], xa[k0], z, 0, 0, 0);
+          f32x4_s z = {0.f, 0.f, 0.f, 0.f}, wv[FT];
+          const float *wb = W1s + (ht * 16 + l16) * XS + 4 * lg;
+#pragma unroll
+          for (int g = 0; g < FT; ++g) wv[g] = quad(wb + 16 * g);
+#pragma unroll
+          for (int g = 0; g < FT; ++g)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) z = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[g][s], xv[g][s], z, 0, 0, 0);
 #pragma unroll
           for (int i = 0; i < 4; ++i) av[ht][i] = hidden_act(ACT, z[i], sl[ht][i]);
         }
@@ -262,61 +288,56 @@ __global__ __launch_bounds__(NW * 64) void k_small_train(
       const float d2 = dscale * err * y * (1.0f - y);
       gb2 += d2;
       Dd[l16 * 4 + k] = d2;   // row-major [row][output] for the gW2 contraction
+      float dv[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const float v = Dd[(4 * s + lg) * 4 + (l16 & 3)];
+        dv[s] = l16 < 4 ? v : 0.0f;
+      }
 #pragma unroll
       for (int ht = 0; ht < HTM; ++ht) {
         if (ht < HT) {
-          // gW2^T += a^T delta2 (M = hidden, N = outputs, K = the tile's
-          // rows), a staged row-major through the wave's LDS tile
+          // a and delta1 row-major through two LDS tiles of the wave (the
+          // second one is its block of partials, free until they are
+          // written), both written before either is read back:
+          //   delta1^T = W2^T delta2^T (the pre-update W2), times the slope
+          //   gW2^T += a^T delta2 (M = hidden, N = outputs, K = the tile's rows)
+          //   gW1 += delta1^T [X 1]
           *reinterpret_cast<f32x4_s *>(Dst + l16 * 16 + 4 * lg) =
               f32x4_s{av[ht][0], av[ht][1], av[ht][2], av[ht][3]};
-          f32x4_s g2 = g2acc[ht];
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            const float dv = Dd[(4 * s + lg) * 4 + (l16 & 3)];
-            g2 = __builtin_amdgcn_mfma_f32_16x16x4f32(Dst[(4 * s + lg) * 16 + l16], l16 < 4 ? dv : 0.0f,
-                                                     g2, 0, 0, 0);
-          }
-          g2acc[ht] = g2;
-          // delta1^T = W2^T delta2^T (the pre-update W2), times the slope
           const f32x4_s bp = __builtin_amdgcn_mfma_f32_16x16x4f32(
               W2s[lg * HP + ht * 16 + l16], d2, f32x4_s{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-          *reinterpret_cast<f32x4_s *>(Dst + l16 * 16 + 4 * lg) =
+          *reinterpret_cast<f32x4_s *>(Dst2 + l16 * 16 + 4 * lg) =
               f32x4_s{bp[0] * sl[ht][0], bp[1] * sl[ht][1], bp[2] * sl[ht][2], bp[3] * sl[ht][3]};
-          // gW1 += delta1^T [X 1] on MFMA
-          const float *da = Dst + lg * 16 + l16;
+          float ao[4], da[4];
 #pragma unroll
-          for (int ft = 0; ft < 4; ++ft) {
-            if (ft < FT) {
-              const float *xb = Xs + (r0 + lg) * XS + ft * 16 + l16;
-              f32x4_s g = gacc[ht][ft];
+          for (int s = 0; s < 4; ++s) ao[s] = Dst[(4 * s + lg) * 16 + l16];
 #pragma unroll
-              for (int s = 0; s < 4; ++s)
-                g = __builtin_amdgcn_mfma_f32_16x16x4f32(da[s * 64], xb[s * 4 * XS], g, 0, 0, 0);
-              gacc[ht][ft] = g;
-            }
-          }
+          for (int s = 0; s < 4; ++s) da[s] = Dst2[(4 * s + lg) * 16 + l16];
+          f32x4_s g2 = g2acc[ht];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) g2 = __builtin_amdgcn_mfma_f32_16x16x4f32(ao[s], dv[s], g2, 0, 0, 0);
+          g2acc[ht] = g2;
+          // (the feature tiles' chains interleave)
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int ft = 0; ft < FT; ++ft)
+              gacc[ht][ft] = __builtin_amdgcn_mfma_f32_16x16x4f32(da[s], xb[ft][s], gacc[ht][ft], 0, 0, 0);
         }
       }
     }
 
     // ======================= wave partials to LDS
     float *pw = Part + wave * PW;
-    // this lane's base in the block, opaque to the compiler each epoch: the
-    // per-lane addresses below are then formed here (base + a wave-uniform
-    // offset) instead of being kept live across the epoch loop, where the
-    // wide instances would spill them
-    int lbase = 4 * lg * DN + l16;
-    asm volatile("" : "+v"(lbase));
+    // gW1 as the tiles lie in the lanes: 16 bytes a lane
+    int lbase = 4 * lane;
+    asm volatile("" : "+v"(lbase));   // addresses formed here, not held (or spilled) across the epoch loop
 #pragma unroll
     for (int ht = 0; ht < HTM; ++ht) {
       if (ht < HT) {
 #pragma unroll
-        for (int ft = 0; ft < 4; ++ft) {
-          if (ft < FT) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) pw[lbase + (ht * 16 + i) * DN + ft * 16] = gacc[ht][ft][i];
-          }
-        }
+        for (int ft = 0; ft < FT; ++ft) *reinterpret_cast<f32x4_s *>(pw + lbase + (ht * FT + ft) * 256) = gacc[ht][ft];
         // lane (output l16, group lg): hidden units 4 lg .. 4 lg + 3
         if (l16 < 4) *reinterpret_cast<f32x4_s *>(pw + HP * DN + l16 * HP + ht * 16 + 4 * lg) = g2acc[ht];
       }
@@ -331,8 +352,9 @@ __global__ __launch_bounds__(NW * 64) void k_small_train(
     __syncthreads();
 
     // ======================= sum the wave partials in order; update
-    if (loss_hist && tid == 0) {
+    if (loss_hist && tid == NT - 1) {   // (the last wave owns the fewest parameters)
       float s = 0.0f;
+#pragma unroll
       for (int w = 0; w < NW; ++w) s += Part[w * PW + HP * DN + 4 * HP + 4];
       loss_hist[(int64_t)blockIdx.x * epochs + e] = s * inv_nk;
     }
@@ -413,40 +435,16 @@ __global__ __launch_bounds__(NW * 64) void k_small_train(
     for (int q = tid; q < nP; q += NT) var.vel[packed(q)] = Vs[q];
 }
 
-template <int NW, int HTM, int KO, int ACT>
-hipError_t launch_one(const mlp_batch_item *items, mlp_batch_item one, int n_nets, int n_in,
-                      int n_out, size_t lds, const float *X, const float *T, float *theta,
-                      float *comp, int epochs, float *loss_hist, SmallVariant var, hipStream_t s) {
-  auto kern = k_small_train<NW, HTM, KO, ACT>;
-  hipError_t e = hipFuncSetAttribute((const void *)kern,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(n_nets), dim3(NW * 64), lds, s, items, one, n_in, n_out, X, T,
-                     theta, comp, epochs, loss_hist, var);
-  return hipGetLastError();
-}
-
-template <int NW, int ACT>
-hipError_t launch_nw(int max_hidden, const mlp_batch_item *items, mlp_batch_item one, int n_nets,
-                     int n_in, int n_out, size_t lds, const float *X, const float *T,
-                     float *theta, float *comp, int epochs, float *loss_hist, SmallVariant var,
-                     hipStream_t s) {
-  // registers are sized for the widest hidden layer of the launch
-  const int ht = (max_hidden + 15) / 16;
-  if (n_out <= 3) {
-    if (ht <= 1)
-      return launch_one<NW, 1, 3, ACT>(items, one, n_nets, n_in, n_out, lds, X, T, theta, comp, epochs, loss_hist, var, s);
-    if (ht <= 2)
-      return launch_one<NW, 2, 3, ACT>(items, one, n_nets, n_in, n_out, lds, X, T, theta, comp, epochs, loss_hist, var, s);
-    return launch_one<NW, 4, 3, ACT>(items, one, n_nets, n_in, n_out, lds, X, T, theta, comp, epochs, loss_hist, var, s);
+// The instance for a launch's waves, widest net, features and activation.
+template <int NW, int ACT, int HTM = 1, int FT = 1>
+const void *small_kernel(int ht, int ft) {
+  if (ht == HTM && ft == FT) return (const void *)k_small_train<NW, HTM, FT, ACT>;
+  if constexpr (HTM < 4) {
+    if (ht > HTM) return small_kernel<NW, ACT, HTM + 1, FT>(ht, ft);
   }
-  if (ht <= 1)
-    return launch_one<NW, 1, 4, ACT>(items, one, n_nets, n_in, n_out, lds, X, T, theta, comp, epochs, loss_hist, var, s);
-  if (ht <= 2)
-    return launch_one<NW, 2, 4, ACT>(items, one, n_nets, n_in, n_out, lds, X, T, theta, comp, epochs, loss_hist, var, s);
-  return launch_one<NW, 4, 4, ACT>(items, one, n_nets, n_in, n_out, lds, X, T, theta, comp, epochs, loss_hist, var, s);
+  if constexpr (FT < 4) return small_kernel<NW, ACT, HTM, FT + 1>(ht, ft);
+  return nullptr;
 }
-
 
 // ---------------------------------------------------------------------------
 // Hidden-split form of the same trainer (the paper's sigmoid network, plain
@@ -624,7 +622,23 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
         if (r0 + 1 < NPT) {
           const float *xb = xa + 16 * XS;
           f32x4_s za = {0.f, 0.f, 0.f, 0.f}, zb = {0.f, 0.f, 0.f, 0.f};
-          for (int k0 = 0; k0 < DK; k0 += 4) {
+          // four steps' operands at a time, ahead of their products
+          int k0 = 0;
+          for (; k0 + 16 <= DK; k0 += 16) {
+            float w[4], a[4], b[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+              w[s] = wb[k0 + 4 * s];
+              a[s] = xa[k0 + 4 * s];
+              b[s] = xb[k0 + 4 * s];
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+              za = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], a[s], za, 0, 0, 0);
+              zb = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], b[s], zb, 0, 0, 0);
+            }
+          }
+          for (; k0 < DK; k0 += 4) {
             const float w = wb[k0];
             za = __builtin_amdgcn_mfma_f32_16x16x4f32(w, xa[k0], za, 0, 0, 0);
             zb = __builtin_amdgcn_mfma_f32_16x16x4f32(w, xb[k0], zb, 0, 0, 0);
@@ -820,20 +834,24 @@ hipError_t launch_hsplit_nw(const mlp_batch_item *items, mlp_batch_item one, int
 namespace mlph {
 
 size_t small_lds_bytes(int n_rows, int n_hidden, int n_in, int threads, bool momentum) {
-  mlpk::SmallLayout L(n_rows, n_hidden, n_in, 4, threads / 64);
-  return sizeof(float) * (size_t)L.total(momentum);
+  const int nw = threads / 64, ht = (n_hidden + 15) / 16, ft = (n_in + 16) / 16, np = (n_rows + 15) / 16 * 16;
+  const int hp = 16 * ht, dn = 16 * ft;   // SmallPlan's, for run-time sizes
+  const int pw = hp * dn + 4 * hp + 8;
+  const int mom = momentum ? (n_hidden * (n_in + 1) + 4 * n_hidden + 4 + 3) / 4 * 4 : 0;
+  return sizeof(float) * (size_t)(hp * (dn + 2) + 4 * hp + 4 + nw * (256 + 64 + pw) + np * (4 + dn + 2) + mom);
 }
 
 // Launch shape of n_nets nets of at most max_hidden units (0: no hint).  Up
 // to one net per CU a net's own epoch counts: 8 waves (86 nets of 120 rows x
-// 63 units, 20 epochs: 192 us against 306 on 4 waves, 302 hidden-split).
+// 63 units, 20 epochs: 171 us against 224 on 4 waves, 275 hidden-split).
 // Above, the chip is shared and the work of a net counts: hidden-split over
-// 16 units (1450 nets of 120 rows x 64 units: 808 us against 1004 on 8 waves
-// and 1450 on 2), 4 waves up to 16 (2759 nets: 563 us against 647 and 875).
+// 32 units (1450 nets of 120 rows x 64 units: 760 us against 883 on 8 waves,
+// 1038 on 2 and 1225 on 4), else 4 waves (1465 nets of up to 32 units: 452 us
+// against 521 on 8, 597 hidden-split; 2759 of up to 16: 368, 392, 713).
 int small_threads(int n_nets, int max_hidden, int n_cu, int hint) {
   if (hint == kHiddenSplit || hint == 128 || hint == 256 || hint == 512) return hint;
   if (n_nets <= n_cu) return 512;
-  return max_hidden > 16 ? kHiddenSplit : 256;
+  return max_hidden > 32 ? kHiddenSplit : 256;
 }
 
 size_t small_launch_lds_bytes(int max_rows, int max_hidden, int n_in, int threads, bool momentum) {
@@ -869,21 +887,20 @@ hipError_t launch_small_train(const mlp_batch_item *items, mlp_batch_item one, i
   while (threads > 128 && small_launch_lds_bytes(max_rows, max_hidden, n_in, threads, mom) > 160 * 1024)
     threads /= 2;
   const size_t lds = small_launch_lds_bytes(max_rows, max_hidden, n_in, threads, mom);
-  if (act == 1) {
-    // the tanh variant is instantiated for 8 waves only; the host API
-    // checks that its LDS plan fits before launching
-    if (threads != 512) return hipErrorInvalidValue;
-    return mlpk::launch_nw<8, 1>(max_hidden, items, one, n_nets, n_in, n_out, lds, X, T, theta, comp,
-                                 epochs, loss_hist, var, s);
-  }
-  if (threads == 512)
-    return mlpk::launch_nw<8, 0>(max_hidden, items, one, n_nets, n_in, n_out, lds, X, T, theta, comp,
-                                 epochs, loss_hist, var, s);
-  if (threads == 256)
-    return mlpk::launch_nw<4, 0>(max_hidden, items, one, n_nets, n_in, n_out, lds, X, T, theta, comp,
-                                 epochs, loss_hist, var, s);
-  return mlpk::launch_nw<2, 0>(max_hidden, items, one, n_nets, n_in, n_out, lds, X, T, theta, comp,
-                               epochs, loss_hist, var, s);
+  // the tanh variant is instantiated for 8 waves only; the host API checks
+  // that its LDS plan fits before launching
+  if (act == 1 && threads != 512) return hipErrorInvalidValue;
+  const int ht = (max_hidden + 15) / 16, ft = (n_in + 16) / 16;   // (the constant column is a feature)
+  const void *kern = act == 1         ? mlpk::small_kernel<8, 1>(ht, ft)
+                     : threads == 512 ? mlpk::small_kernel<8, 0>(ht, ft)
+                     : threads == 256 ? mlpk::small_kernel<4, 0>(ht, ft)
+                                      : mlpk::small_kernel<2, 0>(ht, ft);
+  hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  mlpk::SmallVariant v = var;
+  void *args[] = {&items, &one, &n_in, &n_out, &X, &T, &theta, &comp, &epochs, &loss_hist, &v};
+  e = hipLaunchKernel(kern, dim3(n_nets), dim3(threads), args, lds, s);
+  return e == hipSuccess ? hipGetLastError() : e;
 }
 
 }  // namespace mlph

@@ -1,0 +1,48 @@
+"""Every instance of the row-split small trainer (hidden tiles x feature tiles,
+2, 4 and 8 waves) at the edges of its tiles, against the FP64 oracle."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from oracle import Params
+from paper_1908_07847_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    from paper_1908_07847_amd import mlp
+    return mlp
+
+
+@pytest.mark.parametrize("threads", [128, 256, 512])
+@pytest.mark.parametrize("n,d,h,k", [
+    (16, 15, 16, 4),    # one whole tile of everything (the constant column fills the features)
+    (17, 16, 17, 1),    # one past each: two feature tiles, two hidden tiles
+    (113, 31, 33, 3),   # eight row tiles; two feature tiles exactly, three hidden tiles
+    (128, 47, 48, 2),   # three feature tiles exactly
+    (65, 48, 49, 3),    # four feature tiles, four hidden tiles
+])
+def test_small_instances_match_the_oracle(M, threads, n, d, h, k):
+    print(f"small n={n} {d}-{h}-{k}, {threads} threads", flush=True)
+    sys.stdout.flush()
+    g = np.random.default_rng(n + h)
+    X = g.standard_normal((n, d)).astype(np.float32)
+    T = np.zeros((n, k), np.float32)
+    T[np.arange(n), g.integers(0, k, n)] = 1.0
+    th = g.uniform(-0.5, 0.5, d * h + h + h * k + k).astype(np.float32)
+    M.set_launch_hint(small_threads=threads)
+    try:
+        net = M.Net(d, h, k, n, theta=th)
+        hist = net.train(torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda(), 100)
+        torch.cuda.synchronize()
+    finally:
+        M.reset_launch_hint()
+    q, ref = oracle.train(X, T, Params.of(synth.Theta.unpack(th, d, h, k)), 0.1, 100)
+    got = synth.Theta.unpack(net.flat.cpu().numpy(), d, h, k)
+    for a, b in ((got.W1, q.W1), (got.b1, q.b1), (got.W2, q.W2), (got.b2, q.b2), (hist.cpu().numpy(), ref)):
+        assert np.max(np.abs(a - b)) <= 1e-5 * np.max(np.abs(b))   # the trainers' stated tolerance
