@@ -287,24 +287,28 @@ __device__ __forceinline__ uint8_t e4m3_byte(float v) {
 // plus a few float ulps.  The contraction operands of these forms carry
 // 2^-9 (bf16) or 2^-4 (e4m3) relative rounding; the float32 form keeps the
 // compensated evaluation of sigmoid_e.  PREC selects the form by operand type.
+//
+// The products z of these forms enter as t = fma(z, cz, bt) with cz = -log2(e)
+// (times the e4m3 scales' inverse, a power of two) and bt = -log2(e) b1, the
+// bias and the scale in one instruction.
+constexpr float kNegLog2e = -1.44269502162933349609375f;
 template <int PREC>
-__device__ __forceinline__ float hidden_sigmoid_e(float z, float &e_out) {
-  if (PREC == 0) return sigmoid_e(z, e_out);
-  const float t = fminf(-z * 1.44269502162933349609375f, 126.0f);
-  const float e = __builtin_amdgcn_exp2f(t);
-  e_out = e;
-  return __builtin_amdgcn_rcpf(1.0f + e);
-}
-template <int PREC>
-__device__ __forceinline__ float hidden_sigmoid(float z) {
+__device__ __forceinline__ float hidden_sigmoid(float z, float cz, float bias) {
   float e;
-  return hidden_sigmoid_e<PREC>(z, e);
+  if (PREC == 0) return sigmoid_e(z + bias, e);
+  // (e^-z may overflow to infinity: sigma is then 0)
+  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(fmaf(z, cz, bias)));
 }
 // sigma and its slope e^-z sigma^2 (see sigmoid_slope)
 template <int PREC>
-__device__ __forceinline__ float hidden_sigmoid_slope(float z, float &slope) {
-  float e;
-  const float a = hidden_sigmoid_e<PREC>(z, e);
+__device__ __forceinline__ float hidden_sigmoid_slope(float z, float cz, float bias, float &slope) {
+  float e, a;
+  if (PREC == 0) {
+    a = sigmoid_e(z + bias, e);
+  } else {
+    e = __builtin_amdgcn_exp2f(fminf(fmaf(z, cz, bias), 126.0f));
+    a = __builtin_amdgcn_rcpf(1.0f + e);
+  }
   slope = (e * a) * a;
   return a;
 }
@@ -802,6 +806,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
     }
     const float sw = ldexpf(1.0f, ew), isw = ldexpf(1.0f, -ew);
     const float sd = ldexpf(1.0f, ed), isd = ldexpf(1.0f, -ed);
+    const float cz = PREC == 2 ? kNegLog2e * (isx * isw) : kNegLog2e;   // scale of z in the hidden sigmoid
 
     // ---- this workgroup's slice of W1 (operand precision), b1, W2 to LDS
     {
@@ -839,7 +844,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
 #pragma unroll
       for (int u = 0; u < kBW; ++u) {   // b1s and w2s are adjacent: run r starts at 64 r
         const int run = wave + u * kNW;
-        if (run < (1 + K) * nb64) b1s[run * 64 + lane] = bw[u];
+        if (run < (1 + K) * nb64) b1s[run * 64 + lane] = PREC != 0 && run < nb64 ? bw[u] * kNegLog2e : bw[u];
       }
     }
     int cur_piece = 0;   // piece of the row block held in LDS
@@ -965,8 +970,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
               z1v = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(xa[1][ks], w1e[hb][ks], z1v, 0, 0, 0);
             }
           }
-          zt[hb][0] = z0 * (isx * isw);
-          zt[hb][1] = z1v * (isx * isw);
+          zt[hb][0] = z0;   // (the scales enter with the sigmoid)
+          zt[hb][1] = z1v;
         }
       }
     };
@@ -997,7 +1002,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
           const f32x4 z = zt[hb][rs];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const float av = hidden_sigmoid<PREC>(z[i] + bias);
+            const float av = hidden_sigmoid<PREC>(z[i], cz, bias);
 #pragma unroll
             for (int k = 0; k < KO; ++k) zp[rs][i][k] = fmaf(av, w2v[k], zp[rs][i][k]);
           }
@@ -1068,8 +1073,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
           xa8[ks] = *reinterpret_cast<const long *>(reinterpret_cast<const uint8_t *>(xr) + (r0 + l16) * XROW +
                                                     8 * lg + 32 * ks);
       }
-      // Tiles go in groups of 4; a group's tile index is clamped to the block
-      // (the products of a clamped tile are computed and dropped).  bf16 /
+      // Tiles go in groups of 4 (a hidden block is a multiple of 64 units).  bf16 /
       // e4m3: the W1 operands of the next group are loaded while this group's
       // sigma runs; float32 (16 operands per tile): the group's 64 operands
       // are loaded together ahead of its products.
@@ -1078,10 +1082,9 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
       auto load_group = [&](int t0) {
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
-          const int t = min(t0 + tt, NT - 1);
 #pragma unroll
           for (int ks = 0; ks < 2; ++ks) {
-            const int o = (16 * t + l16) * XROW + 8 * lg + 32 * ks;
+            const int o = (16 * t0 + l16) * XROW + 8 * lg + 16 * tt * XROW + 32 * ks;
             if (PREC == 1) wvb[tt][ks] = *reinterpret_cast<const bf16x8 *>(reinterpret_cast<const __bf16 *>(w1s) + o);
             if (PREC == 2) wve[tt][ks] = *reinterpret_cast<const long *>(reinterpret_cast<const uint8_t *>(w1s) + o);
           }
@@ -1092,7 +1095,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
         float bias[4], w2v[4][KO];
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
-          const int hl = 16 * min(t0 + tt, NT - 1) + l16;
+          const int hl = 16 * t0 + l16 + 16 * tt;
           bias[tt] = b1s[hl];
 #pragma unroll
           for (int k = 0; k < KO; ++k) w2v[tt][k] = w2s[k * HB + hl];
@@ -1102,7 +1105,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
           float wv[4][16];
 #pragma unroll
           for (int tt = 0; tt < 4; ++tt) {
-            const float *wb = reinterpret_cast<const float *>(w1s) + (16 * min(t0 + tt, NT - 1) + l16) * XROW + lg;
+            const float *wb = reinterpret_cast<const float *>(w1s) + (16 * t0 + l16) * XROW + lg + 16 * tt * XROW;
 #pragma unroll
             for (int st = 0; st < 16; ++st) wv[tt][st] = wb[4 * st];
           }
@@ -1130,20 +1133,14 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
             }
           }
           if (t0 + 4 < NT) load_group(t0 + 4);
-          if (PREC == 2) {
-#pragma unroll
-            for (int tt = 0; tt < 4; ++tt) z[tt] = z[tt] * (isx * isw);
-          }
         }
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
-          if (t0 + tt < NT) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const float av = hidden_sigmoid<PREC>(z[tt][i] + bias[tt]);
+          for (int i = 0; i < 4; ++i) {
+            const float av = hidden_sigmoid<PREC>(z[tt][i], cz, bias[tt]);
 #pragma unroll
-              for (int k = 0; k < KO; ++k) zp[i][k] = fmaf(av, w2v[tt][k], zp[i][k]);
-            }
+            for (int k = 0; k < KO; ++k) zp[i][k] = fmaf(av, w2v[tt][k], zp[i][k]);
           }
         }
       }
@@ -1279,16 +1276,22 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
       // is read for the same rows.
       // z1 of the next chunk is issued on the matrix cores before this
       // chunk's vector work (sigma', delta1), which does not depend on it
+      // (float32: 64 products; the few 16-wide ones of the reduced precisions
+      // are issued with their chunk, without the copies)
       f32x4 ztn[NHM][2];
-      z1_tiles(0, ztn);
+      if (PREC == 0) z1_tiles(0, ztn);
       for (int c0 = 0; c0 < RBP; c0 += kRC) {
       f32x4 zt[NHM][2];
+      if (PREC == 0) {
 #pragma unroll
-      for (int hb = 0; hb < NHM; ++hb) {
-        zt[hb][0] = ztn[hb][0];
-        zt[hb][1] = ztn[hb][1];
+        for (int hb = 0; hb < NHM; ++hb) {
+          zt[hb][0] = ztn[hb][0];
+          zt[hb][1] = ztn[hb][1];
+        }
+        if (c0 + kRC < RBP) z1_tiles(c0 + kRC, ztn);
+      } else {
+        z1_tiles(c0, zt);
       }
-      if (c0 + kRC < RBP) z1_tiles(c0 + kRC, ztn);
       // X operands of this chunk's gW1 contraction, shared by the wave's tiles:
       // float32 [rs][i][fb] = X[c0 + 16 rs + 4 lg + i][16 fb + l16]; bf16 /
       // e4m3 [fb] = X[rows c0 + 4 lg .. +3, then c0 + 16 + 4 lg .. +3][16 fb + l16]
@@ -1337,7 +1340,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
             for (int i = 0; i < 4; ++i) {
               const int rr = rs * 16 + 4 * lg + i;          // row within the chunk
               float slope;
-              const float av = hidden_sigmoid_slope<PREC>(z[i] + bias, slope);
+              const float av = hidden_sigmoid_slope<PREC>(z[i], cz, bias, slope);
               const float4 dv = *reinterpret_cast<const float4 *>(d2s + (c0 + rr) * 4);
               const float dd[4] = {dv.x, dv.y, dv.z, dv.w};
               float bp = 0.0f;
