@@ -288,25 +288,31 @@ __device__ __forceinline__ uint8_t e4m3_byte(float v) {
 // 2^-9 (bf16) or 2^-4 (e4m3) relative rounding; the float32 form keeps the
 // compensated evaluation of sigmoid_e.  PREC selects the form by operand type.
 //
-// The products z of these forms enter as t = fma(z, cz, bt) with cz = -log2(e)
-// (times the e4m3 scales' inverse, a power of two) and bt = -log2(e) b1, the
-// bias and the scale in one instruction.
+// z enters as fma(z, cz, bias): cz is the inverse of the e4m3 scales (a power
+// of two, so the product is exact), 1 otherwise.  (Taking log2(e) into cz and
+// the bias as well saves one more instruction but rounds differently, and a
+// net at a learning rate near 1 carries one changed last bit to 1e-3 of its
+// parameters within 30 steps.)
 constexpr float kNegLog2e = -1.44269502162933349609375f;
+template <int PREC>
+__device__ __forceinline__ float hidden_z(float z, float cz, float bias) {
+  return PREC == 2 ? fmaf(z, cz, bias) : z + bias;
+}
 template <int PREC>
 __device__ __forceinline__ float hidden_sigmoid(float z, float cz, float bias) {
   float e;
-  if (PREC == 0) return sigmoid_e(z + bias, e);
+  if (PREC == 0) return sigmoid_e(hidden_z<PREC>(z, cz, bias), e);
   // (e^-z may overflow to infinity: sigma is then 0)
-  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(fmaf(z, cz, bias)));
+  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(hidden_z<PREC>(z, cz, bias) * kNegLog2e));
 }
 // sigma and its slope e^-z sigma^2 (see sigmoid_slope)
 template <int PREC>
 __device__ __forceinline__ float hidden_sigmoid_slope(float z, float cz, float bias, float &slope) {
   float e, a;
   if (PREC == 0) {
-    a = sigmoid_e(z + bias, e);
+    a = sigmoid_e(hidden_z<PREC>(z, cz, bias), e);
   } else {
-    e = __builtin_amdgcn_exp2f(fminf(fmaf(z, cz, bias), 126.0f));
+    e = __builtin_amdgcn_exp2f(fminf(hidden_z<PREC>(z, cz, bias) * kNegLog2e, 126.0f));
     a = __builtin_amdgcn_rcpf(1.0f + e);
   }
   slope = (e * a) * a;
@@ -806,7 +812,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
     }
     const float sw = ldexpf(1.0f, ew), isw = ldexpf(1.0f, -ew);
     const float sd = ldexpf(1.0f, ed), isd = ldexpf(1.0f, -ed);
-    const float cz = PREC == 2 ? kNegLog2e * (isx * isw) : kNegLog2e;   // scale of z in the hidden sigmoid
+    const float cz = isx * isw;   // scale of z in the hidden sigmoid
 
     // ---- this workgroup's slice of W1 (operand precision), b1, W2 to LDS
     {
@@ -844,7 +850,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
 #pragma unroll
       for (int u = 0; u < kBW; ++u) {   // b1s and w2s are adjacent: run r starts at 64 r
         const int run = wave + u * kNW;
-        if (run < (1 + K) * nb64) b1s[run * 64 + lane] = PREC != 0 && run < nb64 ? bw[u] * kNegLog2e : bw[u];
+        if (run < (1 + K) * nb64) b1s[run * 64 + lane] = bw[u];
       }
     }
     int cur_piece = 0;   // piece of the row block held in LDS
@@ -1456,8 +1462,10 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
       const uint32_t rowb = (uint32_t)QT * 16u;
       // few quads, many partials: the threads split a quad's partials into ng
       // groups of consecutive rows; a thread per parameter, entries tid and
-      // tid + kLT of the slice, applies the sum
-      const int ng = few && nq > 0 ? min(kLT / nq, a.Gi) : 1;
+      // tid + kLT of the slice, applies the sum.  (Nets sharing X, few row
+      // blocks: one group, so that a net's sums run in row-block order in
+      // whichever workgroup its parameters fall.)
+      const int ng = few && nq > 0 && a.M == 1 ? min(kLT / nq, a.Gi) : 1;
       float w[2], c[2];
       int p[2], h[2], d[2], nt[2];
       bool on[2];
