@@ -1769,26 +1769,48 @@ int max_row_blocks(int M, int Gj) { return M == 1 ? kMaxRowBlocks : std::max(1, 
 
 }  // namespace
 
-// Grid shape.  One net: Gj hidden blocks of <= 256 units (a multiple of 64)
-// and Gi row blocks of >= 64 rows (>= 32 when the minibatch is smaller),
-// Gi*Gj workgroups filling the CUs, with a launch-hint override for the
-// autotuner.  (For 4096-row minibatches of a 256-unit layer, 64 row blocks
-// x 4 hidden blocks run 5 % faster than 128 x 2: a step there is latency,
-// and the longer row blocks halve the partial gradients summed per update.)  M > 1 nets sharing X: each net
+// Grid shape.  One net: of the grids with hidden blocks of 64..256 units (Gi
+// and Gj doubling), the one with the most workgroups, and among those the one
+// whose blocks are nearest to square (rows = units), with a launch-hint
+// override for the autotuner.  A step's exchanges grow with both counts -- Gi
+// partial gradients, Gj partial pre-activations -- and its work is the same,
+// so neither should be large: fp32, 48-512-3 at 8192 rows 34.8 us a step on
+// 64 x 4 against 39.3 on 128 x 2, 60-777-3 at 4096 rows 37.8 on 32 x 8 against
+// 42.0 on 64 x 4, 64-256-3 at 16384 rows 38.9 on 128 x 2 against 42.4 on
+// 256 x 1 (bf16 24.0 against 27.9, 25.3 against 29.2, 25.7 against 29.5).
+// Row blocks of 32 rows instead of 64 halve a block's work and double the
+// partial gradients summed: that gains while there are few of them (33-256-3
+// at 1024 rows, 32 x 4 against 16 x 4: fp32 15.4 against 16.8, bf16 14.0
+// against 14.9, e4m3 16.4 against 16.8) and ends earlier where the products
+// are cheaper: 33-64-3 at 2048 rows, 64 against 32 row blocks, fp32 13.2
+// against 14.9, bf16 12.4 against 12.5, e4m3 15.2 against 14.9; at 4096, 128
+// against 64, 14.9 against 15.4, 13.8 against 12.9, 16.4 against 16.1; at
+// 8192, 256 against 128, 19.2 against 16.9.  M > 1 nets sharing X: each net
 // takes the minimum number of hidden blocks, and row blocks are added while
 // Gi*M*Gj workgroups still fit one per CU.  Rows of a block are staged in
 // LDS in pieces (all of them at once when they fit).
 static bool plan_for(const mlp_config &c, int M, int n_cu, Plan *pl, std::string *why) {
   const int64_t b = batch_of(c);
   const int H = c.n_hidden;
-  int Gj = min_hidden_blocks(H);
-  int Gi = 1;   // row blocks: at least 64 rows each for one net (32 for nets sharing X)
-  const int64_t min_rows = (M == 1 && b >= 64) ? 64 : 32;
-  while (Gi * 2 * M * Gj <= n_cu && b % (Gi * 2 * min_rows) == 0 && Gi * 2 <= max_row_blocks(M, Gj)) Gi *= 2;
+  const int Gj0 = min_hidden_blocks(H);
+  int Gi = 1, Gj = Gj0;
+  if (M > 1)
+    while (Gi * 2 * M * Gj <= n_cu && b % (Gi * 2 * 32) == 0 && Gi * 2 <= max_row_blocks(M, Gj)) Gi *= 2;
   if (M == 1) {
-    // fill the remaining CUs by splitting the hidden layer further
-    while (Gi * Gj * 2 <= n_cu && (H + 64 * Gj * 2 - 1) / (64 * Gj * 2) * 64 >= 64 && H > 64 * Gj)
-      Gj *= 2;
+    auto skew = [&](int gi, int gj) {   // how far from square the blocks are
+      const double r = (double)(b / gi) / (double)((H + 64 * gj - 1) / (64 * gj) * 64);
+      return r < 1.0 ? 1.0 / r : r;
+    };
+    const int most_cu = std::min(n_cu, kMaxGrid);
+    const int short_rows = c.prec == MLP_FP32 ? 128 : 32;   // row blocks of less than 64 rows: at most so many
+    for (int gj = Gj0; gj <= kMaxHiddenBlocks && (gj == Gj0 || H > 64 * (gj / 2)) && gj <= most_cu; gj *= 2)
+      for (int gi = 1; gi * gj <= most_cu && gi <= kMaxRowBlocks && b % ((int64_t)gi * 32) == 0; gi *= 2) {
+        if (b / gi < 64 && gi > short_rows) break;
+        if (gi * gj > Gi * Gj || (gi * gj == Gi * Gj && skew(gi, gj) < skew(Gi, Gj))) {
+          Gi = gi;
+          Gj = gj;
+        }
+      }
     if (g_grid_rows > 0 && g_grid_hidden > 0) {
       Gi = g_grid_rows;
       Gj = g_grid_hidden;
