@@ -473,45 +473,42 @@ const void *small_kernel(int ht, int ft) {
 // one barrier per epoch suffices and no per-wave partial gradients exist:
 // LDS holds X, the parameters and the shares only (the targets of a lane's
 // rows stay in its registers for the run).  The row stride of X and W1 is
-// DK + 2, the z1 contraction's length: the gW1 operand of the feature block
-// past DK reads into the next row, which only feeds gradients of padding
+// the z1 contraction's length: the gW1 operand of the feature block past it
+// reads into the next row, which only feeds gradients of padding
 // features that are never applied; so three 120-row, 64-unit nets share a CU.
 // Limits: N <= 128 rows, H <= 16 NW <= 64, D <= 48, K <= KO <= 4.
 struct HSplitLayout {
-  int N, H, D, NW, KO, NP, NPT, DA, DK, DN, FT, XS, HP;
+  int NP, HP, XS, NW, KO;
   __host__ __device__ HSplitLayout(int n, int h, int d, int nw, int ko)
-      : N(n), H(h), D(d), NW(nw), KO(ko) {
-    NP = (n + 15) / 16 * 16;
-    NPT = NP / 16;
-    DA = d + 1;
-    DK = (DA + 3) / 4 * 4;
-    DN = (DA + 15) / 16 * 16;
-    FT = DN / 16;
-    XS = DK + 2;
-    HP = (h + 15) / 16 * 16;
-  }
+      : NP((n + 15) / 16 * 16), HP((h + 15) / 16 * 16), XS(row_stride(steps(d))), NW(nw), KO(ko) {}
+  __host__ __device__ static constexpr int steps(int d) { return (d + 1 + 3) / 4; }
+  // an odd multiple of 4: the 16 rows x 4 features of a z1 operand lie in 64 banks
+  __host__ __device__ static constexpr int row_stride(int ks) { return 4 * (ks | 1); }
   __host__ __device__ int xs() const { return 0; }                 // [NP][XS] rows, ones column
   __host__ __device__ int w1() const { return xs() + NP * XS; }    // [HP][XS] W1 | b1
-  __host__ __device__ int w2() const { return w1() + HP * XS; }    // [4][HP]
-  __host__ __device__ int zs() const { return w2() + 4 * HP; }     // [2][NW][NP][KO] z2 shares
-  __host__ __device__ int dst() const { return zs() + 2 * NW * NP * KO; }   // [NW][2][16][16] staging
+  __host__ __device__ int w2() const { return w1() + HP * XS; }    // [4][64]
+  __host__ __device__ int zs() const { return w2() + 256; }        // [2][NW][NP][KO] z2 shares
+  __host__ __device__ int dst() const { return (zs() + 2 * NW * NP * KO + 3) / 4 * 4; }   // [NW][2][16][16] staging
   __host__ __device__ int dd() const { return dst() + NW * 512; }  // [NW][2][16][4] delta2 staging
   __host__ __device__ int total() const { return dd() + NW * 128 + 64; }   // + the over-read of the last X row
 };
 
 // At most 168 registers per lane (three waves per SIMD): three of the
 // largest nets (52 KB of LDS each) share a CU.
-template <int NW, int KO>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) void k_small_hsplit(
+// The contraction's length is a template size (KS steps of 4 features), so
+// every LDS address is a lane's base and an immediate.
+template <int KS, int KO>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_small_hsplit(
     const mlp_batch_item *__restrict__ items, mlp_batch_item one, int D, int K,
     const float *__restrict__ X, const float *__restrict__ T, float *__restrict__ theta,
     float *__restrict__ comp, int epochs, float *__restrict__ loss_hist) {
-  constexpr int NT = NW * 64;
+  constexpr int XS = HSplitLayout::row_stride(KS), FT = (KS + 3) / 4, WS2 = 64;   // WS2: row stride of W2
+  const int NT = blockDim.x, NW = NT >> 6;
   const mlp_batch_item it = items ? items[blockIdx.x] : one;
   const int N = it.n_rows, H = it.n_hidden;
   const float lr = it.lr;
   const HSplitLayout L(N, H, D, NW, KO);
-  const int XS = L.XS, HP = L.HP, FT = L.FT, DK = L.DK, NP = L.NP, NPT = L.NPT;
+  const int HP = L.HP, NP = L.NP, NPT = NP / 16;
   const int HTn = HP / 16;   // hidden tiles of this net
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16_0 = lane & 15, lg_0 = lane >> 4;
@@ -550,8 +547,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
     const int n = rt * 16 + l16;
     tv[rt] = (n < N && lg < K) ? Tg[(int64_t)n * K + lg] : 0.0f;
   }
-  for (int i = tid; i < 4 * HP; i += NT) {
-    const int k = i / HP, h = i - k * HP;
+  for (int i = tid; i < 4 * WS2; i += NT) {
+    const int k = i / WS2, h = i - k * WS2;
     W2s[i] = (k < K && h < H) ? P[oW2 + k * H + h] : 0.0f;
   }
   // this wave's tile and the parameters its lanes update: W1[h0 + 4 lg + i]
@@ -559,9 +556,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
   // b2[lg] (every wave's own copy)
   const bool own = wave < HTn;
   const int h0 = wave * 16;
-  float c1[4][4], c2[4];
+  float c1[FT][4], c2[4];
 #pragma unroll
-  for (int ft = 0; ft < 4; ++ft)
+  for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int h = h0 + 4 * lg + i, d = 16 * ft + l16;
@@ -580,18 +577,25 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
   const float inv_nk = 1.0f / (float)(N * K);
 
   for (int e = 0; e < epochs; ++e) {
-    float *zs = Zs + (e & 1) * (NW * NP * KO);
+    float *zs = Zs + (e & 1) * (NW * NP * KO) + l16_0 * KO + lg_0;   // this lane's share in wave 0's row tile 0
     // the lane coordinates, opaque to the compiler each epoch: the per-lane
     // LDS addresses are formed here instead of being hoisted out of the
     // epoch loop and held (or spilled) for the whole run
     int l16 = l16_0, lg = lg_0;
     asm volatile("" : "+v"(l16), "+v"(lg));
     float ez[8][4];   // e^-z1 of this wave's units, every row tile (a and the slope are re-formed from it)
+    const int ZW = NP * KO;   // z2 shares of a wave
     // ======================= phase A: a of this wave's tile, its share of z2
     // Row tiles go in pairs whose two z1 chains share the W1 operand and
     // interleave on the matrix cores (a lone last tile runs its own chain).
     if (own) {
       const float *wb = W1s + (h0 + l16) * XS + lg;
+      float w[KS];
+#pragma unroll
+      for (int s = 0; s < KS; ++s) w[s] = wb[4 * s];
+      f32x4_s w2v[KO];
+#pragma unroll
+      for (int k = 0; k < KO; ++k) w2v[k] = *reinterpret_cast<const f32x4_s *>(W2s + k * WS2 + h0 + 4 * lg);
       auto finish = [&](auto rt_c, const f32x4_s &z) {
         constexpr int rt = decltype(rt_c)::value;
         float a[4];
@@ -601,11 +605,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
         }
         float zp[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int k = 0; k < KO; ++k) {
-          const f32x4_s w = *reinterpret_cast<const f32x4_s *>(W2s + k * HP + h0 + 4 * lg);
+        for (int k = 0; k < KO; ++k)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) zp[k] = fmaf(a[i], w[i], zp[k]);
-        }
+          for (int i = 0; i < 4; ++i) zp[k] = fmaf(a[i], w2v[k][i], zp[k]);
         // reduce-scatter over the row's four lane groups: lane (row, lg)
         // ends with output lg of the row
         const bool hi2 = (lg & 2) != 0, hi1 = (lg & 1) != 0;
@@ -614,7 +616,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
         ka += __shfl_xor(sa, 32, kWave);
         kb += __shfl_xor(sb, 32, kWave);
         const float share = (hi1 ? kb : ka) + __shfl_xor(hi1 ? ka : kb, 16, kWave);
-        if (lg < KO) zs[(wave * NP + rt * 16 + l16) * KO + lg] = share;
+        if (lg < KO) zs[wave * ZW + rt * 16 * KO] = share;
       };
       auto pair = [&](auto r0_c) {
         constexpr int r0 = decltype(r0_c)::value;
@@ -622,32 +624,26 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
         if (r0 + 1 < NPT) {
           const float *xb = xa + 16 * XS;
           f32x4_s za = {0.f, 0.f, 0.f, 0.f}, zb = {0.f, 0.f, 0.f, 0.f};
-          // four steps' operands at a time, ahead of their products
-          int k0 = 0;
-          for (; k0 + 16 <= DK; k0 += 16) {
-            float w[4], a[4], b[4];
+          float a[KS], b[KS];   // read ahead of the products
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-              w[s] = wb[k0 + 4 * s];
-              a[s] = xa[k0 + 4 * s];
-              b[s] = xb[k0 + 4 * s];
-            }
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-              za = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], a[s], za, 0, 0, 0);
-              zb = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], b[s], zb, 0, 0, 0);
-            }
+          for (int s = 0; s < KS; ++s) {
+            a[s] = xa[4 * s];
+            b[s] = xb[4 * s];
           }
-          for (; k0 < DK; k0 += 4) {
-            const float w = wb[k0];
-            za = __builtin_amdgcn_mfma_f32_16x16x4f32(w, xa[k0], za, 0, 0, 0);
-            zb = __builtin_amdgcn_mfma_f32_16x16x4f32(w, xb[k0], zb, 0, 0, 0);
+#pragma unroll
+          for (int s = 0; s < KS; ++s) {
+            za = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], a[s], za, 0, 0, 0);
+            zb = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], b[s], zb, 0, 0, 0);
           }
           finish(std::integral_constant<int, r0>{}, za);
           finish(std::integral_constant<int, r0 + 1>{}, zb);
         } else if (r0 < NPT) {
           f32x4_s za = {0.f, 0.f, 0.f, 0.f};
-          for (int k0 = 0; k0 < DK; k0 += 4) za = __builtin_amdgcn_mfma_f32_16x16x4f32(wb[k0], xa[k0], za, 0, 0, 0);
+          float a[KS];
+#pragma unroll
+          for (int s = 0; s < KS; ++s) a[s] = xa[4 * s];
+#pragma unroll
+          for (int s = 0; s < KS; ++s) za = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], a[s], za, 0, 0, 0);
           finish(std::integral_constant<int, r0>{}, za);
         }
       };
@@ -662,17 +658,21 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
     // Row tiles again go in pairs (two staging buffers), every product in
     // the order a tile-by-tile loop would issue it, so a pair gives the same
     // bits as its two tiles one after the other.
-    f32x4_s gacc[4], g2 = {0.f, 0.f, 0.f, 0.f};
+    f32x4_s gacc[FT], g2 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ft = 0; ft < 4; ++ft) gacc[ft] = f32x4_s{0.f, 0.f, 0.f, 0.f};
+    for (int ft = 0; ft < FT; ++ft) gacc[ft] = f32x4_s{0.f, 0.f, 0.f, 0.f};
     float gb2 = 0.0f, sq = 0.0f;
     // delta2 of row tile rt in lane (row l16, output lg)
     auto delta2 = [&](auto rt_c) {
       constexpr int rt = decltype(rt_c)::value;
       const int n = rt * 16 + l16, k = lg;
       float z2 = 0.0f;
-      if (k < KO)
-        for (int w = 0; w < HTn; ++w) z2 += zs[(w * NP + n) * KO + k];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {   // (a share past the net's last wave: its own last one, adding zero)
+        const float share = zs[min(w, HTn - 1) * ZW + rt * 16 * KO];
+        z2 += w < HTn ? share : 0.0f;
+      }
+      if (k >= KO) z2 = 0.0f;   // no output: another row's share
       const float y = sigmoid(z2 + b2v);
       const bool on = k < K && n < N;
       const float err = on ? y - tv[rt] : 0.0f;
@@ -707,25 +707,26 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
       // delta1^T = W2^T delta2^T (the pre-update W2), times the slope
 #pragma unroll
       for (int j = 0; j < NR; ++j) {
-        const f32x4_s bp = __builtin_amdgcn_mfma_f32_16x16x4f32(W2s[lg * HP + h0 + l16], d2[j],
+        const f32x4_s bp = __builtin_amdgcn_mfma_f32_16x16x4f32(W2s[lg * WS2 + h0 + l16], d2[j],
                                                                f32x4_s{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
         *reinterpret_cast<f32x4_s *>(Dst + j * 256 + l16 * 16 + 4 * lg) =
             f32x4_s{bp[0] * sl[j][0], bp[1] * sl[j][1], bp[2] * sl[j][2], bp[3] * sl[j][3]};
       }
       // gW1 += delta1^T [X 1] (M = hidden, N = features, K = the tile's rows)
 #pragma unroll
-      for (int ft = 0; ft < 4; ++ft) {
-        if (ft < FT) {
-          f32x4_s g = gacc[ft];
+      for (int j = 0; j < NR; ++j) {
+        float da[4], xb[FT][4];
 #pragma unroll
-          for (int j = 0; j < NR; ++j) {
-            const float *da = Dst + j * 256 + lg * 16 + l16;
-            const float *xb = Xs + ((r0 + j) * 16 + lg) * XS + ft * 16 + l16;
+        for (int s = 0; s < 4; ++s) {
+          da[s] = Dst[j * 256 + (lg + 4 * s) * 16 + l16];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) g = __builtin_amdgcn_mfma_f32_16x16x4f32(da[s * 64], xb[s * 4 * XS], g, 0, 0, 0);
-          }
-          gacc[ft] = g;
+          for (int ft = 0; ft < FT; ++ft) xb[ft][s] = Xs[((r0 + j) * 16 + lg + 4 * s) * XS + ft * 16 + l16];
         }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int ft = 0; ft < FT; ++ft)
+            gacc[ft] = __builtin_amdgcn_mfma_f32_16x16x4f32(da[s], xb[ft][s], gacc[ft], 0, 0, 0);
       }
     };
     auto pair_b = [&](auto r0_c) {
@@ -743,16 +744,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
     }
     // ======================= update: this wave's W1 rows and W2 columns, b2
 #pragma unroll
-    for (int ft = 0; ft < 4; ++ft) {
-      if (ft < FT) {
+    for (int i = 0; i < 4; ++i) {
+      const int h = h0 + 4 * lg + i;
+      if (h < H) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int h = h0 + 4 * lg + i, d = 16 * ft + l16;
-          if (h < H && d < D1) {
-            const int o = h * XS + d;
-            float wv = W1s[o];
+        for (int ft = 0; ft < FT; ++ft) {
+          if (ft < FT - 1 || 16 * ft + l16 < D1) {
+            float *wp = W1s + (h0 + 4 * lg) * XS + l16 + i * XS + 16 * ft;
+            float wv = *wp;
             gd_update(wv, c1[ft][i], lr, gacc[ft][i], compensated);
-            W1s[o] = wv;
+            *wp = wv;
           }
         }
       }
@@ -762,7 +763,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
       for (int i = 0; i < 4; ++i) {
         const int h = h0 + 4 * lg + i;
         if (h < H) {
-          const int o = l16 * HP + h;
+          const int o = l16 * WS2 + h;
           float wv = W2s[o];
           gd_update(wv, c2[i], lr, g2[i], compensated);
           W2s[o] = wv;
@@ -778,16 +779,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
   // ---- write the trained parameters (and compensation) back once
   if (own) {
 #pragma unroll
-    for (int ft = 0; ft < 4; ++ft) {
-      if (ft < FT) {
+    for (int ft = 0; ft < FT; ++ft) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int h = h0 + 4 * lg + i, d = 16 * ft + l16;
-          if (h < H && d < D1) {
-            const int o = d < D ? h * D + d : oB1 + h;
-            P[o] = W1s[h * XS + d];
-            if (compensated) Cp[o] = c1[ft][i];
-          }
+      for (int i = 0; i < 4; ++i) {
+        const int h = h0 + 4 * lg + i, d = 16 * ft + l16;
+        if (h < H && d < D1) {
+          const int o = d < D ? h * D + d : oB1 + h;
+          P[o] = W1s[h * XS + d];
+          if (compensated) Cp[o] = c1[ft][i];
         }
       }
     }
@@ -796,7 +795,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
       for (int i = 0; i < 4; ++i) {
         const int h = h0 + 4 * lg + i;
         if (h < H) {
-          P[oW2 + l16 * H + h] = W2s[l16 * HP + h];
+          P[oW2 + l16 * H + h] = W2s[l16 * WS2 + h];
           if (compensated) Cp[oW2 + l16 * H + h] = c2[i];
         }
       }
@@ -808,25 +807,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
   }
 }
 
-template <int NW, int KO>
-hipError_t launch_hsplit_one(const mlp_batch_item *items, mlp_batch_item one, int n_nets, int n_in, int n_out,
-                             size_t lds, const float *X, const float *T, float *theta, float *comp, int epochs,
-                             float *loss_hist, hipStream_t s) {
-  auto kern = k_small_hsplit<NW, KO>;
-  hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(n_nets), dim3(NW * 64), lds, s, items, one, n_in, n_out, X, T, theta, comp,
-                     epochs, loss_hist);
-  return hipGetLastError();
-}
-
-template <int NW>
-hipError_t launch_hsplit_nw(const mlp_batch_item *items, mlp_batch_item one, int n_nets, int n_in, int n_out,
-                            size_t lds, const float *X, const float *T, float *theta, float *comp, int epochs,
-                            float *loss_hist, hipStream_t s) {
-  if (n_out <= 3)
-    return launch_hsplit_one<NW, 3>(items, one, n_nets, n_in, n_out, lds, X, T, theta, comp, epochs, loss_hist, s);
-  return launch_hsplit_one<NW, 4>(items, one, n_nets, n_in, n_out, lds, X, T, theta, comp, epochs, loss_hist, s);
+// The instance for KS steps of 4 features (n_in <= 48 and the constant column).
+template <int KO, int KS = 13>
+const void *hsplit_kernel(int steps) {
+  if constexpr (KS > 1) {
+    if (steps < KS) return hsplit_kernel<KO, KS - 1>(steps);
+  }
+  return reinterpret_cast<const void *>(&k_small_hsplit<KS, KO>);
 }
 
 }  // namespace mlpk
@@ -872,14 +859,13 @@ hipError_t launch_small_train(const mlp_batch_item *items, mlp_batch_item one, i
       const int nw = tiles <= 1 ? 1 : (tiles <= 2 ? 2 : 4);
       const size_t lds =
           sizeof(float) * (size_t)mlpk::HSplitLayout(max_rows, max_hidden, n_in, nw, n_out <= 3 ? 3 : 4).total();
-      if (nw == 1)
-        return mlpk::launch_hsplit_nw<1>(items, one, n_nets, n_in, n_out, lds, X, T, theta, comp, epochs,
-                                         loss_hist, s);
-      if (nw == 2)
-        return mlpk::launch_hsplit_nw<2>(items, one, n_nets, n_in, n_out, lds, X, T, theta, comp, epochs,
-                                         loss_hist, s);
-      return mlpk::launch_hsplit_nw<4>(items, one, n_nets, n_in, n_out, lds, X, T, theta, comp, epochs,
-                                       loss_hist, s);
+      const int steps = mlpk::HSplitLayout::steps(n_in);
+      const void *kern = n_out <= 3 ? mlpk::hsplit_kernel<3>(steps) : mlpk::hsplit_kernel<4>(steps);
+      hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+      void *args[] = {&items, &one, &n_in, &n_out, &X, &T, &theta, &comp, &epochs, &loss_hist};
+      e = hipLaunchKernel(kern, dim3(n_nets), dim3(64 * nw), args, lds, s);
+      return e == hipSuccess ? hipGetLastError() : e;
     }
     threads = 128;   // the variants run on the row-split form
   }
