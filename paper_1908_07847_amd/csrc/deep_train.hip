@@ -427,8 +427,7 @@ __global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
         }
       }
       if (it == 0) {   // the tile that also sums its units' bias gradients
-        gb += __shfl_xor(gb, 16, kWave);
-        gb += __shfl_xor(gb, 32, kWave);
+        gb = sum_rows(gb);
         const int o = 16 * ot + l16;
         if (lg == 0 && o < wo) {
           float *bp = sm + p.boff[l] + o;

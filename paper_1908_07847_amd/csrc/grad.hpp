@@ -216,16 +216,12 @@ __global__ __launch_bounds__(64 * kGWaves) void k_grad_sum(int64_t n, int din, i
   if (first_f) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      float v = gb[t];
-      v += __shfl_xor(v, 16, kWave);
-      v += __shfl_xor(v, 32, kWave);
+      const float v = sum_rows(gb[t]);
       if (lg == 0) small[wave][16 * t + l16][0] = v;
       if constexpr (KO > 0) {
 #pragma unroll
         for (int k = 0; k < KO; ++k) {
-          float g = gw2[t][k];
-          g += __shfl_xor(g, 16, kWave);
-          g += __shfl_xor(g, 32, kWave);
+          const float g = sum_rows(gw2[t][k]);
           if (lg == 0) small[wave][16 * t + l16][1 + k] = g;
         }
       }

@@ -1397,7 +1397,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
 
     // loss and gb2 partials of this net's row block (hidden block 0 only)
     if (gj == 0) {
-      for (int off = 32; off >= 1; off >>= 1) gb2 += __shfl_xor(gb2, off, kWave);
+      gb2 = wave_sum(gb2);
       sq = wg_reduce_sum(sq, 0);
       if (tid == 0) xst(a.lossp + (int64_t)gi * a.M + net, sq);
       if (lane == 0 && wave < K) xst(a.gp + ((int64_t)gi * a.M + net) * go.q + go.nw + a.Hp * (1 + K) + wave, gb2);
@@ -1422,16 +1422,11 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
           for (int fb = 0; fb < 4; ++fb)
             if (fb < NFB)
               xst16(gpr, 4u * (row + (uint32_t)((tile * NFB + fb) * 256 + lane_o * 4)), gacc[hb][fb] * gscale);
-          float v = gb1[hb];
-          v += __shfl_xor(v, 16, kWave);
-          v += __shfl_xor(v, 32, kWave);
+          const float v = sum_rows(gb1[hb]);
           float w[KO];
 #pragma unroll
           for (int k = 0; k < KO; ++k) {
-            float t = gw2[hb][k];
-            t += __shfl_xor(t, 16, kWave);
-            t += __shfl_xor(t, 32, kWave);
-            w[k] = t;
+            w[k] = sum_rows(gw2[hb][k]);
           }
           if (lane_o < 16) {
             float *g1 = gpi + go.nw + tile * 16 + lane_o;

@@ -51,6 +51,29 @@ __device__ __forceinline__ float sigmoid_slope_of_e(float e, float &slope) {
   return r;
 }
 
+// sigmoid_e of four values, stage by stage: the same bits; left to itself the
+// compiler may run the four chains one after the other (60 cycles each).
+__device__ __forceinline__ void sigmoid_e4(const float *z, float *a, float *e) {
+  const float L_HI = 1.44269502162933349609375f, L_LO = 1.925963033500011079e-08f, LN2 = 0.693147180559945309f;
+  float tl[4], r[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float th = -z[i] * L_HI;
+    tl[i] = fmaf(-z[i], L_LO, fmaf(-z[i], L_HI, -th)) * LN2;
+    e[i] = __builtin_amdgcn_exp2f(fminf(th, 126.0f));
+  }
+  asm volatile("" : "+v"(e[0]), "+v"(e[1]), "+v"(e[2]), "+v"(e[3]));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    e[i] = fmaf(e[i], tl[i], e[i]);
+    a[i] = 1.0f + e[i];
+    r[i] = __builtin_amdgcn_rcpf(a[i]);
+  }
+  asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a[i] = fmaf(r[i], fmaf(-a[i], r[i], 1.0f), r[i]);
+}
+
 __device__ __forceinline__ float sigmoid(float z) {
   float e;
   return sigmoid_e(z, e);
@@ -106,14 +129,27 @@ __device__ __forceinline__ float gld(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
 }
 
-// Sum over the 64 lanes of a wave, fixed butterfly order (deterministic).
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
+// Lanes 0..31: a plus a of lane + 32; lanes 32..63: b plus b of lane - 32 (one
+// exchange in the vector unit; a shuffle goes through the LDS crossbar).
+__device__ __forceinline__ float add_swap32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b),
+                                                  false, false);
+  const uint32_t x = r[0], y = r[1];
+  return __builtin_bit_cast(float, x) + __builtin_bit_cast(float, y);
+}
+// The same between neighbouring rows of 16 lanes: even rows a, odd rows b.
+__device__ __forceinline__ float add_swap16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b),
+                                                  false, false);
+  const uint32_t x = r[0], y = r[1];
+  return __builtin_bit_cast(float, x) + __builtin_bit_cast(float, y);
 }
 
-__device__ __forceinline__ int round_up(int v, int m) { return (v + m - 1) / m * m; }
+// Sum over lanes l, l + 16, l + 32, l + 48, in every one of them.
+__device__ __forceinline__ float sum_rows(float v) {
+  v = add_swap16(v, v);
+  return add_swap32(v, v);
+}
 
 // v plus lane (v) permuted by a DPP row pattern (a VALU op, no LDS traffic).
 template <int CTRL>
@@ -121,6 +157,18 @@ __device__ __forceinline__ float add_dpp(float v) {
   const int s = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false);
   return v + __builtin_bit_cast(float, s);
 }
+
+// Sum over the 64 lanes of a wave, fixed butterfly order (deterministic).
+__device__ __forceinline__ float wave_sum(float v) {
+  v = add_swap32(v, v);
+  v = add_swap16(v, v);
+  v = add_dpp<0x128>(v);   // row_ror 8
+  v += __shfl_xor(v, 4, kWave);
+  v = add_dpp<0x4E>(v);    // quad_perm [2,3,0,1]
+  return add_dpp<0xB1>(v); // quad_perm [1,0,3,2]
+}
+
+__device__ __forceinline__ int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 // Sum over each row of 16 lanes: swap neighbours, swap pairs, mirror within
 // 8, mirror within 16.  Every lane of the row ends with the same value

@@ -88,8 +88,13 @@ __device__ __forceinline__ f32x4_s quad(const float *q) {
   return f32x4_s{lo.x, lo.y, hi.x, hi.y};
 }
 
+// Waves per SIMD that the registers have to allow: two workgroups of 8 waves
+// on a CU where the kernel is near 128 registers (472 nets of up to 32 units
+// and 30 features: 307 us, with 130 registers 347).
+constexpr int small_waves(int nw, int htm, int ft) { return nw == 8 ? (htm <= 2 && ft <= 2 ? 4 : 2) : 1; }
+
 template <int NW, int HTM, int FT, int ACT>
-__global__ __launch_bounds__(NW * 64) void k_small_train(
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(small_waves(NW, HTM, FT)))) void k_small_train(
     const mlp_batch_item *__restrict__ items, mlp_batch_item one, int D, int K,
     const float *__restrict__ X, const float *__restrict__ T, float *__restrict__ theta,
     float *__restrict__ comp, int epochs, float *__restrict__ loss_hist, SmallVariant var) {
@@ -240,6 +245,12 @@ __global__ __launch_bounds__(NW * 64) void k_small_train(
       // its products (one step at a time, each product waited for its own
       // reads: z1 and sigma took 1490 of a 60-row epoch's 5460 cycles).
       if (!keep_x) load_x(r0);
+      const float b2k = b2s[lg], tk = Ts[n * 4 + lg];
+      f32x4_s w2v[KO];   // one hidden tile: its W2 is read ahead of the products too (more: not enough registers)
+      if (HTM == 1) {
+#pragma unroll
+        for (int k = 0; k < KO; ++k) w2v[k] = quad(W2s + k * HP + 4 * lg);
+      }
       float av[HTM][4], sl[HTM][4];
 #pragma unroll
       for (int ht = 0; ht < HTM; ++ht) {
@@ -255,8 +266,19 @@ __global__ __launch_bounds__(NW * 64) void k_small_train(
 #pragma unroll
             for (int s = 0; s < 4; ++s) z = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[g][s], xv[g][s], z, 0, 0, 0);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) av[ht][i] = hidden_act(ACT, z[i], sl[ht][i]);
+          for (int i = 0; i < 4; ++i) av[ht][i] = ACT == 0 ? z[i] : hidden_act(ACT, z[i], sl[ht][i]);
+          if (ACT == 0) {
+            float ez[4];
+            sigmoid_e4(av[ht], av[ht], ez);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sl[ht][i] = (ez[i] * av[ht][i]) * av[ht][i];
+          }
         }
+      }
+      if (HTM == 1) {   // read by here, not one by one below
+        asm volatile("" ::"v"(b2k), "v"(tk));
+#pragma unroll
+        for (int k = 0; k < KO; ++k) asm volatile("" ::"v"(w2v[k]));
       }
       // output layer: each lane's share of z2 (its 4 hidden units per tile)
       // for every output, then a reduce-scatter over the four row groups
@@ -269,21 +291,16 @@ __global__ __launch_bounds__(NW * 64) void k_small_train(
         const int hs = (ht < HT ? ht : 0) * 16 + 4 * lg;
 #pragma unroll
         for (int k = 0; k < KO; ++k) {
-          const f32x4_s w = *reinterpret_cast<const f32x4_s *>(W2s + k * HP + hs);
+          const f32x4_s w = HTM == 1 ? w2v[k] : quad(W2s + k * HP + hs);
 #pragma unroll
           for (int i = 0; i < 4; ++i) zp[k] = fmaf(av[ht][i], w[i], zp[k]);
         }
       }
-      const bool hi2 = (lg & 2) != 0, hi1 = (lg & 1) != 0;
-      float ka = hi2 ? zp[2] : zp[0], kb = hi2 ? zp[3] : zp[1];   // outputs kept
-      const float sa = hi2 ? zp[0] : zp[2], sb = hi2 ? zp[1] : zp[3];
-      ka += __shfl_xor(sa, 32, kWave);
-      kb += __shfl_xor(sb, 32, kWave);
-      const float z2 = (hi1 ? kb : ka) + __shfl_xor(hi1 ? ka : kb, 16, kWave);
+      const float z2 = add_swap16(add_swap32(zp[0], zp[2]), add_swap32(zp[1], zp[3]));
       const int k = lg;
-      const float y = sigmoid(z2 + b2s[k]);
+      const float y = sigmoid(z2 + b2k);
       const bool on = k < K && n < N;
-      const float err = on ? y - Ts[n * 4 + k] : 0.0f;
+      const float err = on ? y - tk : 0.0f;
       sq = fmaf(err, err, sq);
       const float d2 = dscale * err * y * (1.0f - y);
       gb2 += d2;
@@ -598,11 +615,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       for (int k = 0; k < KO; ++k) w2v[k] = *reinterpret_cast<const f32x4_s *>(W2s + k * WS2 + h0 + 4 * lg);
       auto finish = [&](auto rt_c, const f32x4_s &z) {
         constexpr int rt = decltype(rt_c)::value;
-        float a[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          a[i] = sigmoid_e(z[i], ez[rt][i]);
-        }
+        float a[4] = {z[0], z[1], z[2], z[3]};
+        sigmoid_e4(a, a, ez[rt]);
         float zp[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int k = 0; k < KO; ++k)
@@ -610,12 +624,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
           for (int i = 0; i < 4; ++i) zp[k] = fmaf(a[i], w2v[k][i], zp[k]);
         // reduce-scatter over the row's four lane groups: lane (row, lg)
         // ends with output lg of the row
-        const bool hi2 = (lg & 2) != 0, hi1 = (lg & 1) != 0;
-        float ka = hi2 ? zp[2] : zp[0], kb = hi2 ? zp[3] : zp[1];
-        const float sa = hi2 ? zp[0] : zp[2], sb = hi2 ? zp[1] : zp[3];
-        ka += __shfl_xor(sa, 32, kWave);
-        kb += __shfl_xor(sb, 32, kWave);
-        const float share = (hi1 ? kb : ka) + __shfl_xor(hi1 ? ka : kb, 16, kWave);
+        const float share = add_swap16(add_swap32(zp[0], zp[2]), add_swap32(zp[1], zp[3]));
         if (lg < KO) zs[wave * ZW + rt * 16 * KO] = share;
       };
       auto pair = [&](auto r0_c) {
