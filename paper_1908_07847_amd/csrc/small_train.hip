@@ -839,11 +839,11 @@ size_t small_lds_bytes(int n_rows, int n_hidden, int n_in, int threads, bool mom
 
 // Launch shape of n_nets nets of at most max_hidden units (0: no hint).  Up
 // to one net per CU a net's own epoch counts: 8 waves (86 nets of 120 rows x
-// 63 units, 20 epochs: 171 us against 224 on 4 waves, 275 hidden-split).
+// 63 units, 20 epochs: 170 us against 220 on 4 waves, 206 hidden-split).
 // Above, the chip is shared and the work of a net counts: hidden-split over
-// 32 units (1450 nets of 120 rows x 64 units: 760 us against 883 on 8 waves,
-// 1038 on 2 and 1225 on 4), else 4 waves (1465 nets of up to 32 units: 452 us
-// against 521 on 8, 597 hidden-split; 2759 of up to 16: 368, 392, 713).
+// 32 units (1450 nets of 120 rows x 64 units: 804 us against 1014 on 8 waves,
+// 1227 on 2 and 1312 on 4), else 4 waves (1465 nets of 32 units: 472 us
+// against 555 on 8, 582 hidden-split; 2759 of 16: 428, 455, 701).
 int small_threads(int n_nets, int max_hidden, int n_cu, int hint) {
   if (hint == kHiddenSplit || hint == 128 || hint == 256 || hint == 512) return hint;
   if (n_nets <= n_cu) return 512;

@@ -1,5 +1,6 @@
 """Every instance of the row-split small trainer (hidden tiles x feature tiles,
-2, 4 and 8 waves) at the edges of its tiles, against the FP64 oracle."""
+2, 4 and 8 waves) and of the hidden-split one (steps of four features) at the
+edges of its tiles, against the FP64 oracle."""
 import sys
 
 import numpy as np
@@ -28,6 +29,17 @@ def M():
     (65, 48, 49, 3),    # four feature tiles, four hidden tiles
 ])
 def test_small_instances_match_the_oracle(M, threads, n, d, h, k):
+    check(M, threads, n, d, h, k)
+
+
+@pytest.mark.parametrize("n,d,h,k", [(16 + 7 * i, d, h, 1 + i % 4) for i, (d, h) in enumerate(
+    [(1, 5), (3, 16), (4, 17), (8, 33), (12, 64), (16, 30), (20, 48), (24, 49), (28, 20), (32, 32), (36, 61),
+     (40, 64), (44, 16), (47, 50), (48, 64)])])
+def test_hidden_split_instances_match_the_oracle(M, n, d, h, k):
+    check(M, 64, n, d, h, k)
+
+
+def check(M, threads, n, d, h, k):
     print(f"small n={n} {d}-{h}-{k}, {threads} threads", flush=True)
     sys.stdout.flush()
     g = np.random.default_rng(n + h)
