@@ -177,8 +177,9 @@ def timed(fn, stream):
     return time.perf_counter() - t0, ev0.elapsed_time(ev1) / 1e3
 
 
-# grid-wide synchronisations per minibatch step of the large-N trainer
-LARGE_BARRIERS_PER_STEP = 3
+# grid-wide synchronisations per minibatch step of the large-N trainer (a
+# third one is among the workgroups of a row block only)
+LARGE_BARRIERS_PER_STEP = 2
 
 
 def sync_adjusted(mlp, torch, flops: float, peak_tflops: float, hbm_bytes: float, n_steps: int, kernel_s: float):

@@ -383,7 +383,7 @@ mlp_status mlp_deep_train(const float *X, const float *T, int64_t n, int32_t n_l
 /* Grid-barrier latency probe for the sync-adjusted bound of the large-N
  * trainer: one cooperative launch of n_workgroups workgroups (256 threads
  * each, at most one per CU on the device) that pass `rounds` grid barriers
- * of the kind the large-N trainer passes three times per minibatch step
+ * of the kind the large-N trainer passes twice per minibatch step
  * (section 2.2's loop: forward, backpropagation, update), and do nothing
  * else.  Timing two launches with different round counts on the stream
  * gives the time one barrier adds.

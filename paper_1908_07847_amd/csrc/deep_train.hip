@@ -227,7 +227,7 @@ __global__ __launch_bounds__(mlph::kDeepThreads) void k_deep_train(
 // Bound: one workgroup's chain of dependent products, LDS reads and
 // activations.  The lane-per-entry form above reads both operands of every
 // product from LDS one float at a time and passes eight barriers per epoch of
-// a three-layer network: 11.6 us for 33-16-16-3 on 120 rows, here 3.9.
+// a three-layer network: 11.6 us for 33-16-16-3 on 120 rows, here 3.7.
 using mlph::DeepTilePlan;
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 

@@ -38,7 +38,8 @@
 // output deltas 1.4, gradients 3.4 and their stores 1.3, grid barrier 2.9,
 // update 1.8, grid barrier 2.7.  For 64-1024-3 at 16384 rows the float32
 // products (z1 twice, gW1) and the vector work, which share the SIMDs' float32
-// units, take 54 of 88.5 us (96.5 before); bf16 44, e4m3 48 us.
+// units, take 54 of 88.5 us (96.5 before); bf16 41.3, e4m3 45.8 us (49.7 and
+// 58.8 before).
 // All reductions use fixed orders, so runs are bitwise repeatable.
 #include <hip/hip_runtime.h>
 
@@ -319,6 +320,16 @@ __device__ __forceinline__ float hidden_sigmoid_slope(float z, float cz, float b
   return a;
 }
 
+// sum_rows, in e4m3 as shuffles (64-1024-3 at 16384 rows: 45.8 us a step
+// against 46.3 with lane exchanges, whose second operand is a register more
+// where the instance has none left; float32 88.7 against 88.3).
+template <int PREC>
+__device__ __forceinline__ float sum_rows_of(float v) {
+  if (PREC != 2) return sum_rows(v);
+  v += __shfl_xor(v, 16, kWave);
+  return v + __shfl_xor(v, 32, kWave);
+}
+
 constexpr int kStageU = 16;  // loads in flight per thread while staging
 constexpr int kPre = 32;     // X elements per thread loaded in one batch for a step's first piece
 constexpr int kRedU = 12;    // 16-byte partial-gradient loads in flight per thread
@@ -332,13 +343,8 @@ __device__ __forceinline__ int div_by(int q, uint32_t md) {
 // *p if ok, else 0, with the load itself unconditional (it reads *safe
 // when !ok): a predicated load becomes a branch around it, and the compiler
 // then waits for the load inside that branch, which serialises a batch of
-// loads that should be in flight together.
-__device__ __forceinline__ float load_if(const float *p, const float *safe, bool ok) {
-  const float v = *(ok ? p : safe);
-  return ok ? v : 0.0f;
-}
-
-// The same as an agent-scope load (parameters, exchanged between workgroups).
+// loads that should be in flight together.  (Agent scope: parameters,
+// exchanged between workgroups.)
 __device__ __forceinline__ float xld_if(const float *p, const float *safe, bool ok) {
   const float v = xld(ok ? p : safe);
   return ok ? v : 0.0f;
@@ -1422,11 +1428,11 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
           for (int fb = 0; fb < 4; ++fb)
             if (fb < NFB)
               xst16(gpr, 4u * (row + (uint32_t)((tile * NFB + fb) * 256 + lane_o * 4)), gacc[hb][fb] * gscale);
-          const float v = sum_rows(gb1[hb]);
+          const float v = sum_rows_of<PREC>(gb1[hb]);
           float w[KO];
 #pragma unroll
           for (int k = 0; k < KO; ++k) {
-            w[k] = sum_rows(gw2[hb][k]);
+            w[k] = sum_rows_of<PREC>(gw2[hb][k]);
           }
           if (lane_o < 16) {
             float *g1 = gpi + go.nw + tile * 16 + lane_o;
@@ -1600,7 +1606,7 @@ __global__ void k_zero_u32(unsigned *p, int n) {
 // Grid-barrier probe: the workgroups of a co-resident grid pass `rounds`
 // grid barriers of the trainer's kind and do nothing else, so a launch's
 // time over its rounds is the latency one barrier adds to a step when every
-// workgroup arrives together (the trainer pays three per step, plus the
+// workgroup arrives together (the trainer pays two per step, plus the
 // wait for its slowest workgroup).
 __global__ __launch_bounds__(kProbeLT) void k_barrier_probe(unsigned *bar, int rounds, uint64_t wait_limit) {
   __shared__ int ok_s;

@@ -2,6 +2,10 @@
 // section 2.2), for callers that drive the steps themselves -- e.g. a
 // torch.autograd.Function whose backward is this hand-written adjoint.
 //
+//  k_forward_rows  n_in <= 64, n_out <= 4: W1 in LDS once per workgroup, rows
+//                  straight from memory to the operands, a wave walking its
+//                  16-row sets; predictions take class and count from the
+//                  outputs in registers
 //  k_forward_tiled 64 rows per workgroup, 16 per wave: the row tile of X and
 //                  a 64-unit block of W1 at a time in LDS, z1 on
 //                  v_mfma_f32_16x16x4_f32, sigma in the accumulator layout,
@@ -18,7 +22,10 @@
 //                  a velocity buffer, heavy-ball momentum (v <- mu v + g,
 //                  theta <- theta - lr v).  Forward and backward take the
 //                  hidden activation (sigma, or the tanh variant).
-//  k_eval_batched  one workgroup per net of a batched item table: loss and
+//  k_eval_tiled    one workgroup per net of a batched item table, z1 on the
+//                  matrix cores; k_cv_means, k_cv_best: the folds' mean losses
+//                  and the best group
+//  k_eval_batched  the same for any n_in, n_out: loss and
 //                  correct count of the net on its own rows (e.g. a held-out
 //                  fold), threads over rows, fixed-order block sums
 //  k_argmax        rows in a grid-stride loop (at most 512 workgroups): the
@@ -151,7 +158,8 @@ __device__ __forceinline__ int argmax_row(const float *v, int K) {
 // Bound: the float32 matrix cores (2 D H of the row's flops) and the vector
 // ALU of the activation about equally; the next rows' X loads overlap.
 // Staging X and W1 per 64 rows with an index division per element held
-// 1,048,576 rows of a 33-256-3 network at 582 us with the separate argmax.
+// 1,048,576 rows of a 33-256-3 network at 582 us with the separate argmax,
+// now 341.
 constexpr int kFwrHB = 256;
 
 struct PredictOut {
