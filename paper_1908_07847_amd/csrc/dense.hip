@@ -5,6 +5,7 @@
 //   k_dense_fwd<ACT>  Y = act(X W^T + b); a workgroup computes 64 rows x 64
 //                     outputs, 16 rows per wave, on v_mfma_f32_16x16x4_f32
 //                     with X and W staged in LDS in chunks of 64 inputs
+//   k_grad_unit       gW and gb of a layer of few rows
 //   adjoint           grad.hpp: dZ = dY . act'(Y) (act' from the layer's
 //                     output) is formed where the gradient sums gW = dZ^T X,
 //                     gb = sum dZ and the optional dX = dZ W consume it; row
@@ -98,6 +99,48 @@ __global__ __launch_bounds__(256) void k_dense_fwd(int64_t n, int din, int dout,
   }
 }
 
+// gW and gb of few rows: a workgroup owns one unit and 64 inputs (a lane each),
+// its 8 waves take 64-row sets in turn, a lane forming delta of one row, and
+// meet in LDS in wave order.  k_grad_sum's 64 x 64 tiles leave such a layer to
+// one workgroup (512 rows of 50 -> 38: 20.0 us a call, here 4.6).
+constexpr int kUnitWaves = 8;
+__global__ __launch_bounds__(64 * kUnitWaves) void k_grad_unit(int64_t n, int din, int dout, int ftiles,
+                                                               const float *__restrict__ X, DenseDelta src,
+                                                               float *__restrict__ gW, float *__restrict__ gb) {
+  __shared__ float part[kUnitWaves][64];
+  __shared__ float partb[kUnitWaves];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int o = blockIdx.x / ftiles, ft = blockIdx.x - o * ftiles, f = ft * 64 + lane;
+  float acc[4] = {0.f, 0.f, 0.f, 0.f}, bsum = 0.0f;
+  for (int64_t r0 = wave * 64; r0 < n; r0 += 64 * kUnitWaves) {
+    const int rows = (int)min((int64_t)64, n - r0);
+    const __amdgpu_buffer_rsrc_t xr = gbuf(X + r0 * din, (uint32_t)(rows * din) * 4u);   // rows past n read zero
+    float x[64];
+#pragma unroll
+    for (int j = 0; j < 64; ++j) x[j] = gld(xr, f < din ? 4u * (uint32_t)(j * din + f) : kNoLoad);
+    const int64_t q = (r0 + min(lane, rows - 1)) * dout + o;
+    float d = src.slope_times(src.Y[q], src.dY[q]);
+    d = lane < rows ? d : 0.0f;
+    bsum += d;
+#pragma unroll
+    for (int j = 0; j < 64; ++j)
+      acc[j & 3] = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), j)), x[j], acc[j & 3]);
+  }
+  part[wave][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  bsum = wave_sum(bsum);
+  if (lane == 0) partb[wave] = bsum;
+  __syncthreads();
+  if (wave != 0) return;
+  float w = 0.0f, b = 0.0f;
+#pragma unroll
+  for (int v = 0; v < kUnitWaves; ++v) {
+    w += part[v][lane];
+    b += partb[v];
+  }
+  if (f < din) gW[(int64_t)o * din + f] = w;
+  if (ft == 0 && lane == 0) gb[o] = b;
+}
+
 __global__ __launch_bounds__(256) void k_update(int64_t P, float *__restrict__ theta, const float *__restrict__ g,
                                                 float *__restrict__ comp, float lr) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -159,10 +202,25 @@ hipError_t launch_dense_forward(int64_t n, int din, int dout, const float *X, co
 }
 
 // ws: n dout floats, for the row ranges' partial gradients ([gW | gb] each).
+// k_grad_unit up to these rows and rows x workgroups: beyond, X read once per
+// unit costs more than k_grad_sum's tiles and the launch that adds its partials
+// (microseconds, here against there: 50 -> 38, 512 rows 4.6 / 20.0, 1195 7.0 /
+// 14.0, 2048 10.0 / 11.3, 3000 13.8 / 14.8, 4096 17.6 / 10.7; 64 -> 256, 1195
+// rows 8.0 / 13.9, 2048 15.7 / 11.4; 64 -> 512, 800 rows 9.3 / 13.9, 1195
+// 15.2 / 14.1).
+constexpr int64_t kUnitRows = 2048, kUnitWork = 400000;
 hipError_t launch_dense_backward(int64_t n, int din, int dout, const float *X, const float *Y, const float *dY,
                                  const float *W, int act, float *gW, float *gb, float *dX, float *ws,
                                  hipStream_t s) {
   const mlpk::DenseDelta src{Y, dY, act};
+  const int64_t ft = ((int64_t)din + 63) / 64, groups = dout * ft;
+  if (n <= kUnitRows && n * groups <= kUnitWork) {
+    hipLaunchKernelGGL(mlpk::k_grad_unit, dim3((unsigned)groups), dim3(64 * mlpk::kUnitWaves), 0, s, n, din, dout,
+                       (int)ft, X, src, gW, gb);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !dX) return e;
+    return launch_grad_dx(n, din, dout, W, src, dX, s);
+  }
   const int64_t nW = (int64_t)dout * din, Q = nW + dout;
   const mlpk::GradDst dst{{gW, gb, nullptr, nullptr, nullptr}, {nW, Q, Q, Q, Q}, 1.0f};
   hipError_t e = launch_grad_sum(n, din, dout, X, src, gW, gb, ws, n * dout, Q, dst, s);

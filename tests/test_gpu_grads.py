@@ -104,3 +104,10 @@ def test_dense_backward_edges(M, n, din, dout, act):
     within("gW", gW, dZ.T @ X, mag.T @ np.abs(X), n + 6)
     within("gb", gb, dZ.sum(0), mag.sum(0), n + 6)
     within("dX", dX, dZ @ W, mag @ np.abs(W), dout + 6)
+
+
+@pytest.mark.parametrize("n,din,dout,act", [(63, 64, 1, 0), (511, 65, 7, 1), (512, 48, 37, 0), (513, 129, 33, 1),
+                                            (2048, 64, 195, 0), (2048, 63, 196, 1), (1562, 64, 256, 1),
+                                            (1563, 64, 256, 0), (2049, 20, 3, 0)])
+def test_dense_backward_few_rows(M, n, din, dout, act):   # both sides of the few-rows rule
+    test_dense_backward_edges(M, n, din, dout, act)
