@@ -330,7 +330,12 @@ mlp_status mlp_dense_forward(const float *X, int64_t n, int32_t d_in, int32_t d_
  * own output Y:  dZ = dY . act'(Y),  gW = dZ^T X,  gb = sum over rows of dZ,
  * dX = dZ W (dX may be NULL).  gW [d_out][d_in], gb [d_out] are
  * overwritten; row sums run in a fixed order (bitwise repeatable).
- * workspace: >= n * d_out * 4 bytes (dZ), 4-byte aligned. */
+ * workspace: >= n * d_out * 4 bytes, 4-byte aligned (partial sums of row
+ * ranges, or dZ); its contents afterwards are unspecified.  dX may lie over X,
+ * Y or dY, and gW, gb or the workspace over Y or dY (the workspace entry for
+ * entry, starting where Y or dY starts): dZ is then written to the workspace
+ * before anything else.  Other overlaps of outputs, inputs and workspace are
+ * not allowed. */
 mlp_status mlp_dense_backward(const float *X, const float *Y, const float *dY, int64_t n, int32_t d_in,
                               int32_t d_out, const float *W, int32_t act, float *gW, float *gb, float *dX,
                               void *workspace, size_t ws_bytes, void *stream);

@@ -10,6 +10,7 @@
 //                     output) is formed where the gradient sums gW = dZ^T X,
 //                     gb = sum dZ and the optional dX = dZ W consume it; row
 //                     sums run in a fixed order (bitwise repeatable)
+//   k_dense_dz        dZ into the workspace first, where an output lies over Y or dY
 //   k_update          theta <- theta - lr g over a packed parameter vector,
 //                     optionally Kahan-compensated
 //   k_mse_grad        the error of section 2.2 read as the mean squared error,
@@ -104,8 +105,9 @@ __global__ __launch_bounds__(256) void k_dense_fwd(int64_t n, int din, int dout,
 // meet in LDS in wave order.  k_grad_sum's 64 x 64 tiles leave such a layer to
 // one workgroup (512 rows of 50 -> 38: 20.0 us a call, here 4.6).
 constexpr int kUnitWaves = 8;
+template <class Src>
 __global__ __launch_bounds__(64 * kUnitWaves) void k_grad_unit(int64_t n, int din, int dout, int ftiles,
-                                                               const float *__restrict__ X, DenseDelta src,
+                                                               const float *__restrict__ X, Src src,
                                                                float *__restrict__ gW, float *__restrict__ gb) {
   __shared__ float part[kUnitWaves][64];
   __shared__ float partb[kUnitWaves];
@@ -139,6 +141,12 @@ __global__ __launch_bounds__(64 * kUnitWaves) void k_grad_unit(int64_t n, int di
   }
   if (f < din) gW[(int64_t)o * din + f] = w;
   if (ft == 0 && lane == 0) gb[o] = b;
+}
+
+// dZ = dY . act'(Y), entry by entry, so dZ may be Y's or dY's own memory.
+__global__ __launch_bounds__(256) void k_dense_dz(int64_t m, DenseDelta<false> src, float *dZ) {
+  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q < m) dZ[q] = src.slope_times(src.Y[q], src.dY[q]);
 }
 
 __global__ __launch_bounds__(256) void k_update(int64_t P, float *__restrict__ theta, const float *__restrict__ g,
@@ -209,23 +217,47 @@ hipError_t launch_dense_forward(int64_t n, int din, int dout, const float *X, co
 // rows 8.0 / 13.9, 2048 15.7 / 11.4; 64 -> 512, 800 rows 9.3 / 13.9, 1195
 // 15.2 / 14.1).
 constexpr int64_t kUnitRows = 2048, kUnitWork = 400000;
+template <bool GIVEN>
+static hipError_t dense_backward(int64_t n, int din, int dout, const float *X, const mlpk::DenseDelta<GIVEN> &src,
+                                 const float *W, float *gW, float *gb, float *dX, float *ws, int64_t ws_floats,
+                                 hipStream_t s) {
+  const int64_t ft = ((int64_t)din + 63) / 64, groups = dout * ft;
+  hipError_t e;
+  if (n <= kUnitRows && n * groups <= kUnitWork) {
+    hipLaunchKernelGGL(mlpk::k_grad_unit<mlpk::DenseDelta<GIVEN>>, dim3((unsigned)groups),
+                       dim3(64 * mlpk::kUnitWaves), 0, s, n, din, dout, (int)ft, X, src, gW, gb);
+    e = hipGetLastError();
+  } else {
+    const int64_t nW = (int64_t)dout * din, Q = nW + dout;
+    const mlpk::GradDst dst{{gW, gb, nullptr, nullptr, nullptr}, {nW, Q, Q, Q, Q}, 1.0f};
+    e = launch_grad_sum(n, din, dout, X, src, gW, gb, ws, ws_floats, Q, dst, s);
+  }
+  if (e != hipSuccess || !dX) return e;
+  return launch_grad_dx(n, din, dout, W, src, dX, s);
+}
+
+static bool overlap(const float *a, int64_t na, const float *b, int64_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + sizeof(float) * (uintptr_t)nb && y < x + sizeof(float) * (uintptr_t)na;
+}
+
+// An output (or the workspace) over Y or dY: the kernels read both to the end,
+// in every workgroup, so dZ goes to the workspace first and they read that
+// (the partial gradients then have no room: one range of rows).
 hipError_t launch_dense_backward(int64_t n, int din, int dout, const float *X, const float *Y, const float *dY,
                                  const float *W, int act, float *gW, float *gb, float *dX, float *ws,
                                  hipStream_t s) {
-  const mlpk::DenseDelta src{Y, dY, act};
-  const int64_t ft = ((int64_t)din + 63) / 64, groups = dout * ft;
-  if (n <= kUnitRows && n * groups <= kUnitWork) {
-    hipLaunchKernelGGL(mlpk::k_grad_unit, dim3((unsigned)groups), dim3(64 * mlpk::kUnitWaves), 0, s, n, din, dout,
-                       (int)ft, X, src, gW, gb);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !dX) return e;
-    return launch_grad_dx(n, din, dout, W, src, dX, s);
-  }
-  const int64_t nW = (int64_t)dout * din, Q = nW + dout;
-  const mlpk::GradDst dst{{gW, gb, nullptr, nullptr, nullptr}, {nW, Q, Q, Q, Q}, 1.0f};
-  hipError_t e = launch_grad_sum(n, din, dout, X, src, gW, gb, ws, n * dout, Q, dst, s);
-  if (e != hipSuccess || !dX) return e;
-  return launch_grad_dx(n, din, dout, W, src, dX, s);
+  const int64_t m = n * dout;
+  const mlpk::DenseDelta<false> src{Y, dY, act};
+  const struct { const float *p; int64_t n; } outs[] = {{dX, n * din}, {gW, (int64_t)dout * din}, {gb, dout}, {ws, m}};
+  for (const auto &o : outs)
+    if (overlap(o.p, o.n, Y, m) || overlap(o.p, o.n, dY, m)) {
+      hipLaunchKernelGGL(mlpk::k_dense_dz, blocks_for(m, 256), dim3(256), 0, s, m, src, ws);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      return dense_backward(n, din, dout, X, mlpk::DenseDelta<true>{ws, ws, act}, W, gW, gb, dX, ws, 0, s);
+    }
+  return dense_backward(n, din, dout, X, src, W, gW, gb, dX, ws, m, s);
 }
 
 hipError_t launch_mse_grad(int64_t n, int k, const float *Y, const float *T, float *dY, float *loss, hipStream_t s) {

@@ -43,12 +43,15 @@ struct GradOut {
   float *gW, *gb;
 };
 
-// delta of a dense layer: dY . act'(Y)
+// delta of a dense layer: dY . act'(Y), or (GIVEN) the delta itself in both
+// arrays, for calls whose outputs lie over Y or dY.
+template <bool GIVEN>
 struct DenseDelta {
   static constexpr int KO = 0;   // no output layer above: nothing beside gW, gb
   const float *Y, *dY;
   int act;
   __device__ __forceinline__ float slope_times(float y, float s) const {
+    if (GIVEN) return s;
     return act == 1 ? s * (1.0f - y * y) : s * (y * (1.0f - y));
   }
 };
