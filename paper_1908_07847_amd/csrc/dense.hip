@@ -102,7 +102,8 @@ __global__ __launch_bounds__(256) void k_dense_fwd(int64_t n, int din, int dout,
 
 // gW and gb of few rows: a workgroup owns one unit and 64 inputs (a lane each),
 // its 8 waves take 64-row sets in turn, a lane forming delta of one row, and
-// meet in LDS in wave order.  k_grad_sum's 64 x 64 tiles leave such a layer to
+// meet in LDS in pairs.  (Eight chains per wave: a sum of n rows is n / 64
+// steps deep and 6 to meet, as with a wave of lanes over the rows.)  k_grad_sum's 64 x 64 tiles leave such a layer to
 // one workgroup (512 rows of 50 -> 38: 20.0 us a call, here 4.6).
 constexpr int kUnitWaves = 8;
 template <class Src>
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(64 * kUnitWaves) void k_grad_unit(int64_t n, int di
   __shared__ float partb[kUnitWaves];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int o = blockIdx.x / ftiles, ft = blockIdx.x - o * ftiles, f = ft * 64 + lane;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f}, bsum = 0.0f;
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, bsum = 0.0f;
   for (int64_t r0 = wave * 64; r0 < n; r0 += 64 * kUnitWaves) {
     const int rows = (int)min((int64_t)64, n - r0);
     const __amdgpu_buffer_rsrc_t xr = gbuf(X + r0 * din, (uint32_t)(rows * din) * 4u);   // rows past n read zero
@@ -126,21 +127,28 @@ __global__ __launch_bounds__(64 * kUnitWaves) void k_grad_unit(int64_t n, int di
     bsum += d;
 #pragma unroll
     for (int j = 0; j < 64; ++j)
-      acc[j & 3] = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), j)), x[j], acc[j & 3]);
+      acc[j & 7] = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), j)), x[j], acc[j & 7]);
   }
-  part[wave][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  part[wave][lane] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
   bsum = wave_sum(bsum);
   if (lane == 0) partb[wave] = bsum;
   __syncthreads();
   if (wave != 0) return;
-  float w = 0.0f, b = 0.0f;
+  float w[kUnitWaves], b[kUnitWaves];
 #pragma unroll
   for (int v = 0; v < kUnitWaves; ++v) {
-    w += part[v][lane];
-    b += partb[v];
+    w[v] = part[v][lane];
+    b[v] = partb[v];
   }
-  if (f < din) gW[(int64_t)o * din + f] = w;
-  if (ft == 0 && lane == 0) gb[o] = b;
+#pragma unroll
+  for (int st = 1; st < kUnitWaves; st *= 2)
+#pragma unroll
+    for (int v = 0; v < kUnitWaves; v += 2 * st) {
+      w[v] += w[v + st];
+      b[v] += b[v + st];
+    }
+  if (f < din) gW[(int64_t)o * din + f] = w[0];
+  if (ft == 0 && lane == 0) gb[o] = b[0];
 }
 
 // dZ = dY . act'(Y), entry by entry, so dZ may be Y's or dY's own memory.

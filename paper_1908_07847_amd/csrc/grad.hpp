@@ -34,6 +34,16 @@ typedef float f32x4_g __attribute__((ext_vector_type(4)));
 constexpr int kGT = 64;    // units and inputs per tile
 constexpr int kGSet = 32;  // rows of a wave's set
 constexpr int kGWaves = 4;
+// Depth of the float32 sums.  A chain of matrix-core products errs like one
+// rounding per row, so a wave starts every 16 rows from zero and adds the
+// result to its totals, and a range adds the totals of every kGFold rows in
+// memory: n rows of one range are 16 + min(n, kGFold) / 64 + n / kGFold steps
+// deep, however few ranges the tiles and the workspace leave.  One chain per
+// range is n / 4 deep: 262,144 rows of 33-64-3 in one range, equal terms, gW1
+// off by 7.6e-4 of itself, so 3.1e-6; 512 rows of random terms 2.7e-7 and
+// 1.3e-7; 40,000 rows of 1024 -> 2048 3.1e-6 and 3.5e-7.  It costs 6 % where the
+// products bound (30,000 rows of 33-256-3 27.3 -> 28.9 us).
+constexpr int kGFold = 16384;
 
 // Where a parameter's gradient goes: packed [W | b | extra] order as partial
 // s of `part` (stride Q), or the final arrays when one range covers all rows.
@@ -86,8 +96,8 @@ struct HiddenDelta {
   }
 };
 
-template <class Src>
-__global__ __launch_bounds__(64 * kGWaves) void k_grad_sum(int64_t n, int din, int dout, int64_t per, int ftiles,
+template <class Src>   // (two workgroups per CU, as grad_ranges counts, where no register spills for it)
+__global__ __launch_bounds__(64 * kGWaves, Src::KO > 4 ? 1 : 2) void k_grad_sum(int64_t n, int din, int dout, int64_t per, int ftiles,
                                                            const float *__restrict__ X, Src src, GradOut out) {
   constexpr int KO = Src::KO, KR = KO > 0 ? KO : 1;
   __shared__ float buf[2][kGT][kGT + 1];
@@ -120,153 +130,175 @@ __global__ __launch_bounds__(64 * kGWaves) void k_grad_sum(int64_t n, int din, i
 #pragma unroll
       for (int k = 0; k < KO; ++k) w2[t][k] = k < src.K ? src.W2[(int64_t)k * dout + oc[t]] : 0.0f;
   }
-  f32x4_g acc[4][4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) acc[t][u] = f32x4_g{0.f, 0.f, 0.f, 0.f};
-  float gb[4] = {0.f, 0.f, 0.f, 0.f}, gw2[4][KR], gb2[KR], sq = 0.0f;
-#pragma unroll
-  for (int k = 0; k < KR; ++k) {
-    gb2[k] = 0.0f;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) gw2[t][k] = 0.0f;
-  }
-
-  for (int64_t base = r_begin + wave * kGSet; base < r_end; base += kGWaves * kGSet) {
-    const int rows = (int)min((int64_t)kGSet, r_end - base);
-    const float *xb = X + base * din;
-    if constexpr (KO > 0) {
-      // output deltas of the set's rows: lane = row (the upper half idles)
-      if (lane < kGSet) {
-#pragma unroll
-        for (int k = 0; k < KO; ++k) {
-          float d = 0.0f;
-          if (lane < rows && k < src.K) d = src.d2(base + lane, k, sq);
-          gb2[k] += d;
-          d2s[wave][lane][k] = d;
-        }
-      }
-    }
-    for (int h = 0; h < kGSet; h += 16) {   // 16 rows: their loads are issued together
-      if (h >= rows) break;
-      float xv[4][4], ov[4][4], uv[4][4];
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int row = h + 4 * s + lg, rc = row < rows ? row : 0;
-        const uint32_t xo = (uint32_t)(rc * din), oo_ = (uint32_t)(rc * dout);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          xv[s][t] = xb[xo + (uint32_t)fc[t]];
-          if constexpr (KO > 0) {
-            ov[s][t] = (src.A + base * dout)[oo_ + (uint32_t)oc[t]];
-          } else {
-            ov[s][t] = (src.Y + base * dout)[oo_ + (uint32_t)oc[t]];
-            uv[s][t] = (src.dY + base * dout)[oo_ + (uint32_t)oc[t]];
-          }
-        }
-      }
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int row = h + 4 * s + lg;
-        const bool ron = row < rows;
-        float dd[KR];
-        if constexpr (KO > 0) {
-#pragma unroll
-          for (int k = 0; k < KO; ++k) dd[k] = d2s[wave][row][k];
-        }
-        float xm[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) xm[u] = ron && fo[u] ? xv[s][u] : 0.0f;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          float d;
-          if constexpr (KO > 0) {
-            const float a = ron && oo[t] ? ov[s][t] : 0.0f;
-            float bp = 0.0f;
-#pragma unroll
-            for (int k = 0; k < KO; ++k) {
-              bp = fmaf(dd[k], w2[t][k], bp);
-              gw2[t][k] = fmaf(dd[k], a, gw2[t][k]);
-            }
-            d = src.slope_times(a, bp);
-          } else {
-            d = src.slope_times(ov[s][t], uv[s][t]);
-          }
-          d = ron && oo[t] ? d : 0.0f;
-          gb[t] += d;
-#pragma unroll
-          for (int u = 0; u < 4; ++u) acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(d, xm[u], acc[t][u], 0, 0, 0);
-        }
-      }
-    }
-  }
-
-  // ---- the four waves meet in a fixed order: (w0 + w2) + (w1 + w3).  Lane
-  // (input l16, group lg) holds units 4 lg .. 4 lg + 3 of each 16 x 16 tile.
-  auto put = [&](int b, bool add) {
+  for (int64_t fold = r_begin; fold < r_end; fold += kGFold) {
+    const int64_t f_end = min(r_end, fold + kGFold);
+    if (fold > r_begin) __syncthreads();   // the previous fold's LDS is no longer read
+    f32x4_g acc[4][4];
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < 4; ++u) acc[t][u] = f32x4_g{0.f, 0.f, 0.f, 0.f};
+    float gb[4] = {0.f, 0.f, 0.f, 0.f}, gw2[4][KR], gb2[KR], sq = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float *p = &buf[b][16 * t + 4 * lg + i][16 * u + l16];
-          *p = add ? acc[t][u][i] + *p : acc[t][u][i];
-        }
-  };
-  if (wave >= 2) put(wave - 2, false);
-  if (first_f) {
+    for (int k = 0; k < KR; ++k) {
+      gb2[k] = 0.0f;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const float v = sum_rows(gb[t]);
-      if (lg == 0) small[wave][16 * t + l16][0] = v;
+      for (int t = 0; t < 4; ++t) gw2[t][k] = 0.0f;
+    }
+
+    for (int64_t base = fold + wave * kGSet; base < f_end; base += kGWaves * kGSet) {
+      const int rows = (int)min((int64_t)kGSet, f_end - base);
+      const float *xb = X + base * din;
       if constexpr (KO > 0) {
+        // output deltas of the set's rows: lane = row (the upper half idles)
+        if (lane < kGSet) {
 #pragma unroll
-        for (int k = 0; k < KO; ++k) {
-          const float g = sum_rows(gw2[t][k]);
-          if (lg == 0) small[wave][16 * t + l16][1 + k] = g;
+          for (int k = 0; k < KO; ++k) {
+            float d = 0.0f;
+            if (lane < rows && k < src.K) d = src.d2(base + lane, k, sq);
+            gb2[k] += d;
+            d2s[wave][lane][k] = d;
+          }
+        }
+      }
+      for (int h = 0; h < kGSet; h += 16) {   // 16 rows: their loads are issued together
+        if (h >= rows) break;
+        float xv[4][4], ov[4][4], uv[4][4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int row = h + 4 * s + lg, rc = row < rows ? row : 0;
+          const uint32_t xo = (uint32_t)(rc * din), oo_ = (uint32_t)(rc * dout);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            xv[s][t] = xb[xo + (uint32_t)fc[t]];
+            if constexpr (KO > 0) {
+              ov[s][t] = (src.A + base * dout)[oo_ + (uint32_t)oc[t]];
+            } else {
+              ov[s][t] = (src.Y + base * dout)[oo_ + (uint32_t)oc[t]];
+              uv[s][t] = (src.dY + base * dout)[oo_ + (uint32_t)oc[t]];
+            }
+          }
+        }
+        float xm[4][4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) xm[s][u] = h + 4 * s + lg < rows && fo[u] ? xv[s][u] : 0.0f;
+        float dk[4][KR];
+        if constexpr (KO > 0) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int k = 0; k < KO; ++k) dk[s][k] = d2s[wave][h + 4 * s + lg][k];
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {   // the 16 rows from zero, then onto the totals
+          f32x4_g part[4];
+          float gbh = 0.0f, gw2h[KR];
+#pragma unroll
+          for (int k = 0; k < KR; ++k) gw2h[k] = 0.0f;
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int row = h + 4 * s + lg;
+            const bool on = row < rows && oo[t];
+            float d;
+            if constexpr (KO > 0) {
+              const float a = on ? ov[s][t] : 0.0f;
+              float bp = 0.0f;
+#pragma unroll
+              for (int k = 0; k < KO; ++k) {
+                bp = fmaf(dk[s][k], w2[t][k], bp);
+                gw2h[k] = fmaf(dk[s][k], a, gw2h[k]);
+              }
+              d = src.slope_times(a, bp);
+            } else {
+              d = src.slope_times(ov[s][t], uv[s][t]);
+            }
+            d = on ? d : 0.0f;
+            gbh += d;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              part[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(d, xm[s][u], s ? part[u] : f32x4_g{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+          }
+          gb[t] += gbh;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc[t][u] += part[u];
+          if constexpr (KO > 0) {
+#pragma unroll
+            for (int k = 0; k < KO; ++k) gw2[t][k] += gw2h[k];
+          }
         }
       }
     }
-    if constexpr (KO > 0) {
-      if (first) {
+
+    // ---- the four waves meet in a fixed order: (w0 + w2) + (w1 + w3), and add
+    // what this thread wrote for the range's earlier folds.  Lane
+    // (input l16, group lg) holds units 4 lg .. 4 lg + 3 of each 16 x 16 tile.
+    auto put = [&](int b, bool add) {
 #pragma unroll
-        for (int k = 0; k < KO; ++k) {
-          const float v = wave_sum(gb2[k]);
-          if (lane == 0) tail[wave][k] = v;
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float *p = &buf[b][16 * t + 4 * lg + i][16 * u + l16];
+            *p = add ? acc[t][u][i] + *p : acc[t][u][i];
+          }
+    };
+    if (wave >= 2) put(wave - 2, false);
+    if (first_f) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const float v = sum_rows(gb[t]);
+        if (lg == 0) small[wave][16 * t + l16][0] = v;
+        if constexpr (KO > 0) {
+#pragma unroll
+          for (int k = 0; k < KO; ++k) {
+            const float g = sum_rows(gw2[t][k]);
+            if (lg == 0) small[wave][16 * t + l16][1 + k] = g;
+          }
         }
-        sq = wave_sum(sq);
-        if (lane == 0) tail[wave][KO] = sq;
+      }
+      if constexpr (KO > 0) {
+        if (first) {
+#pragma unroll
+          for (int k = 0; k < KO; ++k) {
+            const float v = wave_sum(gb2[k]);
+            if (lane == 0) tail[wave][k] = v;
+          }
+          sq = wave_sum(sq);
+          if (lane == 0) tail[wave][KO] = sq;
+        }
       }
     }
-  }
-  __syncthreads();
-  if (wave < 2) put(wave, true);
-  __syncthreads();
-  float *pw = out.part ? out.part + (int64_t)blockIdx.y * out.Q : nullptr;
-  float *gW = pw ? pw : out.gW;
-  for (int q = tid; q < kGT * kGT; q += 64 * kGWaves) {
-    const int o = q / kGT, f = q % kGT;
-    if (o0 + o < dout && f0 + f < din) gW[(int64_t)(o0 + o) * din + f0 + f] = buf[0][o][f] + buf[1][o][f];
-  }
-  if (first_f) {
-    auto waves4 = [&](int o, int c) { return (small[0][o][c] + small[2][o][c]) + (small[1][o][c] + small[3][o][c]); };
-    const int64_t oB = (int64_t)dout * din;
-    if (tid < kGT && o0 + tid < dout) (pw ? pw + oB : out.gb)[o0 + tid] = waves4(tid, 0);
-    if constexpr (KO > 0) {
-      float *g2 = pw ? pw + oB + dout : src.gW2;
-      for (int q = tid; q < kGT * src.K; q += 64 * kGWaves) {
-        const int k = q / kGT, o = q % kGT;
-        if (o0 + o < dout) g2[(int64_t)k * dout + o0 + o] = waves4(o, 1 + k);
-      }
-      if (first && tid <= KO) {
-        const float v = (tail[0][tid] + tail[2][tid]) + (tail[1][tid] + tail[3][tid]);
-        const int64_t oT = oB + dout + (int64_t)src.K * dout;
-        if (tid < src.K) (pw ? pw + oT : src.gb2)[tid] = v;
-        if (tid == KO) {
-          if (pw) pw[oT + src.K] = v;
-          else if (src.loss) src.loss[0] = v * src.loss_scale;
+    __syncthreads();
+    if (wave < 2) put(wave, true);
+    __syncthreads();
+    auto store = [&](float *p, float v) { *p = fold == r_begin ? v : *p + v; };
+    float *pw = out.part ? out.part + (int64_t)blockIdx.y * out.Q : nullptr;
+    float *gW = pw ? pw : out.gW;
+    for (int q = tid; q < kGT * kGT; q += 64 * kGWaves) {
+      const int o = q / kGT, f = q % kGT;
+      if (o0 + o < dout && f0 + f < din) store(gW + (int64_t)(o0 + o) * din + f0 + f, buf[0][o][f] + buf[1][o][f]);
+    }
+    if (first_f) {
+      auto waves4 = [&](int o, int c) { return (small[0][o][c] + small[2][o][c]) + (small[1][o][c] + small[3][o][c]); };
+      const int64_t oB = (int64_t)dout * din;
+      if (tid < kGT && o0 + tid < dout) store((pw ? pw + oB : out.gb) + o0 + tid, waves4(tid, 0));
+      if constexpr (KO > 0) {
+        float *g2 = pw ? pw + oB + dout : src.gW2;
+        for (int q = tid; q < kGT * src.K; q += 64 * kGWaves) {
+          const int k = q / kGT, o = q % kGT;
+          if (o0 + o < dout) store(g2 + (int64_t)k * dout + o0 + o, waves4(o, 1 + k));
+        }
+        if (first && tid <= KO) {
+          const float v = (tail[0][tid] + tail[2][tid]) + (tail[1][tid] + tail[3][tid]);
+          const int64_t oT = oB + dout + (int64_t)src.K * dout;
+          if (tid < src.K) store((pw ? pw + oT : src.gb2) + tid, v);
+          if (tid == KO) {
+            if (pw) store(pw + oT + src.K, v);
+            else if (src.loss) store(src.loss, v * src.loss_scale);
+          }
         }
       }
     }
