@@ -227,7 +227,7 @@ __global__ __launch_bounds__(mlph::kDeepThreads) void k_deep_train(
 // Bound: one workgroup's chain of dependent products, LDS reads and
 // activations.  The lane-per-entry form above reads both operands of every
 // product from LDS one float at a time and passes eight barriers per epoch of
-// a three-layer network: 11.6 us for 33-16-16-3 on 120 rows, here 3.7.
+// a three-layer network: 11.6 us for 33-16-16-3 on 120 rows, here 3.9.
 using mlph::DeepTilePlan;
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
@@ -383,8 +383,11 @@ __global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
       const int sa = l ? SH : SX, sd = l == LC - 1 ? ST : SH, wi = p.w[l], wo = p.w[l + 1];
       const float *Dp = sm + p.doff[l] + lg * sd + 16 * ot + l16;
       const float *Ap = sm + p.aoff[l] + lg * sa + 16 * it + l16;
-      // two accumulators, so the chains overlap; a row tile past the end is
-      // not read (NPT odd)
+      // row tiles in pairs whose chains overlap, each from zero and added to
+      // the totals: chains over all rows err like a rounding per row (120 rows
+      // of 33-16-16-3, rms error of a step's gradients 10.0e-9 of the largest,
+      // so 6.8e-9, for 3.95 us an epoch instead of 3.73); a row tile past the
+      // end is not read (NPT odd)
       f32x4_t g0 = {0.f, 0.f, 0.f, 0.f}, g1 = {0.f, 0.f, 0.f, 0.f};
       float gb = 0.0f;
       int rt = 0;
@@ -395,20 +398,25 @@ __global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
           dv[s] = Dp[(16 * rt + 4 * s) * sd];
           av[s] = Ap[(16 * rt + 4 * s) * sa];
         }
+        f32x4_t p0 = {0.f, 0.f, 0.f, 0.f}, p1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          g0 = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[s], av[s], g0, 0, 0, 0);
-          g1 = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[4 + s], av[4 + s], g1, 0, 0, 0);
+          p0 = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[s], av[s], p0, 0, 0, 0);
+          p1 = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[4 + s], av[4 + s], p1, 0, 0, 0);
           gb += dv[s] + dv[4 + s];
         }
+        g0 += p0;
+        g1 += p1;
       }
       if (rt < NPT) {
+        f32x4_t p0 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
           const float dv = Dp[(16 * rt + 4 * s) * sd];
-          g0 = __builtin_amdgcn_mfma_f32_16x16x4f32(dv, Ap[(16 * rt + 4 * s) * sa], g0, 0, 0, 0);
+          p0 = __builtin_amdgcn_mfma_f32_16x16x4f32(dv, Ap[(16 * rt + 4 * s) * sa], p0, 0, 0, 0);
           gb += dv;
         }
+        g0 += p0;
       }
       const int i0 = 16 * it + l16;
       float *Wt = sm + p.woff[l] + (16 * ot + 4 * lg) * sa + i0;
