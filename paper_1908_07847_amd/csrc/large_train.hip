@@ -1895,11 +1895,11 @@ mlp_status large_workspace_bytes(const mlp_config &c, int n_nets, size_t *bytes)
   if (n_nets < 1 || n_nets > mlpk::kMaxNets) return MLP_ERR_UNSUPPORTED;
   const int64_t b = batch_of(c);
   if (b % 32 != 0) return MLP_ERR_UNSUPPORTED;
-  // Size for the largest grid any plan may use.
+  // Size for the largest grid any plan may use (under a hint: any two counts;
+  // the layout grows with the row blocks).
   size_t best = 0;
   if (n_nets == 1) {
-    for (int gj = 1; gj <= kMaxHiddenBlocks; gj *= 2)
-      for (int gi = 1; gi * gj <= kMaxGrid; gi *= 2) best = std::max(best, ws_layout(c, 1, gi, gj).total);
+    for (int gj = 1; gj <= kMaxHiddenBlocks; ++gj) best = std::max(best, ws_layout(c, 1, kMaxGrid / gj, gj).total);
   } else {
     const int gj = min_hidden_blocks(c.n_hidden);
     for (int gi = 1; gi <= max_row_blocks(n_nets, gj); gi *= 2)
