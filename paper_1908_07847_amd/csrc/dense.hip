@@ -5,7 +5,6 @@
 //   k_dense_fwd<ACT>  Y = act(X W^T + b); a workgroup computes 64 rows x 64
 //                     outputs, 16 rows per wave, on v_mfma_f32_16x16x4_f32
 //                     with X and W staged in LDS in chunks of 64 inputs
-//   k_grad_unit       gW and gb of a layer of few rows
 //   adjoint           grad.hpp: dZ = dY . act'(Y) (act' from the layer's
 //                     output) is formed where the gradient sums gW = dZ^T X,
 //                     gb = sum dZ and the optional dX = dZ W consume it; row
@@ -100,57 +99,6 @@ __global__ __launch_bounds__(256) void k_dense_fwd(int64_t n, int din, int dout,
   }
 }
 
-// gW and gb of few rows: a workgroup owns one unit and 64 inputs (a lane each),
-// its 8 waves take 64-row sets in turn, a lane forming delta of one row, and
-// meet in LDS in pairs.  (Eight chains per wave: a sum of n rows is n / 64
-// steps deep and 6 to meet, as with a wave of lanes over the rows.)  k_grad_sum's 64 x 64 tiles leave such a layer to
-// one workgroup (512 rows of 50 -> 38: 20.0 us a call, here 4.6).
-constexpr int kUnitWaves = 8;
-template <class Src>
-__global__ __launch_bounds__(64 * kUnitWaves) void k_grad_unit(int64_t n, int din, int dout, int ftiles,
-                                                               const float *__restrict__ X, Src src,
-                                                               float *__restrict__ gW, float *__restrict__ gb) {
-  __shared__ float part[kUnitWaves][64];
-  __shared__ float partb[kUnitWaves];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int o = blockIdx.x / ftiles, ft = blockIdx.x - o * ftiles, f = ft * 64 + lane;
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, bsum = 0.0f;
-  for (int64_t r0 = wave * 64; r0 < n; r0 += 64 * kUnitWaves) {
-    const int rows = (int)min((int64_t)64, n - r0);
-    const __amdgpu_buffer_rsrc_t xr = gbuf(X + r0 * din, (uint32_t)(rows * din) * 4u);   // rows past n read zero
-    float x[64];
-#pragma unroll
-    for (int j = 0; j < 64; ++j) x[j] = gld(xr, f < din ? 4u * (uint32_t)(j * din + f) : kNoLoad);
-    const int64_t q = (r0 + min(lane, rows - 1)) * dout + o;
-    float d = src.slope_times(src.Y[q], src.dY[q]);
-    d = lane < rows ? d : 0.0f;
-    bsum += d;
-#pragma unroll
-    for (int j = 0; j < 64; ++j)
-      acc[j & 7] = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), j)), x[j], acc[j & 7]);
-  }
-  part[wave][lane] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-  bsum = wave_sum(bsum);
-  if (lane == 0) partb[wave] = bsum;
-  __syncthreads();
-  if (wave != 0) return;
-  float w[kUnitWaves], b[kUnitWaves];
-#pragma unroll
-  for (int v = 0; v < kUnitWaves; ++v) {
-    w[v] = part[v][lane];
-    b[v] = partb[v];
-  }
-#pragma unroll
-  for (int st = 1; st < kUnitWaves; st *= 2)
-#pragma unroll
-    for (int v = 0; v < kUnitWaves; v += 2 * st) {
-      w[v] += w[v + st];
-      b[v] += b[v + st];
-    }
-  if (f < din) gW[(int64_t)o * din + f] = w[0];
-  if (ft == 0 && lane == 0) gb[o] = b[0];
-}
-
 // dZ = dY . act'(Y), entry by entry, so dZ may be Y's or dY's own memory.
 __global__ __launch_bounds__(256) void k_dense_dz(int64_t m, DenseDelta<false> src, float *dZ) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -218,28 +166,13 @@ hipError_t launch_dense_forward(int64_t n, int din, int dout, const float *X, co
 }
 
 // ws: n dout floats, for the row ranges' partial gradients ([gW | gb] each).
-// k_grad_unit up to these rows and rows x workgroups: beyond, X read once per
-// unit costs more than k_grad_sum's tiles and the launch that adds its partials
-// (microseconds, here against there: 50 -> 38, 512 rows 4.6 / 20.0, 1195 7.0 /
-// 14.0, 2048 10.0 / 11.3, 3000 13.8 / 14.8, 4096 17.6 / 10.7; 64 -> 256, 1195
-// rows 8.0 / 13.9, 2048 15.7 / 11.4; 64 -> 512, 800 rows 9.3 / 13.9, 1195
-// 15.2 / 14.1).
-constexpr int64_t kUnitRows = 2048, kUnitWork = 400000;
 template <bool GIVEN>
 static hipError_t dense_backward(int64_t n, int din, int dout, const float *X, const mlpk::DenseDelta<GIVEN> &src,
                                  const float *W, float *gW, float *gb, float *dX, float *ws, int64_t ws_floats,
                                  hipStream_t s) {
-  const int64_t ft = ((int64_t)din + 63) / 64, groups = dout * ft;
-  hipError_t e;
-  if (n <= kUnitRows && n * groups <= kUnitWork) {
-    hipLaunchKernelGGL(mlpk::k_grad_unit<mlpk::DenseDelta<GIVEN>>, dim3((unsigned)groups),
-                       dim3(64 * mlpk::kUnitWaves), 0, s, n, din, dout, (int)ft, X, src, gW, gb);
-    e = hipGetLastError();
-  } else {
-    const int64_t nW = (int64_t)dout * din, Q = nW + dout;
-    const mlpk::GradDst dst{{gW, gb, nullptr, nullptr, nullptr}, {nW, Q, Q, Q, Q}, 1.0f};
-    e = launch_grad_sum(n, din, dout, X, src, gW, gb, ws, ws_floats, Q, dst, s);
-  }
+  const int64_t nW = (int64_t)dout * din, Q = nW + dout;
+  const mlpk::GradDst dst{{gW, gb, nullptr, nullptr, nullptr}, {nW, Q, Q, Q, Q}, 1.0f};
+  const hipError_t e = launch_grads(n, din, dout, X, src, gW, gb, ws, ws_floats, Q, dst, s);
   if (e != hipSuccess || !dX) return e;
   return launch_grad_dx(n, din, dout, W, src, dX, s);
 }

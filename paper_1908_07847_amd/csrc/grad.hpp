@@ -14,6 +14,7 @@
 //                  a lane's operand is one element, 16 lanes read 64
 //                  contiguous bytes), 16 rows' loads issued together; the
 //                  waves meet in LDS in a fixed order.
+//   k_grad_unit    the sums of few rows: a workgroup owns one unit x 64 inputs
 //   k_grad_reduce  adds the row ranges' partials of every parameter in a fixed
 //                  order (not launched when one range covers all rows)
 //   k_grad_dx      64 rows x 64 inputs per workgroup, delta and W staged in
@@ -305,6 +306,102 @@ __global__ __launch_bounds__(64 * kGWaves, Src::KO > 4 ? 1 : 2) void k_grad_sum(
   }
 }
 
+// The sums of few rows: a workgroup owns one unit and 64 inputs (a lane each),
+// its 8 waves take 64-row sets in turn, a lane forming delta of one row, and
+// meet in LDS in pairs.  (Eight chains per wave: a sum of n rows is n / 64
+// steps deep and 6 to meet, as with a wave of lanes over the rows.)  k_grad_sum's
+// 64 x 64 tiles leave a small layer to one workgroup: 512 rows of 50 -> 38
+// 20.0 us a call, here 4.6; mlp_backward of 512 rows of 33-16-3 25.0 us, here 6.0,
+// of 10-10-1 24.2 and 5.5 (device times).
+constexpr int kUnitWaves = 8;
+template <class Src>
+__global__ __launch_bounds__(64 * kUnitWaves) void k_grad_unit(int64_t n, int din, int dout, int ftiles,
+                                                               const float *__restrict__ X, Src src,
+                                                               float *__restrict__ gW, float *__restrict__ gb) {
+  constexpr int KO = Src::KO, KR = KO > 0 ? KO : 1;
+  // lane sums that meet over the waves: gb, and beside an output layer gW2, gb2
+  // and the squared error
+  constexpr int NS = KO > 0 ? 2 + 2 * KO : 1;
+  __shared__ float part[kUnitWaves][64];
+  __shared__ float sums[kUnitWaves][NS];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int o = blockIdx.x / ftiles, ft = blockIdx.x - o * ftiles, f = ft * 64 + lane;
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, sum[NS], w2[KR], sq = 0.0f;
+#pragma unroll
+  for (int i = 0; i < NS; ++i) sum[i] = 0.0f;
+  if constexpr (KO > 0) {
+#pragma unroll
+    for (int k = 0; k < KO; ++k) w2[k] = k < src.K ? src.W2[(int64_t)k * dout + o] : 0.0f;
+  }
+  for (int64_t r0 = wave * 64; r0 < n; r0 += 64 * kUnitWaves) {
+    const int rows = (int)min((int64_t)64, n - r0);
+    const __amdgpu_buffer_rsrc_t xr = gbuf(X + r0 * din, (uint32_t)(rows * din) * 4u);   // rows past n read zero
+    float x[64];
+#pragma unroll
+    for (int j = 0; j < 64; ++j) x[j] = gld(xr, f < din ? 4u * (uint32_t)(j * din + f) : kNoLoad);
+    const int64_t r = r0 + min(lane, rows - 1), q = r * dout + o;
+    float d;
+    if constexpr (KO > 0) {
+      const float a = src.A[q];
+      float bp = 0.0f, sr = 0.0f;
+#pragma unroll
+      for (int k = 0; k < KO; ++k) {
+        float d2 = k < src.K ? src.d2(r, k, sr) : 0.0f;
+        bp = fmaf(d2, w2[k], bp);
+        d2 = lane < rows ? d2 : 0.0f;
+        sum[1 + k] = lane < rows ? fmaf(d2, a, sum[1 + k]) : sum[1 + k];
+        sum[1 + KO + k] += d2;
+      }
+      sq += lane < rows ? sr : 0.0f;
+      d = src.slope_times(a, bp);
+    } else {
+      d = src.slope_times(src.Y[q], src.dY[q]);
+    }
+    d = lane < rows ? d : 0.0f;
+    sum[0] += d;
+#pragma unroll
+    for (int j = 0; j < 64; ++j)
+      acc[j & 7] = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), j)), x[j], acc[j & 7]);
+  }
+  part[wave][lane] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+  if (ft == 0) {   // the workgroup that also sums gb and gW2 (o == 0: gb2, the loss)
+    if constexpr (KO > 0) sum[NS - 1] = sq;
+    const int ns = KO > 0 ? (o == 0 ? NS : 1 + KO) : NS;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      if (i < ns) {
+        const float v = wave_sum(sum[i]);
+        if (lane == 0) sums[wave][i] = v;
+      }
+    }
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  auto meet = [](float (&v)[kUnitWaves]) {
+#pragma unroll
+    for (int st = 1; st < kUnitWaves; st *= 2)
+#pragma unroll
+      for (int w = 0; w < kUnitWaves; w += 2 * st) v[w] += v[w + st];
+    return v[0];
+  };
+  float v[kUnitWaves];
+#pragma unroll
+  for (int w = 0; w < kUnitWaves; ++w) v[w] = part[w][lane];
+  const float g = meet(v);
+  if (f < din) gW[(int64_t)o * din + f] = g;
+  if (ft != 0 || lane >= NS) return;
+#pragma unroll
+  for (int w = 0; w < kUnitWaves; ++w) v[w] = sums[w][lane];
+  const float t = meet(v);
+  if (lane == 0) gb[o] = t;
+  if constexpr (KO > 0) {
+    const int k = lane <= KO ? lane - 1 : lane - 1 - KO;
+    if (lane >= 1 && lane <= KO && k < src.K) src.gW2[(int64_t)k * dout + o] = t;
+    if (o == 0 && lane > KO && k < src.K) src.gb2[k] = t;
+    if (o == 0 && lane == NS - 1 && src.loss) src.loss[0] = t * src.loss_scale;
+  }
+}
+
 // Final arrays of a reduction: packed offsets [0, e0) go to p0, [e0, e1) to
 // p1, and so on; the last entry (the loss) is scaled and may be dropped.
 struct GradDst {
@@ -468,6 +565,28 @@ hipError_t launch_grad_sum(int64_t n, int din, int dout, const float *X, const S
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || S == 1) return e;
   hipLaunchKernelGGL(k_grad_reduce, dim3((unsigned)((Q + 63) / 64)), dim3(256), 0, s, Q, (int)S, ws, dst);
+  return hipGetLastError();
+}
+
+// k_grad_unit up to these rows, workgroups, and rows x workgroups: beyond, X
+// read once per unit costs more than k_grad_sum's tiles and the launch that adds
+// their partials.  Microseconds on the device, here against there: 50 -> 38, 1200
+// rows 7.0 / 11, 2048 10.4 / 10.9, 3000 14.0 / 11.5; 64 -> 256, 1200 rows 7.8 /
+// 11, 2048 14.1 / 11.2; below an output layer 33-16-3, 512 rows 6.0 / 12.7, 2048
+// 13.7 / 13.4, 2500 16.3 / 13.7; 33-1024-3, 60 rows 11.3 / 10.3, 300 16.4 / 12.7;
+// with more than four outputs 64-64-16, 800 rows 19.0 / 21.6, 1200 25.1 / 21.9;
+// 64-512-12, 300 rows 16 / 20, 800 27 / 21.
+constexpr int64_t kUnitRows = 2048, kUnitRowsWide = 1024, kUnitGroups = 512, kUnitWork = 400000;
+
+// The sums by the form that suits the sizes.
+template <class Src>
+hipError_t launch_grads(int64_t n, int din, int dout, const float *X, const Src &src, float *gW, float *gb, float *ws,
+                        int64_t cap, int64_t Q, const mlpk::GradDst &dst, hipStream_t s) {
+  const int64_t ft = ((int64_t)din + 63) / 64, groups = dout * ft;
+  if (n > (Src::KO > 4 ? kUnitRowsWide : kUnitRows) || groups > kUnitGroups || n * groups > kUnitWork)
+    return launch_grad_sum(n, din, dout, X, src, gW, gb, ws, cap, Q, dst, s);
+  hipLaunchKernelGGL(mlpk::k_grad_unit<Src>, dim3((unsigned)groups), dim3(64 * mlpk::kUnitWaves), 0, s, n, din, dout,
+                     (int)ft, X, src, gW, gb);
   return hipGetLastError();
 }
 

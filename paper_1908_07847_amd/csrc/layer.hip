@@ -771,7 +771,7 @@ static hipError_t backward_ko(int64_t n, int64_t ws_floats, int D, int H, int K,
   mlpk::HiddenDelta<KO> src{A, p.W2, Y, dY, T, K, act, 2.0f / ((float)n * (float)K), g.W2, g.b2, loss, inv_nk};
   const int64_t oB1 = (int64_t)D * H, oW2 = oB1 + H, oB2 = oW2 + (int64_t)H * K, P = oB2 + K;
   const mlpk::GradDst dst{{g.W1, g.b1, g.W2, g.b2, loss}, {oB1, oW2, oB2, P, P + 1}, inv_nk};
-  hipError_t e = launch_grad_sum(n, D, H, X, src, g.W1, g.b1, ws, ws_floats, P + 1, dst, s);
+  hipError_t e = launch_grads(n, D, H, X, src, g.W1, g.b1, ws, ws_floats, P + 1, dst, s);
   if (e != hipSuccess || !dX) return e;
   return launch_grad_dx(n, D, H, p.W1, src, dX, s);
 }
