@@ -536,14 +536,13 @@ __global__ __launch_bounds__(256) void k_grad_dx(int64_t n, int din, int dout, c
 namespace mlph {
 
 // Row ranges of the gradient sums: enough workgroups for about two per CU,
-// each range at least 128 rows (a set for every wave), and no more partials
-// than the workspace holds.  Up to 512 rows one range is used, for one launch
-// less (15.4 us at 300 rows, 20.0 at 512; with ranges 13.6 at 513 and a launch
-// more, which callers at these sizes are bound by).
+// each range at least 128 rows (a set for every wave: of 160 rows one wave has
+// two while three wait, 33 -> 16 on 2300 rows 13.9 us, on ranges of 128 10.7),
+// and no more partials than the workspace holds.
 inline int64_t grad_ranges(int64_t n, int64_t tiles, int64_t Q, int64_t cap) {
-  if (n <= 512) return 1;
+  constexpr int64_t least = mlpk::kGWaves * mlpk::kGSet;
   int64_t S = (512 + tiles - 1) / tiles;
-  S = S < n / 128 ? S : n / 128;
+  S = S < (n + least - 1) / least ? S : (n + least - 1) / least;
   S = S < cap / Q ? S : cap / Q;
   S = S < 65535 ? S : 65535;
   return S < 1 ? 1 : S;
@@ -557,7 +556,8 @@ hipError_t launch_grad_sum(int64_t n, int din, int dout, const float *X, const S
   using namespace mlpk;
   const int64_t ot = (dout + kGT - 1) / kGT, ft = (din + kGT - 1) / kGT;
   int64_t S = grad_ranges(n, ot * ft, Q, cap);
-  const int64_t per = ((n + S - 1) / S + kGSet - 1) / kGSet * kGSet;
+  const int64_t even = ((n + S - 1) / S + kGSet - 1) / kGSet * kGSet;
+  const int64_t per = even > kGWaves * kGSet ? even : kGWaves * kGSet;
   S = (n + per - 1) / per;
   const GradOut out{S > 1 ? ws : nullptr, Q, gW, gb};
   hipLaunchKernelGGL(k_grad_sum<Src>, dim3((unsigned)(ot * ft), (unsigned)S), dim3(64 * kGWaves), 0, s, n, din, dout,
