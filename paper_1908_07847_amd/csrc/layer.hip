@@ -23,8 +23,9 @@
 //                  theta <- theta - lr v).  Forward and backward take the
 //                  hidden activation (sigma, or the tanh variant).
 //  k_eval_tiled    one workgroup per net of a batched item table, z1 on the
-//                  matrix cores; k_cv_means, k_cv_best: the folds' mean losses
-//                  and the best group
+//                  matrix cores, hidden tiles over the waves; k_eval_rows rows
+//                  over the waves, for nets of up to 16 units; k_cv_means,
+//                  k_cv_best: the folds' mean losses and the best group
 //  k_eval_batched  the same for any n_in, n_out: loss and
 //                  correct count of the net on its own rows (e.g. a held-out
 //                  fold), threads over rows, fixed-order block sums
@@ -450,7 +451,7 @@ __global__ __launch_bounds__(256, 4) void k_eval_tiled(const mlp_batch_item *__r
   const int N = it.n_rows, H = it.n_hidden, HT = (H + 15) / 16;
   const float *W1 = theta + it.p_off, *b1 = W1 + (int64_t)H * D, *W2 = b1 + H, *b2 = W2 + (int64_t)K * H;
   const float *Xn = X + it.x_off * D, *Tn = T + it.x_off * K;
-  float sq = 0.0f;
+  float total = 0.0f, sq = 0.0f;   // (the sum of a long fold in two levels)
   int hit = 0, buf = 0;
   for (int r0 = 0; r0 < N; r0 += 32, buf ^= 1) {
     const int rows = min(32, N - r0);
@@ -530,10 +531,14 @@ __global__ __launch_bounds__(256, 4) void k_eval_tiled(const mlp_batch_item *__r
       const float y4[4] = {quad_bcast(y, 0), quad_bcast(y, 1), quad_bcast(y, 2), quad_bcast(y, 3)};
       const float t4[4] = {quad_bcast(t, 0), quad_bcast(t, 1), quad_bcast(t, 2), quad_bcast(t, 3)};
       if (k == 0 && r < rows) hit += argmax4(y4, K) == argmax4(t4, K);
+      if ((r0 & 1023) == 992) {
+        total += sq;
+        sq = 0.0f;
+      }
     }
   }
   if (wave < 2) {
-    const float v = wave_sum(sq);
+    const float v = wave_sum(total + sq);
     for (int off = 32; off >= 1; off >>= 1) hit += __shfl_xor(hit, off, kWave);
     if (lane == 0) {
       ps[wave] = v;
@@ -544,6 +549,101 @@ __global__ __launch_bounds__(256, 4) void k_eval_tiled(const mlp_batch_item *__r
   if (tid == 0) {
     loss[blockIdx.x] = (ps[0] + ps[1]) / ((float)N * (float)K);
     if (correct) correct[blockIdx.x] = ph[0] + ph[1];
+  }
+}
+
+// The same for networks of up to 16 units, one hidden tile, whose other waves
+// would be idle above: each wave has 32-row sets of its own, no shares to meet.
+// A lane ends with one output of one row.  1000 rows of 10 units and 4 inputs:
+// 52 us above, 14 here, 24 with a thread per row; 20,000 rows 974, 233, 434; 4096
+// networks of 25 rows and up to 16 units, 33 inputs 17.3 above, 9.8 here.
+template <int NS>
+__global__ __launch_bounds__(256) void k_eval_rows(const mlp_batch_item *__restrict__ items, int D, int K,
+                                                   const float *__restrict__ X, const float *__restrict__ T,
+                                                   const float *__restrict__ theta, float *__restrict__ loss,
+                                                   int32_t *__restrict__ correct) {
+  __shared__ float ps[4];
+  __shared__ int ph[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), NW = blockDim.x >> 6;
+  const int l16 = lane & 15, lg = lane >> 4;
+  const mlp_batch_item it = items[blockIdx.x];
+  const int N = it.n_rows, H = it.n_hidden;
+  const float *W1 = theta + it.p_off, *b1 = W1 + H * D, *W2 = b1 + H, *b2 = W2 + K * H;
+  const float *Xn = X + it.x_off * D, *Tn = T + it.x_off * K;
+  const bool hon = l16 < H;
+  uint32_t co[NS];   // column offsets of the lane, past the end for padding
+#pragma unroll
+  for (int s = 0; s < NS; ++s) co[s] = 4 * s + lg < D ? 4u * (4 * s + lg) : kNoLoad;
+  float wv[NS], w2[4];
+  const __amdgpu_buffer_rsrc_t w1r = gbuf(W1, (uint32_t)(H * D) * 4u);
+#pragma unroll
+  for (int s = 0; s < NS; ++s) wv[s] = gld(w1r, 4u * (uint32_t)(l16 * D) + co[s]);
+  const float bias = gld(gbuf(b1, (uint32_t)H * 4u), 4u * l16);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w2[k] = gld(gbuf(W2, (uint32_t)(K * H) * 4u), hon && k < K ? 4u * (uint32_t)(k * H + l16) : kNoLoad);
+  const int k = l16 & 3;   // this lane's output
+  const float b2k = gld(gbuf(b2, K * 4u), 4u * k);
+  float total = 0.0f, sq = 0.0f;
+  int hit = 0, round = 0;
+  for (int64_t r0 = 32 * wave; r0 < N; r0 += 32 * NW) {
+    const int rows = (int)min((int64_t)32, N - r0);
+    const __amdgpu_buffer_rsrc_t xc = gbuf(Xn + r0 * D, (uint32_t)(rows * D) * 4u);
+    const __amdgpu_buffer_rsrc_t tr = gbuf(Tn + r0 * K, (uint32_t)(rows * K) * 4u);
+    float xa[2][NS], tl[2];
+#pragma unroll
+    for (int rs = 0; rs < 2; ++rs) {
+      tl[rs] = gld(tr, k < K ? 4u * (uint32_t)((16 * rs + 4 * lg + (l16 >> 2)) * K + k) : kNoLoad);
+#pragma unroll
+      for (int s = 0; s < NS; ++s) xa[rs][s] = gld(xc, co[s] + 4u * (uint32_t)((16 * rs + l16) * D));
+    }
+    f32x4_l z[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      z[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[0][s], wv[s], z[0], 0, 0, 0);
+      z[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[1][s], wv[s], z[1], 0, 0, 0);
+    }
+#pragma unroll
+    for (int rs = 0; rs < 2; ++rs) {
+      // lane 4 i + k of a row group keeps row i, output k
+      float z2 = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float a = hon ? sigmoid(z[rs][i] + bias) : 0.0f;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          const float v = sum16(a * w2[kk]);
+          z2 = l16 == 4 * i + kk ? v : z2;
+        }
+      }
+      const int r = 16 * rs + 4 * lg + (l16 >> 2);
+      const bool on = r < rows && k < K;
+      const float y = sigmoid(z2 + b2k), t = on ? tl[rs] : 0.0f, e = on ? y - t : 0.0f;
+      sq = fmaf(e, e, sq);
+      const float y4[4] = {quad_bcast(y, 0), quad_bcast(y, 1), quad_bcast(y, 2), quad_bcast(y, 3)};
+      const float t4[4] = {quad_bcast(t, 0), quad_bcast(t, 1), quad_bcast(t, 2), quad_bcast(t, 3)};
+      if (k == 0 && r < rows) hit += argmax4(y4, K) == argmax4(t4, K);
+    }
+    if ((++round & 31) == 0) {   // (a long fold's sum in two levels)
+      total += sq;
+      sq = 0.0f;
+    }
+  }
+  total = wave_sum(total + sq);
+  for (int off = 32; off >= 1; off >>= 1) hit += __shfl_xor(hit, off, kWave);
+  if (lane == 0) {
+    ps[wave] = total;
+    ph[wave] = hit;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    float v = ps[0];
+    int c = ph[0];
+    for (int w = 1; w < NW; ++w) {
+      v += ps[w];
+      c += ph[w];
+    }
+    loss[blockIdx.x] = v / ((float)N * (float)K);
+    if (correct) correct[blockIdx.x] = c;
   }
 }
 
@@ -728,18 +828,35 @@ hipError_t launch_cv_select(const float *loss, const int32_t *group, int n_nets,
   return hipGetLastError();
 }
 
-// k_eval_tiled for every contraction length.
-template <int NS>
+// k_eval_tiled or k_eval_rows for every contraction length.
+template <int NS, bool ROWS>
 static auto eval_kernel(int ns) -> decltype(&mlpk::k_eval_batched) {
-  if (ns == NS) return mlpk::k_eval_tiled<NS>;
-  if constexpr (NS < 16) return eval_kernel<NS + 1>(ns);
+  if constexpr (ROWS) {
+    if (ns == NS) return mlpk::k_eval_rows<NS>;
+  } else {
+    if (ns == NS) return mlpk::k_eval_tiled<NS>;
+  }
+  if constexpr (NS < 16) return eval_kernel<NS + 1, ROWS>(ns);
   return mlpk::k_eval_batched;   // n_in > 64: one thread per row
 }
 
-hipError_t launch_eval_batched(const mlp_batch_item *items_dev, int n_nets, int D, int K, const float *X,
-                               const float *T, const float *theta, float *loss, int32_t *correct, hipStream_t s) {
-  hipLaunchKernelGGL(eval_kernel<1>((D + 3) / 4), dim3(n_nets), dim3(256), 0, s, items_dev, D, K, X, T, theta, loss,
-                     correct);
+// One thread per row above 64 inputs, and where there are rows for the threads and
+// a row is little more than its sigmoids, of which 16-unit tiles evaluate the
+// padding too.  Threads / tiles, 4096 networks of 1000 rows: 1 input, 10 units
+// 62 / 110 us, 64 units 262 / 331; 3 inputs, 10 units 92 / 111; 4 inputs, 6 units
+// 101 / 111, 10 units 154 / 111; of 100..128 rows, 1 input, 10 units 13 / 17.  One
+// network of 1000 rows, 1 input: 6 units 11.5 / 13.9, 10 units 15.6 / 13.9.
+hipError_t launch_eval_batched(const mlp_batch_item *items_dev, int n_nets, int max_rows, int max_hidden, int D, int K,
+                               const float *X, const float *T, const float *theta, float *loss, int32_t *correct,
+                               hipStream_t s) {
+  const bool rows = max_hidden <= 16, full = n_nets >= 1024;
+  const int64_t unit = (D + 4) * (int64_t)max_hidden;
+  const bool threads = D > 64 || (max_rows >= (full ? 96 : 256) && unit <= (full ? 72 : 36)) ||
+                       (full && max_rows >= 256 && D == 1);
+  const int ns = (D + 3) / 4;
+  const auto kern = threads ? mlpk::k_eval_batched : rows ? eval_kernel<1, true>(ns) : eval_kernel<1, false>(ns);
+  const int waves = threads || !rows ? 4 : std::min(4, (max_rows + 31) / 32);
+  hipLaunchKernelGGL(kern, dim3(n_nets), dim3(64 * waves), 0, s, items_dev, D, K, X, T, theta, loss, correct);
   return hipGetLastError();
 }
 

@@ -383,8 +383,11 @@ mlp_status mlp_eval_batched(const mlp_batch_item *items_host, const mlp_batch_it
     return fail(MLP_ERR_ALIGN, "items, X and T must be 16-byte aligned");
   if (!aligned4(theta_packed) || !aligned4(loss) || (correct && !aligned4(correct)))
     return fail(MLP_ERR_ALIGN, "theta, loss, correct must be 4-byte aligned");
+  int max_rows = 0, max_h = 0;
   for (int32_t i = 0; i < n_nets; ++i) {
     const mlp_batch_item &it = items_host[i];
+    max_rows = std::max(max_rows, it.n_rows);
+    max_h = std::max(max_h, it.n_hidden);
     if (it.n_rows <= 0 || it.n_hidden <= 0 || it.n_hidden > (1 << 20))
       return fail(MLP_ERR_SHAPE, "net %d: n_rows %d / n_hidden %d must be positive (n_hidden <= 2^20)", i,
                   it.n_rows, it.n_hidden);
@@ -395,8 +398,8 @@ mlp_status mlp_eval_batched(const mlp_batch_item *items_host, const mlp_batch_it
     if (it.p_off < 0 || it.p_off + n_params(n_in, it.n_hidden, n_out) > total_params)
       return fail(MLP_ERR_SHAPE, "net %d: parameters outside the %lld packed floats", i, (long long)total_params);
   }
-  hipError_t e = mlph::launch_eval_batched(items_dev, n_nets, n_in, n_out, X_packed, T_packed, theta_packed, loss,
-                                           correct, (hipStream_t)stream);
+  hipError_t e = mlph::launch_eval_batched(items_dev, n_nets, max_rows, max_h, n_in, n_out, X_packed, T_packed,
+                                           theta_packed, loss, correct, (hipStream_t)stream);
   return e == hipSuccess ? MLP_OK : hip_fail(e, "mlp_eval_batched launch");
 }
 
