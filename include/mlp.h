@@ -261,8 +261,8 @@ mlp_status mlp_eval_batched(const mlp_batch_item *items_host, const mlp_batch_it
  * instance mlp_eval_batched's held-out losses), group [n_nets] (int32),
  * group_mean [n_groups] and best [1] are device pointers, 4-byte aligned;
  * 1 <= n_nets, 1 <= n_groups <= 65536.  A net whose group index lies outside
- * [0, n_groups) belongs to no group (the kernel cannot report it).  One
- * launch on the stream, no allocation. */
+ * [0, n_groups) belongs to no group (the kernel cannot report it).  One or
+ * two launches on the stream, no allocation. */
 mlp_status mlp_cv_select(const float *loss, const int32_t *group, int32_t n_nets, int32_t n_groups,
                          float *group_mean, int32_t *best, void *stream);
 
