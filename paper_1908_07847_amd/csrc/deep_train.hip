@@ -231,8 +231,12 @@ __global__ __launch_bounds__(mlph::kDeepThreads) void k_deep_train(
 using mlph::DeepTilePlan;
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-// HT: unit tiles of the hidden layers; LC: layers; ACT: 0 sigma, 1 tanh.
-template <int HT, int ACT, int LC>
+// HT: unit tiles of the widest hidden layer; LC: layers; ACT: 0 sigma, 1 tanh;
+// RAG: a hidden layer has fewer tiles than HT, and the loops over its tiles stop
+// there (uniform branches; without them the padding of narrow layers beside a
+// wide one costs more than the matrix cores gain: 4-8-4-48-1 on 3 rows 9.7 us an
+// epoch, with them 6.0, in the form above 7.2).
+template <int HT, int ACT, int LC, bool RAG>
 __global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
     DeepTilePlan p, const float *__restrict__ X, const float *__restrict__ T, float *__restrict__ theta,
     float *__restrict__ comp, float lr, int epochs, float *__restrict__ loss_hist) {
@@ -270,6 +274,10 @@ __global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
   }
   __syncthreads();
 
+  // unit tiles of layer l's outputs, and of its inputs above the first layer
+  auto tiles_out = [&](int l) { return l == LC - 1 ? 1 : RAG ? (p.w[l + 1] + 15) >> 4 : HT; };
+  auto tiles_in = [&](int l) { return RAG ? (p.w[l] + 15) >> 4 : HT; };
+
   const float dscale = 2.0f / ((float)n * (float)K);
   const float inv_nk = 1.0f / ((float)n * (float)K);
 
@@ -282,7 +290,7 @@ __global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
 #pragma unroll
       for (int l = 0; l < LC; ++l) {
         constexpr int kTop = LC - 1;
-        const int OT = l == kTop ? 1 : HT;
+        const int OT = tiles_out(l);
         const int s0 = l ? SH : SX;
         const float *W = sm + p.woff[l] + l16 * s0 + 4 * lg;
         f32x4_t z[HT];
@@ -304,7 +312,8 @@ __global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
           for (int it = 0; it < IT0; ++it) tile(it, *reinterpret_cast<const f32x4_t *>(x + 16 * it));
         } else {
 #pragma unroll
-          for (int it = 0; it < HT; ++it) tile(it, a[l ? l - 1 : 0][it]);
+          for (int it = 0; it < HT; ++it)
+            if (it < tiles_in(l)) tile(it, a[l ? l - 1 : 0][it]);
         }
 #pragma unroll
         for (int t = 0; t < HT; ++t) {
@@ -331,11 +340,12 @@ __global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
       // the deltas below, through the pre-update weights
 #pragma unroll
       for (int l = LC - 1; l > 0; --l) {
-        const int OT = l == LC - 1 ? 1 : HT;
+        const int OT = tiles_out(l);
         f32x4_t dn[HT];
         const float *W = sm + p.woff[l] + 4 * lg * SH + l16;
 #pragma unroll
         for (int it = 0; it < HT; ++it) {
+          if (it >= tiles_in(l)) break;
           f32x4_t b = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int t = 0; t < HT; ++t)
@@ -381,6 +391,7 @@ __global__ __launch_bounds__(64 * mlph::kDeepTileWaves) void k_deep_tiled(
         ot = l == LC - 1 ? 0 : r - it * HT;
       }
       const int sa = l ? SH : SX, sd = l == LC - 1 ? ST : SH, wi = p.w[l], wo = p.w[l + 1];
+      if (RAG && (16 * it >= wi || 16 * ot >= wo)) continue;   // only padding
       const float *Dp = sm + p.doff[l] + lg * sd + 16 * ot + l16;
       const float *Ap = sm + p.aoff[l] + lg * sa + 16 * it + l16;
       // row tiles in pairs whose chains overlap, each from zero and added to
@@ -509,22 +520,24 @@ bool deep_tile_plan(int L, const int32_t *widths, int64_t n, size_t lds_max, Dee
   return true;
 }
 
-template <int ACT>
-static const void *deep_tiled_kernel(int ht, int L) {
+template <int ACT, int LC>
+static const void *deep_tiled_kernel(int ht, bool ragged) {
   using namespace mlpk;
-  if (L == 2)
-    return ht == 1 ? (const void *)k_deep_tiled<1, ACT, 2>
-                   : (ht == 2 ? (const void *)k_deep_tiled<2, ACT, 2> : (const void *)k_deep_tiled<4, ACT, 2>);
-  if (L == 3)
-    return ht == 1 ? (const void *)k_deep_tiled<1, ACT, 3>
-                   : (ht == 2 ? (const void *)k_deep_tiled<2, ACT, 3> : (const void *)k_deep_tiled<4, ACT, 3>);
-  return ht == 1 ? (const void *)k_deep_tiled<1, ACT, 4>
-                 : (ht == 2 ? (const void *)k_deep_tiled<2, ACT, 4> : (const void *)k_deep_tiled<4, ACT, 4>);
+  if (ht == 4) return ragged ? (const void *)k_deep_tiled<4, ACT, LC, true> : (const void *)k_deep_tiled<4, ACT, LC, false>;
+  return ht == 1 ? (const void *)k_deep_tiled<1, ACT, LC, false> : (const void *)k_deep_tiled<2, ACT, LC, false>;
 }
 
 hipError_t launch_deep_train_tiled(const DeepTilePlan &p, int n_layers, int act, const float *X, const float *T,
                                    float *theta, float *comp, float lr, int epochs, float *loss_hist, hipStream_t s) {
-  const void *kern = act == 1 ? deep_tiled_kernel<1>(p.ht, n_layers) : deep_tiled_kernel<0>(p.ht, n_layers);
+  // the branches pay where at most 0.7 of the padded tiles are real (an epoch on
+  // 2 rows with and without: 48-50-48-32-1, 0.67, 10.9 / 11.1 us; 16-33-64-4, 0.79,
+  // 8.0 / 7.7; 16-33-50-50-2, 0.88, 11.7 / 9.8)
+  int real = 0;
+  for (int l = 0; l < n_layers; ++l) real += (p.w[l] + 15) / 16 * ((p.w[l + 1] + 15) / 16);
+  const bool ragged = 10 * real <= 7 * p.tiles;
+  const void *kern = n_layers == 2   ? (act ? deep_tiled_kernel<1, 2>(p.ht, ragged) : deep_tiled_kernel<0, 2>(p.ht, ragged))
+                     : n_layers == 3 ? (act ? deep_tiled_kernel<1, 3>(p.ht, ragged) : deep_tiled_kernel<0, 3>(p.ht, ragged))
+                                     : (act ? deep_tiled_kernel<1, 4>(p.ht, ragged) : deep_tiled_kernel<0, 4>(p.ht, ragged));
   const size_t lds = (size_t)p.total * sizeof(float);
   hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
