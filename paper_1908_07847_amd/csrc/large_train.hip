@@ -220,6 +220,23 @@ struct GradOrder {
     nw = Hp / 16 * NFB * 256;
     q = nw + Hp * (1 + K) + 4;
   }
+  // entry of parameter p; its unit h and feature d (-1 outside W1).  md = ceil(2^32 / D)
+  // gives p / D exactly below 2^32 / D.
+  __device__ int entry(int p, uint32_t md, int &h, int &d) const {
+    d = -1;
+    if (p < D * H) {
+      h = D == 1 ? p : (int)__umulhi((uint32_t)p, md);
+      d = p - h * D;
+      return (((h >> 4) * NFB + (d >> 4)) * 64 + (h >> 2 & 3) * 16 + (d & 15)) * 4 + (h & 3);
+    }
+    h = p - D * H;
+    int r = 0;   // row 0: b1, 1 .. K: W2, K + 1: b2
+    while (r <= K && h >= H) {
+      h -= H;
+      ++r;
+    }
+    return nw + r * Hp + h;
+  }
   // parameters of entries 4 c .. 4 c + 3: p0 + i stride, those with i < n real
   __device__ void decode(int c, int &p0, int &stride, int &n, int &h, int &d) const {
     const int e = 4 * c;
@@ -333,6 +350,7 @@ __device__ __forceinline__ float sum_rows_of(float v) {
 constexpr int kStageU = 16;  // loads in flight per thread while staging
 constexpr int kPre = 32;     // X elements per thread loaded in one batch for a step's first piece
 constexpr int kRedU = 12;    // 16-byte partial-gradient loads in flight per thread
+constexpr int kLinU = 8;     // parameters of a small grid's update in flight per thread
 
 // q / D for 0 <= q < 2^16 and 1 <= D <= 64 with md = ceil(2^22 / D): the
 // error md*D - 2^22 <= D - 1 keeps q*md / 2^22 below the next integer.
@@ -423,7 +441,10 @@ struct LLayout {
 // or 1 for blocks of at most NW tiles (the loops over a wave's tiles then
 // hold one tile: a step's code is far smaller, and fits the instruction
 // cache that two CUs share, which the general instance's does not).
-template <int PREC, int KO, int NW, int NHM>
+// LIN: the update of a small grid, whose workgroups have more than half their
+// threads in quads of the partial order: a thread per parameter, kLinU of them at
+// a time, so that stores run along whole rows of W1 (see phase 3).
+template <int PREC, int KO, int NW, int NHM, bool LIN>
 __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
   static_assert(NHM >= 1 && NHM <= 16 / NW, "tiles per wave");
   constexpr int kNW = NW, kLT = 64 * NW;
@@ -1457,7 +1478,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
     {
       const int QT = go.q / 4 * a.M;               // quads of one row of partials
       const int per = (QT + G - 1) / G, c0 = bid * per, nq = max(0, min(QT, c0 + per) - c0);
-      const bool few = 2 * nq <= kLT;
+      const bool few = !LIN && 2 * nq <= kLT;
       int tid_o = tid;
       asm volatile("" : "+v"(tid_o));   // addresses formed per step (see the gradient stores)
       const uint32_t rowb = (uint32_t)QT * 16u;
@@ -1491,6 +1512,22 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
           qi = tid_o - grp * nq;
         }
       }
+      // LIN: this workgroup's parameters [l0, l0 + np), its first batch
+      const int lper = ((int)P + G - 1) / G, l0 = bid * lper, np = max(0, min((int)P, l0 + lper) - l0);
+      const uint32_t mdL = (uint32_t)(((1ull << 32) + (uint32_t)D - 1) / (uint32_t)D);
+      float lw[LIN ? kLinU : 1], lc[LIN ? kLinU : 1];
+      const __amdgpu_buffer_rsrc_t cr = xbuf(a.comp, a.comp && LIN ? (uint32_t)(P * 4) : 0u);
+      auto lin_params = [&](int q0) {
+        if constexpr (LIN) {
+#pragma unroll
+          for (int u = 0; u < kLinU; ++u) {
+            const uint32_t at = q0 + u * kLT < np ? 4u * (uint32_t)(l0 + q0 + u * kLT) : kPastEnd;
+            lw[u] = xld4(thr, at);
+            lc[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(cr, (int)at, 0, 0));
+          }
+        }
+      };
+      lin_params(tid_o);
       if (!wait()) { ok = false; break; }
       float wmax = 0.0f;
       // the loss partials of net bid (workgroup n keeps net n's loss), issued
@@ -1515,7 +1552,38 @@ __global__ __launch_bounds__(64 * NW, 1) void k_large_train(LargeArgs a) {
           }
         }
       };
-      if (few) {
+      if constexpr (LIN) {
+        // Rows of partials in order, as below; 4-byte loads, but stores along rows
+        // of W1: a quad of the partial order stores 16 lanes here and 16 there, in
+        // three arrays, and small grids spent half a step on that (33-64-3 at 32
+        // rows 9.9 of 19 us, here 6.0 of 16; 33-4-3 6.5 of 16, here 1.4 of 11.4).
+        for (int q0 = tid_o; q0 < np; q0 += kLinU * kLT) {
+          if (q0 != tid_o) lin_params(q0);
+          uint32_t at[kLinU];
+          int h[kLinU], d[kLinU];
+          float sum[kLinU];
+#pragma unroll
+          for (int u = 0; u < kLinU; ++u) {
+            sum[u] = 0.0f;
+            at[u] = q0 + u * kLT < np ? 4u * (uint32_t)go.entry(l0 + q0 + u * kLT, mdL, h[u], d[u]) : kPastEnd;
+          }
+          for (int gb = 0; gb < a.Gi; gb += 2) {
+            float v[kLinU][2];
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+              for (int u = 0; u < kLinU; ++u)
+                v[u][g] = xld4(gpr, gb + g < a.Gi && at[u] != kPastEnd ? (uint32_t)(gb + g) * rowb + at[u] : kPastEnd);
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+              for (int u = 0; u < kLinU; ++u) sum[u] += v[u][g];
+          }
+#pragma unroll
+          for (int u = 0; u < kLinU; ++u)
+            if (q0 + u * kLT < np) update(0, l0 + q0 + u * kLT, h[u], d[u], lw[u], lc[u], sum[u]);
+        }
+      } else if (few) {
         // 16 bytes a load, kRedU in flight (a row past the group's end reads
         // past the buffer: zero); the groups meet in LDS
         if (grp < ng) {
@@ -1870,14 +1938,14 @@ mlp_status large_plan(const mlp_config &c, int n_nets, int n_cu, int shape[5], s
 
 // The kernel instance: operand type, output count (3 or 4), waves, tiles
 // per wave.
-template <int NW, int NHM>
+template <int NW, int NHM, bool LIN = false>
 static const void *kernel_nw(int prec, bool k3) {
   using namespace mlpk;
   if (prec == MLP_FP32)
-    return k3 ? (const void *)k_large_train<0, 3, NW, NHM> : (const void *)k_large_train<0, 4, NW, NHM>;
+    return k3 ? (const void *)k_large_train<0, 3, NW, NHM, LIN> : (const void *)k_large_train<0, 4, NW, NHM, LIN>;
   if (prec == MLP_BF16)
-    return k3 ? (const void *)k_large_train<1, 3, NW, NHM> : (const void *)k_large_train<1, 4, NW, NHM>;
-  return k3 ? (const void *)k_large_train<2, 3, NW, NHM> : (const void *)k_large_train<2, 4, NW, NHM>;
+    return k3 ? (const void *)k_large_train<1, 3, NW, NHM, LIN> : (const void *)k_large_train<1, 4, NW, NHM, LIN>;
+  return k3 ? (const void *)k_large_train<2, 3, NW, NHM, LIN> : (const void *)k_large_train<2, 4, NW, NHM, LIN>;
 }
 // tiles per wave of a plan: one when the hidden block has at most one
 // 16-unit tile per wave (4 waves), else 16 / waves
@@ -1885,9 +1953,16 @@ static int tiles_per_wave(const Plan &pl) {
   const int nt = pl.Hp / pl.Gj / 16;
   return (pl.nw == 4 && nt <= 4) ? 1 : 16 / pl.nw;
 }
-static const void *kernel_for(int prec, bool k3, const Plan &pl) {
-  if (pl.nw == 8) return kernel_nw<8, 2>(prec, k3);
-  return tiles_per_wave(pl) == 1 ? kernel_nw<4, 1>(prec, k3) : kernel_nw<4, 4>(prec, k3);
+static const void *kernel_for(const mlp_config &c, int n_nets, const Plan &pl) {
+  const bool k3 = c.n_out <= 3;
+  if (pl.nw == 8) return kernel_nw<8, 2>(c.prec, k3);
+  if (tiles_per_wave(pl) != 1) return kernel_nw<4, 4>(c.prec, k3);
+  // one net on a grid so small that a workgroup updates more quads than half its
+  // threads (33-64-3 at 128 rows, four workgroups of 209 quads: update 3.1 us with
+  // quads, 2.6 with parameters)
+  const int quads = mlpk::GradOrder(c.n_in, c.n_hidden, c.n_out, pl.Hp).q / 4, G = pl.Gi * pl.Gj;
+  const bool lin = n_nets == 1 && 2 * ((quads + G - 1) / G) > 256;
+  return lin ? kernel_nw<4, 1, true>(c.prec, k3) : kernel_nw<4, 1>(c.prec, k3);
 }
 
 mlp_status large_workspace_bytes(const mlp_config &c, int n_nets, size_t *bytes) {
@@ -1984,7 +2059,7 @@ mlp_status large_train(const mlp_config &c, int n_nets, const float *lrs, const 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { *err = hipGetErrorString(e); return MLP_ERR_HIP; }
 
-  const void *kern = kernel_for(c.prec, c.n_out <= 3, pl);
+  const void *kern = kernel_for(c, n_nets, pl);
   e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds);
   if (e != hipSuccess) { *err = std::string("hipFuncSetAttribute: ") + hipGetErrorString(e); return MLP_ERR_HIP; }
   int per_cu = 0;
