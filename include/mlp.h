@@ -455,7 +455,8 @@ mlp_status mlp_set_launch_hint(const mlp_launch_hint *hint /*host; NULL resets*/
  * 4-wave block has at most one tile per wave, else 16 / waves).  The default grid
  * fills the CUs with hidden blocks of 64..256 units and row blocks of at least
  * 32 rows (64 where there are more than 32 of them, in fp32 more than 128),
- * for one net the split whose blocks are nearest to square.  Host-only arithmetic (no
+ * for one net the split whose blocks are nearest to square (in fp32 of those
+ * with the least rows x units of a block, units padded to 64).  Host-only arithmetic (no
  * device call): *cfg and shape are host pointers.  MLP_ERR_ARG for a NULL
  * pointer, n_cu < 1 or n_nets outside 1..64; MLP_ERR_UNSUPPORTED when no
  * grid covers the shape (mlp_last_error says why). */

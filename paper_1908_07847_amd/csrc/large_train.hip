@@ -1839,11 +1839,17 @@ int max_row_blocks(int M, int Gj) { return M == 1 ? kMaxRowBlocks : std::max(1, 
 }  // namespace
 
 // Grid shape.  One net: of the grids with hidden blocks of 64..256 units (Gi
-// and Gj doubling), the one with the most workgroups, and among those the one
-// whose blocks are nearest to square (rows = units), with a launch-hint
-// override for the autotuner.  A step's exchanges grow with both counts -- Gi
-// partial gradients, Gj partial pre-activations -- and its work is the same,
-// so neither should be large: fp32, 48-512-3 at 8192 rows 34.8 us a step on
+// and Gj doubling), the one with the most workgroups, among those in float32 the
+// one with the smallest blocks, and then the one whose blocks are nearest to
+// square (rows = units), with a launch-hint override for the autotuner.  Hidden
+// blocks are padded to 64 units each, so blocks of as many workgroups differ in
+// work: the float32 products notice (33-192-3 at 16384 rows 36.0 us a step on 256 x
+// 1, 192 units, 37.6 on 128 x 2, 256; 64-768-3 at 4096 38.5 on 64 x 4, 39.4 on 32 x
+// 8; 64-1500-3 at 2048 38.6 on 32 x 8, 40.9 on 16 x 16), the cheaper ones do not
+// (the same in bf16: 27.6, 27.0; 28.7, 26.9; 28.7, 28.6; e4m3 30.4, 28.9; 31.9,
+// 30.4; 32.8, 33.3).  A step's exchanges grow with both counts -- Gi partial
+// gradients, Gj partial pre-activations -- so with equal blocks neither should be
+// large: fp32, 48-512-3 at 8192 rows 34.8 us a step on
 // 64 x 4 against 39.3 on 128 x 2, 60-777-3 at 4096 rows 37.8 on 32 x 8 against
 // 42.0 on 64 x 4, 64-256-3 at 16384 rows 38.9 on 128 x 2 against 42.4 on
 // 256 x 1 (bf16 24.0 against 27.9, 25.3 against 29.2, 25.7 against 29.5).
@@ -1870,12 +1876,19 @@ static bool plan_for(const mlp_config &c, int M, int n_cu, Plan *pl, std::string
       const double r = (double)(b / gi) / (double)((H + 64 * gj - 1) / (64 * gj) * 64);
       return r < 1.0 ? 1.0 / r : r;
     };
+    // rows x units of a block, padding included
+    auto work = [&](int gi, int gj) { return b / gi * (int64_t)((H + 64 * gj - 1) / (64 * gj) * 64); };
+    auto better = [&](int gi, int gj) {   // than Gi x Gj
+      if (gi * gj != Gi * Gj) return gi * gj > Gi * Gj;
+      if (c.prec == MLP_FP32 && work(gi, gj) != work(Gi, Gj)) return work(gi, gj) < work(Gi, Gj);
+      return skew(gi, gj) < skew(Gi, Gj);
+    };
     const int most_cu = std::min(n_cu, kMaxGrid);
     const int short_rows = c.prec == MLP_FP32 ? 128 : 32;   // row blocks of less than 64 rows: at most so many
     for (int gj = Gj0; gj <= kMaxHiddenBlocks && (gj == Gj0 || H > 64 * (gj / 2)) && gj <= most_cu; gj *= 2)
       for (int gi = 1; gi * gj <= most_cu && gi <= kMaxRowBlocks && b % ((int64_t)gi * 32) == 0; gi *= 2) {
         if (b / gi < 64 && gi > short_rows) break;
-        if (gi * gj > Gi * Gj || (gi * gj == Gi * Gj && skew(gi, gj) < skew(Gi, Gj))) {
+        if (better(gi, gj)) {
           Gi = gi;
           Gj = gj;
         }
