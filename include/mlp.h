@@ -231,7 +231,15 @@ typedef struct {
  * N_i*H_i gives a longest-first schedule.  theta_packed and comp_packed
  * (may be NULL: plain update) are updated in place; loss_hist
  * [n_nets][epochs] (may be NULL) is indexed by table position.  Every net's
- * result is independent of the others and of the table order. */
+ * result is independent of the table order, and of the other nets as long as
+ * these do not change the launch shape: the library picks it from the net
+ * count, the widest net and the device's CU count (up to one net per CU 8
+ * waves that split the rows; above, one wave per 16 units if the widest net
+ * has more than 32, else 4 waves; fewer waves where the longest and widest net's
+ * plan would not fit the LDS), and shapes add a gradient's rows in different
+ * orders, so a net's last bits may differ between them.  A launch hint of 64
+ * or 128 small_threads fixes the shape: a net then has the same bits in any
+ * company. */
 mlp_status mlp_train_batched(const mlp_batch_item *items_host, const mlp_batch_item *items_dev,
                              int32_t n_nets, int32_t n_in, int32_t n_out, const float *X_packed,
                              const float *T_packed, int64_t total_rows, float *theta_packed,

@@ -78,10 +78,6 @@ struct SmallVariant {
   float *vel;
 };
 
-// NW: waves; HTM: hidden tiles of the launch's widest net; FT: feature tiles
-// (D + 1 columns); ACT: the hidden activation (0 sigma, 1 tanh).  Fixed per
-// instance, so that LDS addresses are constants and nothing in the paper's
-// sigmoid network branches for a variant.
 // Four consecutive floats of LDS, 8-byte aligned.
 __device__ __forceinline__ f32x4_s quad(const float *q) {
   const float2 lo = *reinterpret_cast<const float2 *>(q), hi = *reinterpret_cast<const float2 *>(q + 2);
@@ -93,6 +89,10 @@ __device__ __forceinline__ f32x4_s quad(const float *q) {
 // and 30 features: 307 us, with 130 registers 347).
 constexpr int small_waves(int nw, int htm, int ft) { return nw == 8 ? (htm <= 2 && ft <= 2 ? 4 : 2) : 1; }
 
+// NW: waves; HTM: hidden tiles of the launch's widest net; FT: feature tiles
+// (D + 1 columns); ACT: the hidden activation (0 sigma, 1 tanh).  Fixed per
+// instance, so that LDS addresses are constants and nothing in the paper's
+// sigmoid network branches for a variant.
 template <int NW, int HTM, int FT, int ACT>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(small_waves(NW, HTM, FT)))) void k_small_train(
     const mlp_batch_item *__restrict__ items, mlp_batch_item one, int D, int K,
@@ -510,8 +510,8 @@ struct HSplitLayout {
   __host__ __device__ int total() const { return dd() + NW * 128 + 64; }   // + the over-read of the last X row
 };
 
-// At most 168 registers per lane (three waves per SIMD): three of the
-// largest nets (52 KB of LDS each) share a CU.
+// At most 168 registers per lane (three waves per SIMD): three nets of 120 rows,
+// 64 units and 33 features (51 KB of LDS each) share a CU.
 // The contraction's length is a template size (KS steps of 4 features), so
 // every LDS address is a lane's base and an immediate.  Bound: the SIMDs'
 // float32 units, which products (31 % of the cycles) and vector work share;
