@@ -481,7 +481,7 @@ def bench_batched(args):
                 "groups": [{"nets": c, "max_rows": r, "max_hidden": h, "stream": plan.stream_of[g]}
                            for g, (_, c, r, h) in enumerate(plan.groups)],
                 "launch": "hipGraph replay of one trainer launch per size group"},
-        cv_eval={"kernel": "mlpk::k_eval_batched + mlpk::k_cv_select", "ms": eval_s * 1e3, "heldout_rows": vrows,
+        cv_eval={"kernel": "mlpk::k_eval_tiled + mlpk::k_cv_means + mlpk::k_cv_best", "ms": eval_s * 1e3, "heldout_rows": vrows,
                  "rows_per_s": vrows / eval_s, "best_group": best, "best_group_hidden": int(
                      w["items_val"][int(np.nonzero(groups == best)[0][0])]["n_hidden"]),
                  "best_mean_heldout_loss": float(gmean[best]),
@@ -657,7 +657,7 @@ def bench_deep(args):
                   "form": "DenseFunction layers composed by torch.autograd, launched from Python"},
         roofline={"bound": "alu", "achieved": achieved, "peak": PEAK["fp32"], "unit": "TFLOP/s",
                   "frac": achieved / PEAK["fp32"], "traffic": None, "traffic_unit": "bytes per launch",
-                  "kernel": "mlpk::k_deep_train", "kernel_ms": kern * 1e3, "flops_per_launch": flops,
+                  "kernel": "mlpk::k_deep_tiled", "kernel_ms": kern * 1e3, "flops_per_launch": flops,
                   "one_cu": {"peak": cu_peak, "unit": "TFLOP/s", "frac": achieved / cu_peak,
                              "epoch_us": kern * 1e6 / steps}},
         final_loss=final_loss, repeats=reps, steps=steps, warmup=warmup)
@@ -731,7 +731,7 @@ def bench_autograd(args):
                 "n_hidden": H, "n_out": K, "lr": w["lr"], "step": "one epoch"},
         roofline={"bound": "alu", "achieved": achieved, "peak": PEAK["fp32"], "unit": "TFLOP/s",
                   "frac": achieved / PEAK["fp32"], "traffic": None, "traffic_unit": "bytes per launch",
-                  "kernel": "mlpk::k_forward_tiled + k_grad_sum (+ k_grad_reduce) + k_step (per epoch)",
+                  "kernel": "mlpk::k_forward_rows + k_grad_unit + k_step (per epoch)",
                   "kernel_ms": kern * 1e3, "flops_per_launch": flops},
         graph={"value": N * gsteps / gwall, "ms_per_step": gwall * 1e3 / gsteps, "epochs": gsteps,
                "form": f"per epoch mlp_forward, mlp_backward (the library's MSE adjoint) and mlp_step as library "
@@ -772,7 +772,7 @@ def bench_predict(args):
         roofline={"bound": "alu", "achieved": achieved, "peak": PEAK["fp32"], "unit": "TFLOP/s",
                   "frac": achieved / PEAK["fp32"], "traffic": measured_traffic(f"p4-fp32-steps{steps}", "layer"),
                   "traffic_unit": "bytes per launch",
-                  "kernel": "mlp_predict (mlpk::k_fill_i32 + k_forward_tiled + k_argmax)",
+                  "kernel": "mlp_predict (mlpk::k_fill_i32 + k_forward_rows)",
                   "kernel_ms": kern * 1e3 / steps, "flops_per_launch": flops // steps},
         repeats=reps, steps=steps, warmup=warmup)
     return res, dict(w=w)

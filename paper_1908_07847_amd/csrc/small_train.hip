@@ -85,8 +85,11 @@ __device__ __forceinline__ f32x4_s quad(const float *q) {
 }
 
 // Waves per SIMD that the registers have to allow: two workgroups of 8 waves
-// on a CU where the kernel is near 128 registers (472 nets of up to 32 units
-// and 30 features: 307 us, with 130 registers 347).
+// on a CU where the kernel is near 128 registers.  It matters above one net per
+// CU, by launch hint (50 epochs with it and without: 472 nets of 120 x 30, 32 units
+// 325 / 381 us, of 64 rows 225 / 282, of 120 x 20, 20 units, one output 285 / 350;
+// 1000 nets of 120 x 30, 32 units 621 / 749) and costs nothing elsewhere (16 units
+// 182 / 181; 15 features 238 / 241; 200 nets 190 / 190).
 constexpr int small_waves(int nw, int htm, int ft) { return nw == 8 ? (htm <= 2 && ft <= 2 ? 4 : 2) : 1; }
 
 // NW: waves; HTM: hidden tiles of the launch's widest net; FT: feature tiles
@@ -514,10 +517,11 @@ struct HSplitLayout {
 // 64 units and 33 features (51 KB of LDS each) share a CU.
 // The contraction's length is a template size (KS steps of 4 features), so
 // every LDS address is a lane's base and an immediate.  Bound: the SIMDs'
-// float32 units, which products (31 % of the cycles) and vector work share;
-// with run-time strides the vector work was nine instructions a product, a
-// third of them addresses and branches (4096 networks on this form, 100
-// epochs: 8.1 ms, now 6.2).
+// float32 units, which products and vector work share: 1450 nets of up to 120
+// rows and 64 units have the matrix cores busy 37 % of the cycles and the vector
+// unit 41 %, 8.2 vector instructions a product.  With run-time strides they were
+// nine, a third of them addresses and branches (4096 networks on this form, 100
+// epochs: 8.1 ms, now 6.0).
 template <int KS, int KO>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_small_hsplit(
     const mlp_batch_item *__restrict__ items, mlp_batch_item one, int D, int K,
