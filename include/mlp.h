@@ -151,7 +151,9 @@ mlp_status mlp_forward(mlp_net *net, const float *X, int64_t n, float *A, float 
  * NULL the mean-squared-error reading is used against T[n][K]
  * (dL/dY = 2 (Y - T) / (n K)) and, if loss is non-NULL, loss[0] receives
  * L.  grads (device, same shapes as the parameters) are overwritten with
- * the parameter gradients; dX[n][D] (may be NULL) receives delta1 W1.
+ * the parameter gradients; dX[n][D] (may be NULL) receives delta1 W1 and,
+ * where D = K, may lie over Y, dY or T; other overlaps of outputs and inputs
+ * are not allowed.
  * Row sums are reduced in a fixed order: repeated calls are bitwise equal. */
 mlp_status mlp_backward(mlp_net *net, const float *X, const float *A, const float *Y,
                         const float *dY, const float *T, int64_t n, mlp_params grads, float *dX,
