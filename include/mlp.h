@@ -151,9 +151,10 @@ mlp_status mlp_forward(mlp_net *net, const float *X, int64_t n, float *A, float 
  * NULL the mean-squared-error reading is used against T[n][K]
  * (dL/dY = 2 (Y - T) / (n K)) and, if loss is non-NULL, loss[0] receives
  * L.  grads (device, same shapes as the parameters) are overwritten with
- * the parameter gradients; dX[n][D] (may be NULL) receives delta1 W1 and,
- * where D = K, may lie over Y, dY or T; other overlaps of outputs and inputs
- * are not allowed.
+ * the parameter gradients; dX[n][D] (may be NULL) receives delta1 W1.
+ * dX may lie over Y, dY or T where D = K; gradients and loss may lie over
+ * Y, dY or T for n up to min(n_rows, 16384), over two of these at once for
+ * K <= H + 1 besides.  Other overlaps of outputs and inputs are not allowed.
  * Row sums are reduced in a fixed order: repeated calls are bitwise equal. */
 mlp_status mlp_backward(mlp_net *net, const float *X, const float *A, const float *Y,
                         const float *dY, const float *T, int64_t n, mlp_params grads, float *dX,

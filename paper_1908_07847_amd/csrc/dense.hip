@@ -177,11 +177,6 @@ static hipError_t dense_backward(int64_t n, int din, int dout, const float *X, c
   return launch_grad_dx(n, din, dout, W, src, dX, s);
 }
 
-static bool overlap(const float *a, int64_t na, const float *b, int64_t nb) {
-  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-  return a && b && x < y + sizeof(float) * (uintptr_t)nb && y < x + sizeof(float) * (uintptr_t)na;
-}
-
 // An output (or the workspace) over Y or dY: the kernels read both to the end,
 // in every workgroup, so dZ goes to the workspace first and they read that
 // (the partial gradients then have no room: one range of rows).

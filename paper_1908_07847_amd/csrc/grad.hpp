@@ -535,6 +535,12 @@ __global__ __launch_bounds__(256) void k_grad_dx(int64_t n, int din, int dout, c
 
 namespace mlph {
 
+// Whether na floats at a and nb floats at b share memory (NULL: no).
+inline bool overlap(const float *a, int64_t na, const float *b, int64_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + sizeof(float) * (uintptr_t)nb && y < x + sizeof(float) * (uintptr_t)na;
+}
+
 // Row ranges of the gradient sums: enough workgroups for about two per CU,
 // each range at least 128 rows (a set for every wave: of 160 rows one wave has
 // two while three wait, 33 -> 16 on 2300 rows 13.9 us, on ranges of 128 10.7),

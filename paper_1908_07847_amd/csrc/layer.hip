@@ -381,6 +381,11 @@ namespace mlpk {
 
 __global__ void k_fill_i32(int32_t *p, int32_t v) { *p = v; }
 
+__global__ __launch_bounds__(256) void k_copy(int64_t m, const float *__restrict__ src, float *__restrict__ dst) {
+  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q < m) dst[q] = src[q];
+}
+
 __global__ __launch_bounds__(256) void k_eval_batched(const mlp_batch_item *__restrict__ items, int D, int K,
                                                       const float *__restrict__ X, const float *__restrict__ T,
                                                       const float *__restrict__ theta, float *__restrict__ loss,
@@ -943,6 +948,23 @@ hipError_t launch_backward(int64_t n, int64_t ws_floats, int D, int H, int K, co
                            const float *A, const float *Y, const float *dY, const float *T,
                            mlp_params p, mlp_params g, float *dX, float *loss, float *ws, int act,
                            hipStream_t s) {
+  // Gradients or the loss over Y, dY or T: every workgroup reads these while
+  // others write, so a copy in the workspace takes their place (the partials
+  // get the rest of it; its size is n (H + K + 1) floats up to kBackwardChunk rows).
+  const int64_t m = n * K;
+  const struct { const float *p; int64_t n; } outs[] = {
+      {g.W1, (int64_t)D * H}, {g.b1, H}, {g.W2, (int64_t)H * K}, {g.b2, K}, {dY ? nullptr : loss, 1}};
+  for (const float **in : {&Y, &dY, &T}) {
+    bool hit = false;
+    for (const auto &o : outs) hit = hit || overlap(o.p, o.n, *in, m);
+    if (!hit || m > ws_floats || (in == &T && dY)) continue;
+    hipLaunchKernelGGL(mlpk::k_copy, grid_for(m, 256), dim3(256), 0, s, m, *in, ws);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    *in = ws;
+    ws += m;
+    ws_floats -= m;
+  }
   if (K <= 4) return backward_ko<4>(n, ws_floats, D, H, K, X, A, Y, dY, T, p, g, dX, loss, ws, act, s);
   return backward_ko<mlpk::kLayerMaxOut>(n, ws_floats, D, H, K, X, A, Y, dY, T, p, g, dX, loss, ws, act, s);
 }
