@@ -205,7 +205,8 @@ mlp_status mlp_set_wait_limit(int64_t microseconds);
  * T [n][K] (one-hot, or 0/1 for K = 1; may be NULL), correct [1] (out,
  * int32, device) receives the number of rows whose class equals the
  * target's (same rule applied to T); correct must be non-NULL iff T is.
- * Uses the parameters bound to net; X 16-byte aligned, the rest 4. */
+ * Uses the parameters bound to net; X 16-byte aligned, the rest 4.  labels
+ * and correct may lie over X or the parameters, labels over Y for K = 1. */
 mlp_status mlp_predict(mlp_net *net, const float *X, int64_t n, float *Y, int32_t *labels,
                        const float *T, int32_t *correct, void *stream);
 
@@ -272,8 +273,9 @@ mlp_status mlp_eval_batched(const mlp_batch_item *items_host, const mlp_batch_it
  * instance mlp_eval_batched's held-out losses), group [n_nets] (int32),
  * group_mean [n_groups] and best [1] are device pointers, 4-byte aligned;
  * 1 <= n_nets, 1 <= n_groups <= 65536.  A net whose group index lies outside
- * [0, n_groups) belongs to no group (the kernel cannot report it).  One or
- * two launches on the stream, no allocation. */
+ * [0, n_groups) belongs to no group (the kernel cannot report it).
+ * group_mean may lie over loss or group for n_groups <= 1024, best over
+ * either.  One or two launches on the stream, no allocation. */
 mlp_status mlp_cv_select(const float *loss, const int32_t *group, int32_t n_nets, int32_t n_groups,
                          float *group_mean, int32_t *best, void *stream);
 

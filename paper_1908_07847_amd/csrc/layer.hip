@@ -834,13 +834,14 @@ __global__ __launch_bounds__(kSelThreads) void k_cv_best(const float *__restrict
 
 __global__ __launch_bounds__(kSelThreads) void k_cv_small(const float *__restrict__ loss,
                                                           const int32_t *__restrict__ group, int n, int ng, int gpw,
-                                                          float *__restrict__ mean, int32_t *__restrict__ best) {
+                                                          float *mean, int32_t *best) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   float mv = __builtin_inff();
   int mi = 0x7fffffff;
-  for (int g0 = wave * gpw; g0 < ng; g0 += gpw * (int)(blockDim.x >> 6)) {
-    const int m = min(gpw, ng - g0), g = g0 + lane;
+  for (int g0 = wave * gpw; g0 < ng + wave * gpw; g0 += gpw * (int)(blockDim.x >> 6)) {   // as often in every wave
+    const int m = min(gpw, ng - g0), g = g0 + lane;   // (m <= 0: no group is left)
     const float v = cv_mean<2>(loss, group, n, g0, m, lane);
+    __syncthreads();   // the means may lie over what they are made of
     if (lane < m) {
       mean[g] = v;
       if (v < mv || (v == mv && g < mi)) {
@@ -862,7 +863,10 @@ hipError_t launch_cv_select(const float *loss, const int32_t *group, int n_nets,
   // few nets: one launch instead of two (64 nets, 820 groups 4.3 us on the device
   // against 5.6, 4096 groups 5.6 / 7.1; 128 nets 4.5 / 5.8, 6.4 / 7.2; with the
   // nets of a group one after the other in one wave, 256 nets gain nothing)
-  if (n_nets <= kCvSmallNets && n_groups <= kCvSmallGroups) {
+  // means over losses or groups: in one workgroup, which writes them when all are formed
+  const bool over = n_groups <= 1024 && (overlap(group_mean, n_groups, loss, n_nets) ||
+                                         overlap(group_mean, n_groups, reinterpret_cast<const float *>(group), n_nets));
+  if (over || (n_nets <= kCvSmallNets && n_groups <= kCvSmallGroups)) {
     const int waves = std::min(16, n_groups), per = std::min(64, (n_groups + waves - 1) / waves);
     hipLaunchKernelGGL(mlpk::k_cv_small, dim3(1), dim3(64 * waves), 0, s, loss, group, n_nets, n_groups, per,
                        group_mean, best);
@@ -913,15 +917,22 @@ hipError_t launch_eval_batched(const mlp_batch_item *items_dev, int n_nets, int 
 
 hipError_t launch_predict(int64_t n, int D, int H, int K, const float *X, mlp_params p, float *Y,
                           int32_t *labels, const float *T, int32_t *correct, int act, int n_cu, hipStream_t s) {
-  hipError_t e;
-  if (T) {
-    hipLaunchKernelGGL(mlpk::k_fill_i32, dim3(1), dim3(1), 0, s, correct, 0);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  if (forward_rows_covers(D, K))
-    return launch_forward_rows(n, D, H, K, X, p, nullptr, Y, mlpk::PredictOut{labels, T, correct}, act, n_cu, s);
-  e = launch_forward(n, D, H, K, X, p, nullptr, Y, act, n_cu, s);
+  auto fill = [&] {
+    if (T) hipLaunchKernelGGL(mlpk::k_fill_i32, dim3(1), dim3(1), 0, s, correct, 0);
+    return hipGetLastError();
+  };
+  // one pass unless labels or count lie over what the pass reads, or over Y:
+  // these are then written after it
+  const float *lf = reinterpret_cast<const float *>(labels), *cf = reinterpret_cast<const float *>(correct);
+  const struct { const float *p; int64_t n; } ins[] = {{X, n * D}, {Y, n * K}, {p.W1, (int64_t)D * H},
+                                                       {p.b1, H}, {p.W2, (int64_t)H * K}, {p.b2, K}};
+  bool one = forward_rows_covers(D, K);
+  for (const auto &i : ins) one = one && !overlap(lf, n, i.p, i.n) && !(T && overlap(cf, 1, i.p, i.n));
+  hipError_t e = one ? fill() : launch_forward(n, D, H, K, X, p, nullptr, Y, act, n_cu, s);
   if (e != hipSuccess) return e;
+  if (one)
+    return launch_forward_rows(n, D, H, K, X, p, nullptr, Y, mlpk::PredictOut{labels, T, correct}, act, n_cu, s);
+  if ((e = fill()) != hipSuccess) return e;
   // at most 512 blocks (rows in a grid-stride loop): one count add per block
   const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(512, (n + 255) / 256)));
   hipLaunchKernelGGL(mlpk::k_argmax, grid, dim3(256), 0, s, n, K, Y, T, labels, correct);
