@@ -841,7 +841,7 @@ __global__ __launch_bounds__(kSelThreads) void k_cv_small(const float *__restric
   for (int g0 = wave * gpw; g0 < ng + wave * gpw; g0 += gpw * (int)(blockDim.x >> 6)) {   // as often in every wave
     const int m = min(gpw, ng - g0), g = g0 + lane;   // (m <= 0: no group is left)
     const float v = cv_mean<2>(loss, group, n, g0, m, lane);
-    __syncthreads();   // the means may lie over what they are made of
+    if (ng <= kSelThreads) __syncthreads();   // one pass: the means may lie over what they are made of
     if (lane < m) {
       mean[g] = v;
       if (v < mv || (v == mv && g < mi)) {
@@ -864,7 +864,7 @@ hipError_t launch_cv_select(const float *loss, const int32_t *group, int n_nets,
   // against 5.6, 4096 groups 5.6 / 7.1; 128 nets 4.5 / 5.8, 6.4 / 7.2; with the
   // nets of a group one after the other in one wave, 256 nets gain nothing)
   // means over losses or groups: in one workgroup, which writes them when all are formed
-  const bool over = n_groups <= 1024 && (overlap(group_mean, n_groups, loss, n_nets) ||
+  const bool over = n_groups <= mlpk::kSelThreads && (overlap(group_mean, n_groups, loss, n_nets) ||
                                          overlap(group_mean, n_groups, reinterpret_cast<const float *>(group), n_nets));
   if (over || (n_nets <= kCvSmallNets && n_groups <= kCvSmallGroups)) {
     const int waves = std::min(16, n_groups), per = std::min(64, (n_groups + waves - 1) / waves);
